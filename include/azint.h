@@ -226,7 +226,10 @@ int azi_plan_export_csc(const azi_plan* plan, void* data, int32_t* bins, int32_t
  *   tile_nnz  most nonzeros one workgroup sums per tile (64..16384, a
  *             multiple of 64); rows longer than that are cut into pieces
  *             whose sums are added in order by a small fix-up kernel.
- *             0: sized by the library.  Run layout with band 16 or 32
+ *             0: sized by the library.  One-dimensional plans and batches in
+ *             the run layout with band 16 and grid 0 then take the stream
+ *             encoding (see AZI_LAYOUT_RUN), whose tiles are cut from the
+ *             image's size.  Otherwise, run layout with band 16 or 32
  *             (one-dimensional or 2-D plans): each group of bands' common
  *             stretches are cut so that no band has more than a bound of
  *             runs in one, the stretches of a group as even as their number
@@ -234,7 +237,7 @@ int azi_plan_export_csc(const azi_plan* plan, void* data, int32_t* bins, int32_t
  *             within k rounds of what the device holds at once (CUs x 8 for
  *             band 16, x 4 for band 32), k the fewest rounds whose bound is
  *             2048 runs or less: every resident workgroup takes about the
- *             same work.  Other layouts, and every layout of a batch: 2048
+ *             same work.  Other layouts, and batches in the run encoding: 2048
  *             below 2^22 nonzeros (of the instance, in a batch), else 4096.
  *   block     threads per workgroup: 64, 128, 256 or 512.
  *   variant   load scheme, 0..AZI_NUM_VARIANTS-1: 0 four consecutive
@@ -327,7 +330,8 @@ int azi_plan_get_tiling(const azi_plan* plan, azi_tiling* tiling, int32_t* ntile
 int azi_plan_tile_schedule(const azi_plan* plan, const azi_tiling* tiling, int32_t* ntiles,
                            int32_t* tiles, int32_t* nsplits, int32_t* splits);
 
-/* Host-side view of the run encoding (AZI_LAYOUT_RUN) of a one-dimensional
+/* Host-side view of the run encoding (AZI_LAYOUT_RUN; the device may hold the
+ * stream encoding in its place) of a one-dimensional
  * or 2-D plan's matrix with pieces of tile_nnz / 2 runs (tile_nnz 0: sized
  * as the tiling's tile_nnz 0 sizes them on the plan's device, or on 256 CUs
  * for a plan without one; no device needed;
@@ -395,6 +399,17 @@ int azi_plan_run_schedule(const azi_plan* plan, int32_t tile_nnz, int64_t* nruns
  * gives 128-thread workgroups (for batches of small images), any other
  * value 256.  Images up to 2^27 pixels; a batch up to 2^31 runs and
  * entries.
+ * With the tiling sized by the library (tile_nnz 0, band 16, grid 0) the
+ * matrix of a one-dimensional plan or batch is stored in the stream encoding
+ * instead: image tiles of up to 3072 pixels, one 16-bit word per pixel (its
+ * first bin within the tile's bins, and its number of bins), the pixel's
+ * coefficients in the order they are read, every workgroup adding its tile's
+ * products into bins kept in LDS.  The frame is read once, in order.  Plans
+ * it does not serve keep the run encoding: under four pixels, more than 63
+ * bins in one pixel, bins so fine that a tile would hold under 192 pixels on
+ * average, more than 8 MiB of partial sums (a batch: one instance of these, or
+ * positions past 2^31).  The per-run dark values of AZI_STAGE_FOLD are
+ * per-pixel ones there, in the same types.
  * Set before azi_plan_upload (a later call re-uploads).  AZI_ESTATE once
  * corrections are set on an uploaded plan.  A refused or failed call leaves
  * the plan in its previous layout (if the re-upload of the new layout fails,
@@ -485,8 +500,9 @@ int azi_integrate1d_raw(const azi_plan* plan, const void* raw, int32_t raw_dtype
  *   image) give AZI_EINVAL.
  *   Limit: a plan whose partial sums exceed the array (16 bytes per slot:
  *   4 slots per band piece, one per (tile, bin) of the tile and fused
- *   layouts) gives AZI_EINVAL; at the default tiling a ~1e7-pixel frame
- *   with 3162 bins needs about 0.5 MB.
+ *   layouts; 8 bytes per (tile, bin) of the stream encoding) gives
+ *   AZI_EINVAL; at the default tiling a ~1e7-pixel frame with 3162 bins needs
+ *   about 2.8 MB.
  *   Sharing: all calls on one device share its array and every call
  *   overwrites what it needs before reading it, so sequential calls, on one
  *   stream or ordered by events, are safe; calls that overlap in time on

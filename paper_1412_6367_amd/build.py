@@ -21,7 +21,9 @@ ARCH = os.environ.get("AZINT_OFFLOAD_ARCH", "gfx950")
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument"]
-HIP_SOURCES = ("kernels.hip", "azint_api.hip", "plan_device.hip", "fused.hip")
+HIP_SOURCES = ("kernels.hip", "azint_api.hip", "plan_device.hip", "fused.hip", "stream.hip",
+               "stream_f64.hip", "stream_f32.hip", "stream_k32.hip")
+HOST_SOURCES = ("plan_builder.cpp", "stream_builder.cpp")
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
               "-Wall", "-Wextra"]
 
@@ -46,9 +48,10 @@ def _run(cmd, verbose):
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     hipcc = _hipcc()
-    host = os.path.join(BUILD, "plan_builder.o")
-    steps = [(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, "plan_builder.cpp"), "-o", host],
-              host)]
+    steps = []
+    for name in HOST_SOURCES:
+        obj = os.path.join(BUILD, name.replace(".cpp", ".o"))
+        steps.append((["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, name), "-o", obj], obj))
     for name in HIP_SOURCES:
         obj = os.path.join(BUILD, name.replace(".hip", ".o"))
         # the device plan builder and the matrix-free kernel decide bin

@@ -11,11 +11,13 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
 #include "kernels.h"
 #include "plan_device.h"
+#include "stream.h"
 #include "fused.h"
 
 namespace {
@@ -233,6 +235,138 @@ int upload_first(const azi::HostMatrix& m, int device, DevBuf& buf) {
     return AZI_OK;
 }
 
+// Partial sums of azi_integrate1d_raw_noalloc (a static array per device).
+constexpr size_t kScratchBytes = (size_t)8 << 20;
+
+// The stream encoding of a plan or batch on its device: the host-built
+// arrays in one allocation, the work arrays in a second.
+struct StreamBufs {
+    DevBuf built, work;
+    const azi::StreamTile* tiles = nullptr;
+    const azi::StreamChunk* chunks = nullptr;
+    const azi::StreamEnt* ents = nullptr;
+    const int32_t* gbase = nullptr;
+    const uint16_t* words = nullptr;
+    double* ufix = nullptr;   // U of every bin
+    void* parts = nullptr;    // 8 bytes per partial sum
+    void* coef = nullptr;     // storage type
+    int32_t ntiles = 0, nchunks = 0, max_count = 0;
+    int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
+    bool on = false;
+    void release() {
+        built.release();
+        work.release();
+        on = false;
+    }
+    int64_t bytes() const { return (int64_t)(built.bytes + work.bytes); }
+};
+
+// Pixels per stream tile.  One round of the 2048 workgroups that 256 CUs keep
+// resident, but at least 1024 (four blocks of 256, one for each wavefront) and
+// at most 3072 (three for each): 512, 1024 and 2048 at 1043 x 981 float32
+// Kahan 15.1, 14.7 and 14.8 us a pass; 1536, 2560, 3072 and 4096 at 3162 x
+// 3163 float64 60.3, 54.8, 53.3 and 53.1 us, float32 in 1000 bins 31.9, 31.2,
+// 30.9 and 32.2 us.
+int32_t stream_tile_px(int64_t npix) {
+    return (int32_t)std::max<int64_t>(1024, std::min<int64_t>(3072, npix / 2048));
+}
+
+// The run layout's tilings sized by the library (tile_nnz 0, four bands per
+// workgroup, no persistent grid) take the stream encoding where it applies.
+bool stream_tiling(const azi_tiling& t) {
+    return t.tile_nnz == 0 && t.band == 16 && t.grid == 0;
+}
+
+azi::StreamLaunch stream_args(const StreamBufs& b, const void* img, int32_t img_dtype,
+                              int64_t npix, void* I, void* W, void* U, double empty, int32_t dtype,
+                              int32_t accum) {
+    azi::StreamLaunch a;
+    a.npix = npix;
+    a.tiles = b.tiles;
+    a.ntiles = b.ntiles;
+    a.words = b.words;
+    a.gbase = b.gbase;
+    a.coef = b.coef;
+    a.chunks = b.chunks;
+    a.nchunks = b.nchunks;
+    a.ents = b.ents;
+    a.ents_per_chunk = b.ents_per_chunk;
+    a.max_count = b.max_count;
+    a.img = img;
+    a.img_dtype = img_dtype;
+    a.parts = b.parts;
+    a.I = I;
+    a.W = W;
+    a.U = U;
+    a.empty = empty;
+    a.dtype = dtype;
+    a.accum = accum;
+    a.ufix = b.ufix;
+    return a;
+}
+
+azi::StreamCoefLaunch stream_coef_args(const StreamBufs& b, const DevBuf& colptr, const void* src,
+                                       void* coef, int32_t dtype) {
+    azi::StreamCoefLaunch c;
+    c.tiles = b.tiles;
+    c.ntiles = b.ntiles;
+    c.words = b.words;
+    c.gbase = b.gbase;
+    c.colptr = colptr.as<int32_t>();
+    c.src = src;
+    c.coef = coef;
+    c.dtype = dtype;
+    return c;
+}
+
+// Places a stream encoding on the device; its coefficients are gathered from
+// the pixel-major entries there (colptr, cdata), and the U of its npt bins,
+// which no frame changes, is summed once from them (the kernels over the unit
+// image, the same order as W).
+int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32_t accum,
+                  int device, const DevBuf& colptr, const DevBuf& cdata, StreamBufs& b) {
+    b.release();
+    std::vector<char> host;
+    auto put = [&host](const auto& v) {
+        const size_t at = host.size(), n = v.size() * sizeof(v[0]);
+        host.resize(at + round_up((int64_t)n, 16));
+        if (n) std::memcpy(host.data() + at, v.data(), n);
+        return at;
+    };
+    const size_t tiles = put(sm.tiles), chunks = put(sm.chunks), ents = put(sm.ents),
+                 gbase = put(sm.gbase), words = put(sm.words);
+    AZI_HIP(b.built.upload(host.data(), host.size(), device), "stream encoding");
+    const char* d = b.built.as<char>();
+    b.tiles = reinterpret_cast<const azi::StreamTile*>(d + tiles);
+    b.chunks = reinterpret_cast<const azi::StreamChunk*>(d + chunks);
+    b.ents = reinterpret_cast<const azi::StreamEnt*>(d + ents);
+    b.gbase = reinterpret_cast<const int32_t*>(d + gbase);
+    b.words = reinterpret_cast<const uint16_t*>(d + words);
+    const size_t nu = (size_t)round_up(npt * 8, 256);
+    const size_t np = (size_t)round_up(sm.nparts * 8, 256);
+    AZI_HIP(b.work.alloc(nu + np + (size_t)(sm.ncoef + kPad) * elem_size(dtype), device),
+            "stream sums and coefficients");
+    b.ufix = b.work.as<double>();
+    b.parts = b.work.as<char>() + nu;
+    b.coef = b.work.as<char>() + nu + np;
+    b.ntiles = (int32_t)sm.tiles.size();
+    b.nchunks = (int32_t)sm.chunks.size();
+    b.max_count = sm.max_count;
+    b.ncoef = sm.ncoef;
+    b.nparts = sm.nparts;
+    b.ents_per_chunk = (int64_t)(sm.ents.size() / std::max<size_t>(sm.chunks.size(), 1));
+    AZI_HIP(azi::launch_stream_coef(stream_coef_args(b, colptr, cdata.p, b.coef, dtype), nullptr),
+            "stream coefficients");
+    azi::StreamLaunch a = stream_args(b, nullptr, dtype, 0, nullptr, nullptr, nullptr, 0.0, dtype,
+                                      accum);
+    a.corr_kind = azi::kStreamOnes;
+    a.wfix_out = b.ufix;
+    AZI_HIP(azi::launch_stream(a, nullptr), "fixed U");
+    AZI_HIP(hipStreamSynchronize(nullptr), "stream encoding");
+    b.on = true;
+    return AZI_OK;
+}
+
 }  // namespace
 
 struct azi_plan {
@@ -248,6 +382,7 @@ struct azi_plan {
         bparts, npieces_buf, npacked, ncoef, bin_slot, bin_count, nparts_buf, ftiles, fslots,
         fbin_ptr, fparts, corr, cfirst, rgbase, fcoef, ufix, wdark;
     int32_t nstiles = 0, nbtiles = 0, npieces = 0, band_rows = 8, nftiles = 0;
+    StreamBufs stream;    // run layout, library-sized tilings: replaces the run encoding
     bool folded = false;  // run layout, AZI_STAGE_FOLD(_SUM), corrections set
     int32_t max_count = INT32_MAX;  // largest number of band partials of a bin
     int32_t corr_kind = azi::kCorrPair;
@@ -267,6 +402,10 @@ struct azi_batch {
     DevBuf rp, indices, data, colptr, rowidx, cdata, tiles, splits, parts, vwork, order, xwork, pos,
         stiles, lidx, dest, btiles, brows, blp, bcoef, bin_ptr, bparts, npieces_buf, npacked, ncoef,
         bin_slot, bin_count, nparts_buf, cfirst, rgbase;
+    StreamBufs stream;  // as in a plan
+    std::vector<std::pair<int32_t, int32_t>> hw;  // image shape of instance k
+    std::vector<char> two_d;                      // instance k is two-dimensional
+    std::vector<int64_t> stream_off, chunk_off;   // stream tiles, chunks of instance k
     int32_t nbtiles = 0, npieces = 0, band_rows = 8;
     int32_t max_count = INT32_MAX;  // largest number of band partials of a bin
     std::vector<int64_t> cz_off;     // CSC entries of instance k
@@ -411,8 +550,38 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
     return AZI_OK;
 }
 
+// The stream encoding of a plan whose tiling asks for it; *done is false
+// where it does not apply (two-dimensional plans, bins too fine, partial
+// sums beyond the allocation-free call's array): the run encoding then
+// serves.
+int plan_upload_stream(azi_plan* p, bool* done) {
+    *done = false;
+    p->stream.release();
+    if (p->layout != AZI_LAYOUT_RUN || !stream_tiling(p->tiling)) return AZI_OK;
+    try {
+        azi::StreamMatrix sm;
+        if (!azi::build_stream(p->m, p->geom.h, p->geom.w, stream_tile_px(p->m.npix), 0, 0, sm) ||
+            (size_t)sm.nparts * 8 > kScratchBytes)
+            return AZI_OK;
+        const int rc = upload_stream(sm, p->m.npt, p->dtype, p->accum, p->device, p->colptr,
+                                     p->cdata, p->stream);
+        if (rc != AZI_OK) return rc;
+    } catch (const std::bad_alloc&) {
+        return fail(AZI_ENOMEM, "out of host memory building the stream encoding");
+    }
+    for (DevBuf* b : {&p->npieces_buf, &p->npacked, &p->ncoef, &p->bin_slot, &p->bin_count,
+                      &p->nparts_buf})
+        b->release();
+    p->npieces = 0;
+    *done = true;
+    return AZI_OK;
+}
+
 int plan_upload_bands(azi_plan* p) {
     p->rgbase.release();
+    bool streamed = false;
+    const int rcs = plan_upload_stream(p, &streamed);
+    if (rcs != AZI_OK || streamed) return rcs;
     if (p->layout == AZI_LAYOUT_RUN) {
         try {
             azi::RunMatrix rm;
@@ -505,6 +674,38 @@ azi::BandLaunch plan_band_raw_args(const azi_plan* p, const void* raw, int32_t r
         }
     }
     return a;
+}
+
+// An image already corrected (storage type), over the band, run or stream
+// encoding.
+hipError_t plan_launch_image(const azi_plan* p, const void* x, void* I, void* W, void* U,
+                             double empty, hipStream_t s) {
+    if (p->stream.on)
+        return azi::launch_stream(
+            stream_args(p->stream, x, p->dtype, p->m.npix, I, W, U, empty, p->dtype, p->accum), s);
+    return azi::launch_band(plan_band_args(p, x, I, W, U, empty), s);
+}
+
+// A raw frame (see plan_band_raw_args); `parts` replaces the plan's own
+// partial sums when set.
+hipError_t plan_launch_raw(const azi_plan* p, const void* raw, int32_t raw_dtype, void* I, void* W,
+                           void* U, double empty, void* parts, hipStream_t s) {
+    if (p->stream.on) {
+        azi::StreamLaunch a =
+            stream_args(p->stream, raw, raw_dtype, p->m.npix, I, W, U, empty, p->dtype, p->accum);
+        if (p->folded && p->fcoef.p) a.coef = p->fcoef.p;
+        if (p->folded && p->wdark.p) {
+            a.wsub = p->wdark.as<double>();
+        } else if (p->corr.p) {
+            a.corr = p->corr.p;
+            a.corr_kind = p->corr_kind;
+        }
+        if (parts) a.parts = parts;
+        return azi::launch_stream(a, s);
+    }
+    azi::BandLaunch a = plan_band_raw_args(p, raw, raw_dtype, I, W, U, empty);
+    if (parts) a.parts = parts;
+    return azi::launch_band(a, s);
 }
 
 azi::BlockLaunch plan_block_args(const azi_plan* p, const void* img, int32_t img_dtype,
@@ -604,7 +805,64 @@ int download_as_double(const DevBuf& src, int64_t n, std::vector<double>& out, h
     return AZI_OK;
 }
 
+// The folded stages over the stream encoding, on the device: the same
+// coefficients (the doubles times 1 / norm, rounded once), the dark value per
+// pixel (the image's order) instead of per run, D in the per-frame order.
+int plan_fold_stream(azi_plan* p, hipStream_t s) {
+    const int64_t npix = p->m.npix;
+    const StreamBufs& b = p->stream;
+    const bool sum_dark = p->tiling.stage == AZI_STAGE_FOLD_SUM && p->accum == AZI_ACC_F64;
+    if (p->has_norm) {
+        DevBuf exact;  // float32 plans: the double coefficients
+        AZI_HIP(p->fcoef.alloc((size_t)(b.ncoef + kPad) * elem_size(p->dtype), p->device),
+                "folded coefficients");
+        azi::StreamCoefLaunch c =
+            stream_coef_args(b, p->colptr, p->cdata.p, p->fcoef.p, p->dtype);
+        if (p->dtype != AZI_F64) {
+            AZI_HIP(exact.upload(p->m.cdata.data(), p->m.cdata.size() * 8, p->device),
+                    "exact coefficients");
+            c.src = exact.p;
+            c.src_f64 = true;
+        }
+        c.norm = p->norm.p;
+        AZI_HIP(azi::launch_stream_coef(c, s), "folded coefficients");
+        AZI_HIP(hipStreamSynchronize(s), "folded coefficients");
+    }
+    p->corr_kind = azi::kCorrRunDark;
+    if (p->has_dark && sum_dark) {
+        AZI_HIP(p->wdark.alloc((size_t)p->m.npt * 8, p->device), "fixed dark term");
+        azi::StreamLaunch d = stream_args(b, p->dark.p, p->dtype, npix, nullptr, nullptr, nullptr,
+                                          0.0, p->dtype, p->accum);
+        if (p->fcoef.p) d.coef = p->fcoef.p;
+        d.wfix_out = p->wdark.as<double>();
+        AZI_HIP(azi::launch_stream(d, s), "fixed dark term");
+    } else if (p->has_dark) {
+        // uint16, float or the storage type, as for the run encoding
+        DevBuf flags;
+        int32_t kind = 3;
+        AZI_HIP(flags.alloc(4, p->device), "dark check");
+        AZI_HIP(azi::launch_dark_kind(p->dark.p, p->dtype, npix, flags.as<int32_t>(), s),
+                "dark check");
+        AZI_HIP(hipMemcpyAsync(&kind, flags.p, 4, hipMemcpyDeviceToHost, s), "dark check");
+        AZI_HIP(hipStreamSynchronize(s), "dark check");
+        size_t bytes = elem_size(p->dtype);
+        if (!(kind & 1)) {
+            p->corr_kind = azi::kCorrRunDarkU16;
+            bytes = 2;
+        } else if (!(kind & 2) && p->dtype == AZI_F64) {
+            p->corr_kind = azi::kCorrRunDarkF32;
+            bytes = 4;
+        }
+        AZI_HIP(p->corr.alloc((size_t)npix * bytes, p->device), "dark values");
+        AZI_HIP(azi::launch_dark_store(p->dark.p, p->dtype, p->corr_kind, p->corr.p, npix, s),
+                "dark values");
+    }
+    AZI_HIP(hipStreamSynchronize(s), "folded corrections");
+    return AZI_OK;
+}
+
 int plan_fold(azi_plan* p, hipStream_t s) {
+    if (p->stream.on) return plan_fold_stream(p, s);
     const int64_t npix = p->m.npix;
     const bool sum_dark = p->tiling.stage == AZI_STAGE_FOLD_SUM && p->accum == AZI_ACC_F64;
     try {
@@ -1184,7 +1442,8 @@ int azi_plan_export_csc(const azi_plan* p, void* data, int32_t* bins, int32_t* c
 int azi_plan_set_tiling(azi_plan* p, const azi_tiling* t) {
     if (!p || !t) return fail(AZI_EINVAL, "plan and tiling must not be NULL");
     if (!valid_tiling(*t)) return fail(AZI_EINVAL, kTilingRule);
-    const bool retile = t->tile_nnz != p->tiling.tile_nnz || t->band != p->tiling.band;
+    const bool retile = t->tile_nnz != p->tiling.tile_nnz || t->band != p->tiling.band ||
+                        stream_tiling(*t) != stream_tiling(p->tiling);
     const bool restage = t->stage != p->tiling.stage;
     const bool reblock = t->block != p->tiling.block;
     p->tiling = *t;
@@ -1367,6 +1626,7 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
         }
         AZI_HIP(p->xwork.alloc((size_t)p->m.npix * es, device), "work image");
         AZI_HIP(p->vwork.alloc((size_t)(p->m.npt + kAdjPad) * 8, device), "work vector");
+        p->stream.release();
         if (is_band(p->layout)) {
             int rc2 = plan_upload_bands(p);
             if (rc2 != AZI_OK) return rc2;
@@ -1415,7 +1675,7 @@ int64_t azi_plan_device_bytes(const azi_plan* p) {
                             &p->btiles, &p->brows, &p->blp, &p->bcoef, &p->bin_ptr,
                             &p->bparts, &p->npieces_buf, &p->npacked, &p->ncoef, &p->bin_slot,
                             &p->bin_count, &p->nparts_buf};
-    int64_t s = 0;
+    int64_t s = p->stream.bytes();
     for (const DevBuf* b : bufs) s += (int64_t)b->bytes;
     return s;
 }
@@ -1498,7 +1758,7 @@ int azi_integrate1d(const azi_plan* p, const void* x, void* I, void* W, void* U,
         return AZI_OK;
     }
     if (is_band(p->layout)) {
-        AZI_HIP(azi::launch_band(plan_band_args(p, x, I, W, U, empty), s), "band forward kernels");
+        AZI_HIP(plan_launch_image(p, x, I, W, U, empty, s), "band forward kernels");
         return AZI_OK;
     }
     const void* xin = x;
@@ -1549,8 +1809,7 @@ int azi_integrate1d_staged(const azi_plan* p, void* I, void* W, void* U, double 
         return AZI_OK;
     }
     if (is_band(p->layout)) {
-        AZI_HIP(azi::launch_band(plan_band_args(p, p->xwork.p, I, W, U, empty),
-                                 static_cast<hipStream_t>(stream)),
+        AZI_HIP(plan_launch_image(p, p->xwork.p, I, W, U, empty, static_cast<hipStream_t>(stream)),
                 "band forward kernels");
         return AZI_OK;
     }
@@ -1591,8 +1850,8 @@ int azi_integrate1d_raw(const azi_plan* p, const void* raw, int32_t raw_dtype, v
         if (!valid_raw_dtype(raw_dtype)) return fail(AZI_EINVAL, "unknown raw dtype");
         DeviceGuard g(p->device);
         if (g.err != hipSuccess) return hip_fail(g.err, "set device");
-        AZI_HIP(azi::launch_band(plan_band_raw_args(p, raw, raw_dtype, I, W, U, empty),
-                                 static_cast<hipStream_t>(stream)),
+        AZI_HIP(plan_launch_raw(p, raw, raw_dtype, I, W, U, empty, nullptr,
+                                static_cast<hipStream_t>(stream)),
                 "band forward kernels");
         return AZI_OK;
     }
@@ -1608,7 +1867,6 @@ namespace {
 // Partial sums of azi_integrate1d_raw_noalloc.  Each device that loads the
 // library holds its own copy until the process ends; host code reaches it
 // only through the address hipGetSymbolAddress returns for that device.
-constexpr size_t kScratchBytes = (size_t)8 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxScratchDevices = 64;
@@ -1645,7 +1903,8 @@ int azi_integrate1d_raw_noalloc(const azi_plan* p, const void* raw, int32_t raw_
     if (!valid_raw_dtype(raw_dtype)) return fail(AZI_EINVAL, "unknown raw dtype");
     // the layouts whose raw-frame path needs partial sums and nothing else
     size_t need = 0;
-    if (is_band(p->layout) && gather_corrects(p->tiling.stage)) need = p->nparts_buf.bytes;
+    if (is_band(p->layout) && gather_corrects(p->tiling.stage))
+        need = p->stream.on ? (size_t)p->stream.nparts * 8 : p->nparts_buf.bytes;
     else if (p->layout == AZI_LAYOUT_TILE) need = p->bparts.bytes;
     else if (p->layout == AZI_LAYOUT_FUSED) need = p->fparts.bytes;
     else
@@ -1671,9 +1930,8 @@ int azi_integrate1d_raw_noalloc(const azi_plan* p, const void* raw, int32_t raw_
         a.parts = parts;
         AZI_HIP(azi::launch_block(a, s), "blocked forward kernels");
     } else {
-        azi::BandLaunch a = plan_band_raw_args(p, raw, raw_dtype, I, W, U, empty);
-        a.parts = parts;
-        AZI_HIP(azi::launch_band(a, s), "band forward kernels");
+        AZI_HIP(plan_launch_raw(p, raw, raw_dtype, I, W, U, empty, parts, s),
+                "band forward kernels");
     }
     return AZI_OK;
 }
@@ -1787,12 +2045,6 @@ int azi_batch_create(azi_plan* const* plans, int32_t n, int32_t device, azi_batc
                 b->rp_host[b->ip_off[k] + r] = m.indptr[r] + (int32_t)z0;
         }
         b->cz_off = cz_off;
-        if (is_band(b->layout)) {
-            std::vector<const azi::HostMatrix*> ms(n);
-            for (int32_t k = 0; k < n; ++k) ms[k] = &plans[k]->m;
-            int rc2 = batch_build_bands(b.get(), ms);
-            if (rc2 != AZI_OK) return rc2;
-        }
         if (b->layout == AZI_LAYOUT_TILE) {
             azi::BlockMatrix bm;
             b->btile_off.assign(n + 1, 0);
@@ -1853,6 +2105,17 @@ int azi_batch_create(azi_plan* const* plans, int32_t n, int32_t device, azi_batc
         if ((int64_t)first.size() == b->npix)
             AZI_HIP(b->cfirst.upload(first.data(), first.size() * 4, device), "first bins");
         AZI_HIP(b->cdata.upload(cdat.data(), cdat.size(), device), "cdata");
+        std::vector<char>().swap(cdat);
+        for (int32_t k = 0; k < n; ++k) {
+            b->hw.emplace_back(plans[k]->geom.h, plans[k]->geom.w);
+            b->two_d.push_back(plans[k]->m.two_d);
+        }
+        if (is_band(b->layout)) {
+            std::vector<const azi::HostMatrix*> ms(n);
+            for (int32_t k = 0; k < n; ++k) ms[k] = &plans[k]->m;
+            int rc2 = batch_build_bands(b.get(), ms);
+            if (rc2 != AZI_OK) return rc2;
+        }
         AZI_HIP(b->vwork.alloc((size_t)(b->npt + kAdjPad) * 8, device), "work vector");
         std::vector<std::vector<int32_t>> store;
         std::vector<const int32_t*> ptrs;
@@ -1890,11 +2153,12 @@ int azi_batch_set_tiling(azi_batch* b, const azi_tiling* t) {
     DeviceGuard g(b->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
     const bool retile =
-        t->tile_nnz != b->tiling.tile_nnz || t->band != b->tiling.band || b->ntiles == 0;
+        t->tile_nnz != b->tiling.tile_nnz || t->band != b->tiling.band || b->ntiles == 0 ||
+        stream_tiling(*t) != stream_tiling(b->tiling);
     b->tiling = *t;
     if (retile) {
         AZI_HIP(hipDeviceSynchronize(), "synchronise before retiling");
-        if (is_band(b->layout) && b->npieces_buf.p) {
+        if (is_band(b->layout) && (b->npieces_buf.p || b->stream.on)) {
             int rc = batch_rebuild_bands(b);
             if (rc != AZI_OK) return rc;
         }
@@ -1920,8 +2184,64 @@ namespace {
 
 // Brings a batch's images into its work image (ring positions, or a cast
 // copy), instance range [k0, k1) only.
+// The stream encoding of a batch whose tiling asks for it, each instance's
+// tiles and chunks after the other's; *done is false where an instance does
+// not take it.
+int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& ms, bool* done) {
+    *done = false;
+    b->stream.release();
+    if (b->layout != AZI_LAYOUT_RUN || !stream_tiling(b->tiling)) return AZI_OK;
+    azi::StreamMatrix sm;
+    const int32_t px = stream_tile_px(b->npix);
+    b->stream_off.assign(b->n + 1, 0);
+    b->chunk_off.assign(b->n + 1, 0);
+    for (int32_t k = 0; k < b->n; ++k) {
+        if (b->two_d[k] || !azi::build_stream(*ms[k], b->hw[k].first, b->hw[k].second, px,
+                                              b->pix_off[k], b->bin_off[k], sm))
+            return AZI_OK;
+        b->stream_off[k + 1] = (int64_t)sm.tiles.size();
+        b->chunk_off[k + 1] = (int64_t)sm.chunks.size();
+    }
+    const int rc = upload_stream(sm, b->npt, b->dtype, b->accum, b->device, b->colptr, b->cdata,
+                                 b->stream);
+    if (rc != AZI_OK) return rc;
+    for (DevBuf* d : {&b->npieces_buf, &b->npacked, &b->ncoef, &b->bin_slot, &b->bin_count,
+                      &b->nparts_buf})
+        d->release();
+    b->npieces = 0;
+    *done = true;
+    return AZI_OK;
+}
+
+// Instances [k0, k1) of a batch's images (img_dtype, flat over the whole
+// batch) over the band, run or stream encoding.
+azi::BandLaunch batch_band_args(const azi_batch* b, const void* x, int32_t k0, int32_t k1,
+                                void* I, void* W, void* U, double empty);
+hipError_t batch_launch(const azi_batch* b, const void* img, int32_t img_dtype, bool raw,
+                        int32_t k0, int32_t k1, void* I, void* W, void* U, double empty,
+                        hipStream_t s) {
+    if (b->stream.on) {
+        azi::StreamLaunch a =
+            stream_args(b->stream, img, img_dtype, b->npix, I, W, U, empty, b->dtype, b->accum);
+        a.tiles += b->stream_off[k0];
+        a.ntiles = (int32_t)(b->stream_off[k1] - b->stream_off[k0]);
+        a.chunks += b->chunk_off[k0];
+        a.nchunks = (int32_t)(b->chunk_off[k1] - b->chunk_off[k0]);
+        return azi::launch_stream(a, s);
+    }
+    azi::BandLaunch a = batch_band_args(b, raw ? nullptr : img, k0, k1, I, W, U, empty);
+    if (raw) {
+        a.raw = img;
+        a.raw_dtype = img_dtype;
+    }
+    return azi::launch_band(a, s);
+}
+
 int batch_build_bands(azi_batch* b, const std::vector<const azi::HostMatrix*>& ms) {
     b->rgbase.release();
+    bool streamed = false;
+    const int rcs = batch_build_stream(b, ms, &streamed);
+    if (rcs != AZI_OK || streamed) return rcs;
     if (b->layout == AZI_LAYOUT_RUN) {
         azi::RunMatrix rm;
         b->band_rows = azi::kRunRows;
@@ -2113,7 +2433,7 @@ int azi_batch_forward(azi_batch* b, const void* x, void* I, void* W, void* U, do
         return AZI_OK;
     }
     if (is_band(b->layout)) {
-        AZI_HIP(azi::launch_band(batch_band_args(b, x, 0, b->n, I, W, U, empty), s),
+        AZI_HIP(batch_launch(b, x, b->dtype, false, 0, b->n, I, W, U, empty, s),
                 "batched band kernels");
         return AZI_OK;
     }
@@ -2142,16 +2462,14 @@ int azi_batch_forward_raw(azi_batch* b, const void* raw, int32_t raw_dtype, void
         return AZI_OK;
     }
     if (is_band(b->layout) && gather_corrects(b->tiling.stage)) {
-        azi::BandLaunch a = batch_band_args(b, nullptr, 0, b->n, I, W, U, empty);
-        a.raw = raw;
-        a.raw_dtype = raw_dtype;
-        AZI_HIP(azi::launch_band(a, s), "batched band kernels");
+        AZI_HIP(batch_launch(b, raw, raw_dtype, true, 0, b->n, I, W, U, empty, s),
+                "batched band kernels");
         return AZI_OK;
     }
     int rc = batch_stage(b, raw, raw_dtype, 0, b->n, s);
     if (rc != AZI_OK) return rc;
     if (is_band(b->layout)) {
-        AZI_HIP(azi::launch_band(batch_band_args(b, b->xwork.p, 0, b->n, I, W, U, empty), s),
+        AZI_HIP(batch_launch(b, b->xwork.p, b->dtype, false, 0, b->n, I, W, U, empty, s),
                 "batched band kernels");
         return AZI_OK;
     }
@@ -2175,7 +2493,7 @@ int azi_batch_forward_loop(azi_batch* b, const void* x, void* I, void* W, void* 
     }
     if (is_band(b->layout)) {
         for (int32_t k = 0; k < b->n; ++k)
-            AZI_HIP(azi::launch_band(batch_band_args(b, x, k, k + 1, I, W, U, empty), s),
+            AZI_HIP(batch_launch(b, x, b->dtype, false, k, k + 1, I, W, U, empty, s),
                     "per-instance band kernels");
         return AZI_OK;
     }
@@ -2237,8 +2555,10 @@ int azi_batch_autotune(azi_batch* b, const void* x, void* I, void* W, void* U, v
     std::vector<azi_tiling> cands;
     const int32_t st = b->tiling.stage;
     if (b->layout == AZI_LAYOUT_RUN) {
-        // bands of 4 bins are fixed for runs; one band per workgroup of 128
-        // or 256 threads, or four neighbouring bands per workgroup (band 16)
+        // the tiling sized by the library (stream encoding); else bands of 4
+        // bins, one band per workgroup of 128 or 256 threads, or four
+        // neighbouring bands per workgroup (band 16)
+        cands.push_back(azi_tiling{0, 256, 5, 0, 16, st});
         for (int32_t tn : {1024, 2048, 4096, 8192, 16384}) {
             for (int32_t bl : {128, 256})
                 for (int32_t gm : {0, 4, 8, 16})
@@ -2273,7 +2593,8 @@ int azi_batch_autotune(azi_batch* b, const void* x, void* I, void* W, void* U, v
 
         rc = azi_batch_set_tiling(b, &cand);
         if (rc != AZI_OK) break;
-        const int32_t units = is_band(b->layout)             ? b->npieces
+        const int32_t units = b->stream.on                   ? b->stream.ntiles
+                              : is_band(b->layout)           ? b->npieces
                               : b->layout == AZI_LAYOUT_TILE ? b->nbtiles
                                                              : b->ntiles;
         if (cand.grid > 0 && cand.grid >= units) continue;  // same as one per unit

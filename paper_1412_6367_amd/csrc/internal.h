@@ -217,6 +217,77 @@ bool build_runs(const HostMatrix& m, int32_t piece_runs, int64_t pix_off, int64_
                 RunMatrix& rm, const double* scale = nullptr, int32_t waves = 1,
                 int64_t round_tiles = 0);
 
+// Stream encoding of a one-dimensional matrix whose pixels' bins are
+// consecutive: the image cut into tiles (column strips of up to 64 pixels,
+// cut into rows), the tile's pixels taken in blocks of 256: 64 lanes of four
+// neighbouring pixels of a row each, so that a lane reads its words and its
+// pixels with one load.  A block is 2^lgw lanes across and 2^(6 - lgw) rows
+// down; lanes are numbered along the rows or (kStreamRowsMinor) down the
+// columns; blocks follow each other along the tile's rows, pixels past the
+// tile's edge hold nothing.  A pixel has one 16-bit word, its first bin within
+// the tile's bin window | number of bins << kStreamCountShift (0: feeds no
+// bin), at words[word0 + 256 * block + 4 * lane + k] for the lane's k-th pixel.
+// The coefficients of block g start at gbase[g]: those of the lanes' first
+// pixels, slot-major (the first coefficient of each lane that has one in lane
+// order, then the second of those that have one, and so on), then those of
+// the lanes' second pixels, third and fourth.
+//
+// A wavefront adds a block's products pixel by pixel of the lanes to its own
+// copies of the window in LDS; lane l adds to copy l & (2^lk - 1), lk the
+// smallest for which no two lanes that share a copy have the same first bin in
+// the same pixel of the lane: no two lanes of one LDS access then meet in one
+// bin, so the sums need no atomics and have one order.  The block's shape is
+// chosen per tile for few copies: lanes numbered across the direction in
+// which the radius changes.  Tiles whose copies would exceed kStreamSlots are
+// halved.  Every tile writes the partial sums of its window to part[part0 ...];
+// the bins are finished in chunks of up to kStreamChunk, each from the list
+// of the tiles that reach it.
+constexpr int32_t kStreamCountShift = 10;
+constexpr int32_t kStreamMaxCount = 63;    // bins of one pixel
+constexpr int32_t kStreamSlots = 640;      // 5 KB per wavefront: 32 wavefronts fill a CU's LDS
+constexpr int32_t kStreamMaxPix = 16384;   // pixels of a tile
+constexpr int32_t kStreamMaxBlocks = 256;  // 64 for each wavefront of a workgroup
+constexpr int32_t kStreamChunk = 16;
+constexpr int32_t kStreamRowsMinor = 1 << 16;  // flag of StreamTile::shape
+struct StreamTile {
+    int64_t pix0;            // first pixel in the flat image array
+    int32_t w, tw, th;       // image width, tile width and rows
+    int32_t shape;           // lk | lgw << 8 | kStreamRowsMinor
+    int32_t word0, g0;       // first word, first block
+    int32_t wlo, nwin;       // bin window (global bins)
+    int32_t pitch;           // LDS elements per copy
+    int32_t part0;           // first partial sum
+};
+static_assert(sizeof(StreamTile) == 48, "stream tile layout");
+struct StreamEnt {
+    int32_t base;            // partial sum of bin b at base + b
+    int32_t lo, hi;          // bins [lo, hi) of the tile's window
+    int32_t pad;
+};
+struct StreamChunk {
+    int32_t bin0, nbins;     // global bins
+    int32_t k0, k1;          // entries
+};
+struct StreamMatrix {
+    std::vector<StreamTile> tiles;
+    std::vector<StreamTile> blanks;  // tiles whose pixels feed no bin: place and size only
+    std::vector<uint16_t> words;
+    std::vector<int32_t> gbase;
+    std::vector<StreamEnt> ents;
+    std::vector<StreamChunk> chunks;
+    int64_t ncoef = 0, nparts = 0, npix = 0;
+    int32_t max_count = 0;   // most bins of a pixel
+};
+// Appends one h x w instance (its pixels start at pix_off, its bins at
+// bin_off) in tiles of about tile_px pixels.  Returns false where the
+// encoding does not apply: under four pixels, a pixel with non-consecutive bins or more than
+// kStreamMaxCount, bins so fine that the tiles had to be halved again and
+// again (over four times as many as their size asks for, under kStreamMinPix
+// pixels on average), positions past int32.
+constexpr int32_t kStreamMinPix = 192;
+bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, int64_t pix_off,
+                  int64_t bin_off, StreamMatrix& sm);
+
 // Matrix-free ("fused") schedule: the image cut into kFusedH x kFusedW
 // tiles; tile t feeds the bin window [wlo, wlo + nwin) and writes the partial
 // sums of bin wlo + k to slot slots[slot_off + k]; bin b owns slots

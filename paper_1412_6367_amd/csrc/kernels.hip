@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "accum.h"
+#include "correct.h"
 #include "kernels.h"
 
 namespace azi {
@@ -98,12 +99,6 @@ __device__ inline void accumulate(Acc& a, int32_t zlo, int32_t zhi, int lane, in
             }
         }
     }
-}
-
-template <bool NT, class T>
-__device__ inline T ld(const T* p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
 }
 
 // Lane-strided form: lane j of the group takes nonzeros zlo + j, + lanes, ...
@@ -267,32 +262,6 @@ __global__ void k_fixup(const Split* __restrict__ splits, int32_t nsplits,
 // product to the accumulator of the entry's bin within the band.  The R
 // accumulators are then reduced over the workgroup in a fixed tree and
 // written to the piece's R partial slots.
-template <class T> struct Pair2;
-template <> struct Pair2<double> { using type = double2; };
-template <> struct Pair2<float> { using type = float2; };
-
-// (T(raw) - dark) * (1 / norm) from a pair of the storage type, or from a
-// 12-byte record (float dark, double 1 / norm) used when every dark value
-// is a float: the cast back to double is exact, so both give the same bits.
-__device__ inline double corr_apply(double v, const double2& c) { return (v - c.x) * c.y; }
-__device__ inline float corr_apply(float v, const float2& c) { return (v - c.x) * c.y; }
-__device__ inline double corr_apply(double v, const Corr12& c) {
-    const double inv = __hiloint2double((int)c.inv_hi, (int)c.inv_lo);
-    return (v - (double)c.dark) * inv;
-}
-// Dark alone, when the coefficients carry 1 / norm (AZI_STAGE_FOLD): the
-// difference of an integer count and a float dark is exact in double.
-__device__ inline double corr_apply(double v, float d) { return v - (double)d; }
-__device__ inline double corr_apply(double v, double d) { return v - d; }
-__device__ inline float corr_apply(float v, float d) { return v - d; }
-// An integer dark count of 16 bits: exact in float and double alike.
-__device__ inline double corr_apply(double v, uint16_t d) { return v - (double)d; }
-__device__ inline float corr_apply(float v, uint16_t d) { return v - (float)d; }
-template <class T, class V>
-__device__ inline T corr_apply(T v, RunDark<V> d) { return corr_apply(v, d.v); }
-template <class C> struct IsRunDark { static constexpr bool value = false; };
-template <class V> struct IsRunDark<RunDark<V>> { static constexpr bool value = true; };
-
 // With kCorr the image is the raw frame: every gathered pixel is cast and
 // corrected on the way, (T(raw) - dark) * (1 / norm), dark and the
 // reciprocal of norm coming as one pair per pixel (one load), so the

@@ -1,0 +1,77 @@
+// Launch wrappers of the stream kernels (host side): one-dimensional
+// integration over the stream encoding (StreamMatrix).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "kernels.h"
+
+namespace azi {
+
+// Per-pixel correction of a stream launch, read in image order beside the
+// raw count: none, the unit image (U of the plan), the (dark, 1 / norm)
+// pairs or records of the fused stage, or dark alone (kCorrRunDark* kinds,
+// one value per pixel here) where the coefficients carry 1 / norm.
+constexpr int32_t kStreamPlain = -1, kStreamOnes = -2;
+
+struct StreamLaunch {
+    const StreamTile* tiles = nullptr;
+    int32_t ntiles = 0;
+    const uint16_t* words = nullptr;
+    const int32_t* gbase = nullptr;
+    const void* coef = nullptr;        // storage type, 64 spare elements at the end
+    const StreamChunk* chunks = nullptr;
+    int32_t nchunks = 0;
+    const StreamEnt* ents = nullptr;
+    int64_t ents_per_chunk = 0;        // on average: selects the reduction's shape
+    int32_t max_count = 0;             // most bins of a pixel
+    const void* img = nullptr;         // raw or corrected image (flat, img_dtype)
+    int32_t img_dtype = AZI_F64;
+    int64_t npix = 0;                  // pixels of img, four at least
+    const void* corr = nullptr;
+    int32_t corr_kind = kStreamPlain;
+    void* parts = nullptr;             // 8 bytes per partial sum
+    void* I = nullptr;
+    void* W = nullptr;                 // may be null
+    void* U = nullptr;                 // may be null
+    double empty = 0.0;
+    int32_t dtype = AZI_F64;
+    int32_t accum = AZI_ACC_F64;
+    const double* ufix = nullptr;      // U of every bin
+    const double* wsub = nullptr;      // subtracted from W when set
+    double* wfix_out = nullptr;        // only W (or U, of the unit image) is written, here
+};
+
+hipError_t launch_stream(const StreamLaunch& a, hipStream_t s);
+// launch_stream for one storage type and accumulator.
+hipError_t launch_stream_f64(const StreamLaunch& a, hipStream_t s);
+hipError_t launch_stream_f32(const StreamLaunch& a, hipStream_t s);
+hipError_t launch_stream_k32(const StreamLaunch& a, hipStream_t s);
+
+// coef[gbase ...] = src[colptr[p] + j], in stream order; with `norm`
+// (storage type, one value per pixel) multiplied by 1 / norm and rounded once.
+// src holds doubles (src_f64) or the storage type.
+struct StreamCoefLaunch {
+    const StreamTile* tiles = nullptr;
+    int32_t ntiles = 0;
+    const uint16_t* words = nullptr;
+    const int32_t* gbase = nullptr;
+    const int32_t* colptr = nullptr;
+    const void* src = nullptr;
+    bool src_f64 = false;
+    const void* norm = nullptr;
+    void* coef = nullptr;
+    int32_t dtype = AZI_F64;
+};
+hipError_t launch_stream_coef(const StreamCoefLaunch& a, hipStream_t s);
+
+// *flags (device int32) = 1 if some dark[i] is not an integer in [0, 65535],
+// plus 2 if some is not exactly a float.
+hipError_t launch_dark_kind(const void* dark, int32_t dtype, int64_t n, int32_t* flags,
+                            hipStream_t s);
+// out[i] = dark[i] as uint16 (kCorrRunDarkU16), float (kCorrRunDarkF32) or
+// the storage type (kCorrRunDark).
+hipError_t launch_dark_store(const void* dark, int32_t dtype, int32_t kind, void* out, int64_t n,
+                             hipStream_t s);
+
+}  // namespace azi

@@ -1,0 +1,128 @@
+// Device helpers of the stream encoding (StreamMatrix) shared by its kernels.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "correct.h"
+#include "internal.h"
+
+namespace azi {
+namespace {
+
+// Coefficients of a pixel held in registers; pixels of more bins take a loop
+// in the kernels instantiated for this many.
+constexpr int kStreamUnrolled = 4;
+constexpr int kLanePix = 4;                  // neighbouring pixels of a lane
+constexpr int kBlockPix = 64 * kLanePix;
+
+// Four consecutive elements as one load (two or more where they exceed 16
+// bytes), from an address aligned to the element alone.
+template <class V> struct Four { V v[kLanePix]; };
+template <class V> struct Vec4;
+template <> struct Vec4<int16_t> { typedef int16_t type __attribute__((ext_vector_type(4), aligned(2))); };
+template <> struct Vec4<uint16_t> { typedef uint16_t type __attribute__((ext_vector_type(4), aligned(2))); };
+template <> struct Vec4<int32_t> { typedef int32_t type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Vec4<uint32_t> { typedef uint32_t type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Vec4<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+template <class V>
+__device__ __forceinline__ Four<V> load_four(const V* p) {
+    const typename Vec4<V>::type a = *reinterpret_cast<const typename Vec4<V>::type*>(p);
+    return Four<V>{{a.x, a.y, a.z, a.w}};
+}
+typedef double StreamD2 __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ Four<double> load_four(const double* p) {
+    const StreamD2 a = *reinterpret_cast<const StreamD2*>(p);
+    const StreamD2 b = *reinterpret_cast<const StreamD2*>(p + 2);
+    return Four<double>{{a.x, a.y, b.x, b.y}};
+}
+template <class V>
+__device__ __forceinline__ Four<RunDark<V>> load_four(const RunDark<V>* p) {
+    const Four<V> a = load_four(reinterpret_cast<const V*>(p));
+    return Four<RunDark<V>>{{{a.v[0]}, {a.v[1]}, {a.v[2]}, {a.v[3]}}};
+}
+__device__ __forceinline__ Four<float2> load_four(const float2* p) {
+    return Four<float2>{{p[0], p[1], p[2], p[3]}};
+}
+__device__ __forceinline__ Four<double2> load_four(const double2* p) {
+    return Four<double2>{{p[0], p[1], p[2], p[3]}};
+}
+__device__ __forceinline__ Four<Corr12> load_four(const Corr12* p) {
+    return Four<Corr12>{{p[0], p[1], p[2], p[3]}};
+}
+
+// A lane's place in a tile, block after block.  The block's own place is the
+// same for the whole wavefront.
+struct StreamLane {
+    int gw, gh, across;      // block width and height in pixels, blocks across the tile
+    int pr, pc;              // the block's row and column of blocks
+    int r0, c0;              // the lane's first pixel within the block
+    int at;                  // r0 * w + c0
+    __device__ StreamLane(const StreamTile& t, int block, int lane) {
+        const int lgw = (t.shape >> 8) & 255;
+        gw = kLanePix << lgw;
+        gh = 64 >> lgw;
+        const bool rows_minor = t.shape & kStreamRowsMinor;
+        r0 = rows_minor ? lane & (gh - 1) : lane >> lgw;
+        c0 = kLanePix * (rows_minor ? lane >> (6 - lgw) : lane & ((1 << lgw) - 1));
+        at = r0 * t.w + c0;
+        across = (t.tw + gw - 1) / gw;
+        pr = block / across;
+        pc = block - pr * across;
+    }
+    __device__ static int blocks(const StreamTile& t) {
+        const int lgw = (t.shape >> 8) & 255;
+        return ((t.tw + (kLanePix << lgw) - 1) >> (2 + lgw)) *
+               ((t.th + (64 >> lgw) - 1) >> (6 - lgw));
+    }
+    // The lane's first pixel, counted from the tile's first.
+    __device__ int pixel(const StreamTile& t) const { return pr * gh * t.w + pc * gw + at; }
+    // Pixels of the lane that the tile has (0 or less: none).
+    __device__ int inside(const StreamTile& t) const {
+        return pr * gh + r0 < t.th ? t.tw - pc * gw - c0 : 0;
+    }
+    __device__ void next() {
+        ++pc;
+        const bool wrap = pc == across;
+        pc = wrap ? 0 : pc;
+        pr += wrap ? 1 : 0;
+    }
+};
+
+// The first N coefficients of one pixel of every lane (n bins each), those of
+// the wavefront starting at base; returns where the next pixels' start when
+// none has more than N bins.  Lanes without a j-th coefficient read their
+// neighbour's, unused: no branch, no address outside the array and its spare
+// elements.
+template <int N, class T>
+__device__ __forceinline__ int32_t stream_coefs(int32_t base, int n, const T* __restrict__ coef,
+                                                T (&c)[N]) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const uint64_t m = __ballot(n > j);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        c[j] = ld<true>(coef + base + rank);
+        base += (int32_t)__popcll(m);
+    }
+    return base;
+}
+
+// base past the j-th and further coefficients of the lanes' pixels.
+__device__ __forceinline__ int32_t stream_skip(int32_t base, int n, int j) {
+    for (;; ++j) {
+        const uint64_t m = __ballot(n > j);
+        if (m == 0) return base;
+        base += (int32_t)__popcll(m);
+    }
+}
+
+// Keeps the compiler from moving LDS accesses across: other lanes' elements
+// are written in between.  (The hardware completes a wavefront's LDS
+// accesses in order, so no wait is needed.)
+__device__ __forceinline__ void lds_in_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+}  // namespace
+}  // namespace azi
