@@ -242,7 +242,7 @@ constexpr size_t kScratchBytes = (size_t)8 << 20;
 // arrays in one allocation, the work arrays in a second.
 struct StreamBufs {
     DevBuf built, work;
-    const azi::StreamTile* tiles = nullptr;
+    const azi::StreamTile *tiles = nullptr, *blanks = nullptr;
     const azi::StreamChunk* chunks = nullptr;
     const azi::StreamEnt* ents = nullptr;
     const int32_t* gbase = nullptr;
@@ -250,7 +250,7 @@ struct StreamBufs {
     double* ufix = nullptr;   // U of every bin
     void* parts = nullptr;    // 8 bytes per partial sum
     void* coef = nullptr;     // storage type
-    int32_t ntiles = 0, nchunks = 0, max_count = 0;
+    int32_t ntiles = 0, nblanks = 0, nchunks = 0, max_count = 0;
     int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
     bool on = false;
     void release() {
@@ -333,11 +333,12 @@ int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32
         if (n) std::memcpy(host.data() + at, v.data(), n);
         return at;
     };
-    const size_t tiles = put(sm.tiles), chunks = put(sm.chunks), ents = put(sm.ents),
+    const size_t tiles = put(sm.tiles), blanks = put(sm.blanks), chunks = put(sm.chunks), ents = put(sm.ents),
                  gbase = put(sm.gbase), words = put(sm.words);
     AZI_HIP(b.built.upload(host.data(), host.size(), device), "stream encoding");
     const char* d = b.built.as<char>();
     b.tiles = reinterpret_cast<const azi::StreamTile*>(d + tiles);
+    b.blanks = reinterpret_cast<const azi::StreamTile*>(d + blanks);
     b.chunks = reinterpret_cast<const azi::StreamChunk*>(d + chunks);
     b.ents = reinterpret_cast<const azi::StreamEnt*>(d + ents);
     b.gbase = reinterpret_cast<const int32_t*>(d + gbase);
@@ -350,6 +351,7 @@ int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32
     b.parts = b.work.as<char>() + nu;
     b.coef = b.work.as<char>() + nu + np;
     b.ntiles = (int32_t)sm.tiles.size();
+    b.nblanks = (int32_t)sm.blanks.size();
     b.nchunks = (int32_t)sm.chunks.size();
     b.max_count = sm.max_count;
     b.ncoef = sm.ncoef;
@@ -365,6 +367,27 @@ int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32
     AZI_HIP(hipStreamSynchronize(nullptr), "stream encoding");
     b.on = true;
     return AZI_OK;
+}
+
+azi::StreamAdjointLaunch stream_adjoint_args(const StreamBufs& b, const void* U, const void* gI,
+                                             const void* gW, const void* norm, void* gx,
+                                             int32_t dtype) {
+    azi::StreamAdjointLaunch a;
+    a.tiles = b.tiles;
+    a.ntiles = b.ntiles;
+    a.blanks = b.blanks;
+    a.nblanks = b.nblanks;
+    a.words = b.words;
+    a.gbase = b.gbase;
+    a.coef = b.coef;
+    a.max_count = b.max_count;
+    a.U = U;
+    a.gI = gI;
+    a.gW = gW;
+    a.norm = norm;
+    a.gx = gx;
+    a.dtype = dtype;
+    return a;
 }
 
 }  // namespace
@@ -1944,6 +1967,14 @@ int azi_integrate1d_backward(const azi_plan* p, const void* U, const void* gI, c
     if (gI && !U) return fail(AZI_EINVAL, "U is needed with grad_I");
     DeviceGuard g(p->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
+    const void* norm = (wrt_raw && p->has_norm) ? p->norm.p : nullptr;
+    if (p->stream.on) {
+        AZI_HIP(azi::launch_stream_adjoint(
+                    stream_adjoint_args(p->stream, U, gI, gW, norm, gx, p->dtype),
+                    static_cast<hipStream_t>(stream)),
+                "backward kernel");
+        return AZI_OK;
+    }
     azi::BackwardLaunch a;
     a.colptr = p->colptr.as<int32_t>();
     a.rowidx = p->rowidx.as<int32_t>();
@@ -1952,7 +1983,7 @@ int azi_integrate1d_backward(const azi_plan* p, const void* U, const void* gI, c
     a.U = U;
     a.gI = gI;
     a.gW = gW;
-    a.norm = (wrt_raw && p->has_norm) ? p->norm.p : nullptr;
+    a.norm = norm;
     a.v = p->vwork.as<double>();
     a.gx = gx;
     a.npix = p->m.npix;
@@ -2521,6 +2552,13 @@ int azi_batch_backward(azi_batch* b, const void* U, const void* gI, const void* 
     if (gI && !U) return fail(AZI_EINVAL, "U is needed with grad_I");
     DeviceGuard g(b->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
+    if (b->stream.on) {
+        AZI_HIP(azi::launch_stream_adjoint(
+                    stream_adjoint_args(b->stream, U, gI, gW, nullptr, gx, b->dtype),
+                    static_cast<hipStream_t>(stream)),
+                "batched backward");
+        return AZI_OK;
+    }
     azi::BackwardLaunch a;
     a.colptr = b->colptr.as<int32_t>();
     a.rowidx = b->rowidx.as<int32_t>();

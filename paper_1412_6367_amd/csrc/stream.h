@@ -1,5 +1,5 @@
 // Launch wrappers of the stream kernels (host side): one-dimensional
-// integration over the stream encoding (StreamMatrix).
+// integration and its adjoint over the stream encoding (StreamMatrix).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -64,6 +64,25 @@ struct StreamCoefLaunch {
     int32_t dtype = AZI_F64;
 };
 hipError_t launch_stream_coef(const StreamCoefLaunch& a, hipStream_t s);
+
+// Adjoint: gx_p = sum_b A_bp (gI_b / U_b + gW_b).
+struct StreamAdjointLaunch {
+    const StreamTile* tiles = nullptr;
+    int32_t ntiles = 0;
+    const StreamTile* blanks = nullptr;  // pixels without entries: gx = 0
+    int32_t nblanks = 0;
+    const uint16_t* words = nullptr;
+    const int32_t* gbase = nullptr;
+    const void* coef = nullptr;
+    int32_t max_count = 0;
+    const void* U = nullptr;           // storage type
+    const void* gI = nullptr;          // may be null
+    const void* gW = nullptr;          // may be null
+    const void* norm = nullptr;        // divide the result by it when non-null
+    void* gx = nullptr;
+    int32_t dtype = AZI_F64;
+};
+hipError_t launch_stream_adjoint(const StreamAdjointLaunch& a, hipStream_t s);
 
 // *flags (device int32) = 1 if some dark[i] is not an integer in [0, 65535],
 // plus 2 if some is not exactly a float.

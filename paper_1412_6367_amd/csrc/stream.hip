@@ -1,6 +1,6 @@
 // Stream encoding on the device: dispatch of the forward kernels, the
-// coefficients put in stream order, and the per-pixel dark values of the
-// folded stage.
+// coefficients put in stream order, the adjoint, and the per-pixel dark
+// values of the folded stage.
 #include <hip/hip_runtime.h>
 
 #include "accum.h"
@@ -68,6 +68,119 @@ hipError_t coef_launch(const StreamCoefLaunch& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// One workgroup per tile of the forward; the tile's bins' v = gI / U + gW are
+// formed once into LDS (one pass less than a vector formed beforehand, and
+// the pixels' bins then come from LDS instead of the caches), the words and
+// coefficients read as in the forward, every lane writing its four pixels'
+// gradients together.  Workgroups past the tiles clear the pixels that feed
+// no bin.  The products are added in ascending bins, as by k_csc_bwd: the
+// same bits.  Bound by HBM: coefficients, words and gradient; k_csc_bwd read 8
+// bytes of column pointer and first bin a pixel in the words' place.
+template <class T, int NMAX>
+__global__ __launch_bounds__(256) void k_stream_adjoint(
+    const StreamTile* __restrict__ tiles, int32_t ntiles, const StreamTile* __restrict__ blanks,
+    const uint16_t* __restrict__ words, const int32_t* __restrict__ gbase,
+    const T* __restrict__ coef, const T* __restrict__ U, const T* __restrict__ gI,
+    const T* __restrict__ gW, const T* __restrict__ norm, T* __restrict__ gx) {
+    __shared__ double v[kStreamSlots + kStreamUnrolled];  // lanes read past their last bin
+    if ((int32_t)blockIdx.x >= ntiles) {
+        const StreamTile t = blanks[blockIdx.x - ntiles];
+        for (int e = threadIdx.x; e < t.tw * t.th; e += 256) {
+            const int r = e / t.tw;
+            gx[t.pix0 + r * t.w + e - r * t.tw] = T(0);
+        }
+        return;
+    }
+    const StreamTile t = tiles[xcd_block(blockIdx.x, ntiles)];
+    for (int i = threadIdx.x; i < t.nwin; i += 256) {
+        const int b = t.wlo + i;
+        double val = 0.0;
+        if (gI) {
+            const double u = (double)U[b];
+            val = (u != 0.0) ? (double)gI[b] / u : 0.0;
+        }
+        if (gW) val = val + (double)gW[b];
+        v[i] = val;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int ng = StreamLane::blocks(t);
+    const int g0 = (ng * wave) >> 2, g1 = (ng * (wave + 1)) >> 2;
+    StreamLane at(t, g0, lane);
+    const int32_t bases = gbase[t.g0 + min(g0 + lane, ng - 1)];
+    auto fetch = [&](int g) {
+        const int e = t.word0 + min(g, ng - 1) * kBlockPix + kLanePix * lane;
+        return ld<true>(reinterpret_cast<const uint64_t*>(words + e));
+    };
+    uint64_t word = fetch(g0);
+    __syncthreads();
+    for (int g = g0; g < g1; ++g) {
+        T c[kLanePix][NMAX];
+        int32_t more[kLanePix];
+        int32_t base = __builtin_amdgcn_readlane(bases, g - g0);
+        const uint64_t w4 = word;
+        auto bits = [&](int k) { return (uint32_t)(w4 >> (16 * k)) & 0xffffu; };
+#pragma unroll
+        for (int k = 0; k < kLanePix; ++k) {
+            const int n = (int)(bits(k) >> kStreamCountShift);
+            more[k] = base = stream_coefs<NMAX>(base, n, coef, c[k]);
+            if constexpr (NMAX == kStreamUnrolled) base = stream_skip(base, n, NMAX);
+        }
+        word = fetch(g + 1);
+        const int64_t p = t.pix0 + at.pixel(t);
+        const int in = at.inside(t);
+        at.next();
+        Four<T> out;
+#pragma unroll
+        for (int k = 0; k < kLanePix; ++k) {
+            const int n = (int)(bits(k) >> kStreamCountShift);
+            const double* vb = v + (bits(k) & ((1u << kStreamCountShift) - 1));
+            double acc = 0.0;
+#pragma unroll
+            for (int j = 0; j < NMAX; ++j) {
+                const double s = __fma_rn((double)c[k][j], vb[j], acc);
+                acc = n > j ? s : acc;
+            }
+            if constexpr (NMAX == kStreamUnrolled) {
+                for (int j = NMAX; __ballot(n > j) != 0; ++j) {
+                    T cj[1];
+                    more[k] = stream_coefs<1>(more[k], n > j ? 1 : 0, coef, cj);
+                    if (n > j) acc = __fma_rn((double)cj[0], vb[j], acc);
+                }
+            }
+            if (norm && k < in) acc = acc / (double)norm[p + k];
+            out.v[k] = (T)acc;
+        }
+        // the next words are waited for here: a wait after the stores would
+        // be for the stores too
+        asm volatile("" : "+v"(word));
+        if (in >= kLanePix) {
+            store_four(gx + p, out);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kLanePix; ++k)
+                if (k < in) gx[p + k] = out.v[k];
+        }
+    }
+}
+
+template <class T, int NMAX>
+hipError_t adjoint_launch(const StreamAdjointLaunch& a, hipStream_t s) {
+    hipLaunchKernelGGL((k_stream_adjoint<T, NMAX>), dim3((unsigned)(a.ntiles + a.nblanks)),
+                       dim3(256), 0, s, a.tiles, a.ntiles, a.blanks, a.words, a.gbase,
+                       static_cast<const T*>(a.coef), static_cast<const T*>(a.U),
+                       static_cast<const T*>(a.gI), static_cast<const T*>(a.gW),
+                       static_cast<const T*>(a.norm), static_cast<T*>(a.gx));
+    return hipGetLastError();
+}
+
+template <class T>
+hipError_t adjoint_slots(const StreamAdjointLaunch& a, hipStream_t s) {
+    if (a.max_count <= 2) return adjoint_launch<T, 2>(a, s);
+    if (a.max_count == 3) return adjoint_launch<T, 3>(a, s);
+    return adjoint_launch<T, kStreamUnrolled>(a, s);
+}
+
 template <class T>
 __global__ void k_dark_kind(const T* __restrict__ dark, int64_t n, int32_t* __restrict__ flags) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -108,6 +221,11 @@ hipError_t launch_stream_coef(const StreamCoefLaunch& a, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     if (a.dtype == AZI_F64) return coef_launch<double, double>(a, s);
     return a.src_f64 ? coef_launch<float, double>(a, s) : coef_launch<float, float>(a, s);
+}
+
+hipError_t launch_stream_adjoint(const StreamAdjointLaunch& a, hipStream_t s) {
+    if (a.ntiles + a.nblanks <= 0) return hipSuccess;
+    return a.dtype == AZI_F64 ? adjoint_slots<double>(a, s) : adjoint_slots<float>(a, s);
 }
 
 hipError_t launch_dark_kind(const void* dark, int32_t dtype, int64_t n, int32_t* flags,

@@ -35,6 +35,15 @@ __device__ __forceinline__ Four<double> load_four(const double* p) {
     const StreamD2 b = *reinterpret_cast<const StreamD2*>(p + 2);
     return Four<double>{{a.x, a.y, b.x, b.y}};
 }
+__device__ __forceinline__ void store_four(float* p, const Four<float>& a) {
+    typename Vec4<float>::type v = {a.v[0], a.v[1], a.v[2], a.v[3]};
+    *reinterpret_cast<typename Vec4<float>::type*>(p) = v;
+}
+__device__ __forceinline__ void store_four(double* p, const Four<double>& a) {
+    StreamD2 lo = {a.v[0], a.v[1]}, hi = {a.v[2], a.v[3]};
+    reinterpret_cast<StreamD2*>(p)[0] = lo;
+    reinterpret_cast<StreamD2*>(p)[1] = hi;
+}
 template <class V>
 __device__ __forceinline__ Four<RunDark<V>> load_four(const RunDark<V>* p) {
     const Four<V> a = load_four(reinterpret_cast<const V*>(p));

@@ -115,3 +115,34 @@ def test_stream_batch_equals_loop_and_oracle(dev):
             check([o[bo[k]:bo[k + 1]] for o in out], m, x[po[k]:po[k + 1]], TOL64, what=f"{k} {kw}")
     for a, b in zip(first, out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("g", GEOMS + [(200, 260, 100.0, 130.0, 37, "r_m", "bbox")],
+                         ids=lambda g: f"{g[0]}x{g[1]}-{g[4]}-{g[6]}")
+def test_stream_adjoint_bits_equal_entry_adjoint(g, dtype, dev):
+    """The adjoint over the stream encoding gives the bits of the adjoint over
+    the pixel-major entries (same products, same order), with either gradient
+    absent, towards the raw counts too, and zero for pixels that feed no bin."""
+    h, w, cy, cx, npt, unit, split = g
+    print("stream adjoint", g, dtype, flush=True)
+    az = azint()
+    npd = np.float64 if dtype == torch.float64 else np.float32
+    rng = np.random.default_rng(h + 7 * w)
+    t = lambda a: torch.from_numpy(a.astype(npd)).to(dev)
+    flat, x = t(rng.uniform(0.9, 1.1, h * w)), t(rng.uniform(0, 1, h * w))
+    gI, gW = t(rng.standard_normal(npt)), t(rng.standard_normal(npt))
+    kw = dict(center=(cy, cx), unit=unit, split=split, dtype=dtype, device=dev)
+    if (h, w) == (200, 260):
+        kw["range"] = (5e-4, 2e-3)
+    stream, entries = az.Plan(h, w, npt, **kw), az.Plan(h, w, npt, layout="pixel", **kw)
+    U = stream.integrate(x)[2]
+    for p in (stream, entries):
+        p.set_corrections(flat=flat)
+    for grads in ((gI, gW), (gI, None), (None, gW), (None, None)):
+        for wrt_raw in (False, True):
+            out = [torch.full((h * w,), float("nan"), dtype=dtype, device=dev) for _ in range(2)]
+            a = stream.backward(U, *grads, wrt_raw=wrt_raw, out=out[0])
+            b = entries.backward(U, *grads, wrt_raw=wrt_raw, out=out[1])
+            torch.cuda.synchronize()
+            assert torch.equal(a, b), (grads[0] is None, grads[1] is None, wrt_raw)
