@@ -410,6 +410,13 @@ int azi_plan_run_schedule(const azi_plan* plan, int32_t tile_nnz, int64_t* nruns
  * average, more than 8 MiB of partial sums (a batch: one instance of these, or
  * positions past 2^31).  The per-run dark values of AZI_STAGE_FOLD are
  * per-pixel ones there, in the same types.
+ * Two-dimensional plans in AZI_LAYOUT_PIXEL with their default tiling are
+ * integrated from the stream encoding too (their tiles' bins are radial bins
+ * of a few wedges), unless a partial sum would stand for under four nonzeros.
+ * Raw frames are then integrated in one pass: A_bp / norm, rounded once when
+ * the corrections are set, times raw - dark (as many roundings as A_bp times
+ * (raw - dark) / norm), and the work image is not written.  azi_plan_stage and
+ * the staged call keep the two passes; batches keep the CSR.
  * Set before azi_plan_upload (a later call re-uploads).  AZI_ESTATE once
  * corrections are set on an uploaded plan.  A refused or failed call leaves
  * the plan in its previous layout (if the re-upload of the new layout fails,

@@ -246,13 +246,14 @@ struct StreamBufs {
     const azi::StreamChunk* chunks = nullptr;
     const azi::StreamEnt* ents = nullptr;
     const int32_t* gbase = nullptr;
-    const uint16_t* words = nullptr;
+    const uint16_t *words = nullptr, *xpix = nullptr;
+    const int32_t* xsrc = nullptr;
     double* ufix = nullptr;   // U of every bin
     void* parts = nullptr;    // 8 bytes per partial sum
     void* coef = nullptr;     // storage type
-    int32_t ntiles = 0, nblanks = 0, nchunks = 0, max_count = 0;
+    int32_t ntiles = 0, nblanks = 0, nchunks = 0, slots = 4, ents_most = 0;
     int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
-    bool on = false;
+    bool over = true, on = false;
     void release() {
         built.release();
         work.release();
@@ -267,14 +268,25 @@ struct StreamBufs {
 // Kahan 15.1, 14.7 and 14.8 us a pass; 1536, 2560, 3072 and 4096 at 3162 x
 // 3163 float64 60.3, 54.8, 53.3 and 53.1 us, float32 in 1000 bins 31.9, 31.2,
 // 30.9 and 32.2 us.
-int32_t stream_tile_px(int64_t npix) {
+// Two-dimensional plans start from 4096 (64 rows of 64), halved where the
+// window asks for it.
+int32_t stream_tile_px(int64_t npix, bool two_d = false) {
+    if (two_d) return 4096;
     return (int32_t)std::max<int64_t>(1024, std::min<int64_t>(3072, npix / 2048));
 }
 
-// The run layout's tilings sized by the library (tile_nnz 0, four bands per
-// workgroup, no persistent grid) take the stream encoding where it applies.
-bool stream_tiling(const azi_tiling& t) {
-    return t.tile_nnz == 0 && t.band == 16 && t.grid == 0;
+// The tilings that take the stream encoding where it applies: in the run
+// layout, one-dimensional plans, those sized by the library (tile_nnz 0, four
+// bands per workgroup, no persistent grid); in the pixel layout,
+// two-dimensional plans, the default one.  Any other tiling asks for the
+// kernels it tunes.
+bool stream_tiling(const azi_tiling& t, int32_t layout, bool two_d) {
+    if (two_d)
+        return layout == AZI_LAYOUT_PIXEL && t.tile_nnz == kDefaultTiling2d.tile_nnz &&
+               t.block == kDefaultTiling2d.block && t.variant == kDefaultTiling2d.variant &&
+               t.grid == kDefaultTiling2d.grid && t.band == kDefaultTiling2d.band &&
+               t.stage == kDefaultTiling2d.stage;
+    return layout == AZI_LAYOUT_RUN && t.tile_nnz == 0 && t.band == 16 && t.grid == 0;
 }
 
 azi::StreamLaunch stream_args(const StreamBufs& b, const void* img, int32_t img_dtype,
@@ -286,12 +298,15 @@ azi::StreamLaunch stream_args(const StreamBufs& b, const void* img, int32_t img_
     a.ntiles = b.ntiles;
     a.words = b.words;
     a.gbase = b.gbase;
+    a.xpix = b.xpix;
     a.coef = b.coef;
     a.chunks = b.chunks;
     a.nchunks = b.nchunks;
     a.ents = b.ents;
     a.ents_per_chunk = b.ents_per_chunk;
-    a.max_count = b.max_count;
+    a.ents_most = b.ents_most;
+    a.slots = b.slots;
+    a.over = b.over;
     a.img = img;
     a.img_dtype = img_dtype;
     a.parts = b.parts;
@@ -312,6 +327,8 @@ azi::StreamCoefLaunch stream_coef_args(const StreamBufs& b, const DevBuf& colptr
     c.ntiles = b.ntiles;
     c.words = b.words;
     c.gbase = b.gbase;
+    c.xpix = b.xpix;
+    c.xsrc = b.xsrc;
     c.colptr = colptr.as<int32_t>();
     c.src = src;
     c.coef = coef;
@@ -323,8 +340,9 @@ azi::StreamCoefLaunch stream_coef_args(const StreamBufs& b, const DevBuf& colptr
 // the pixel-major entries there (colptr, cdata), and the U of its npt bins,
 // which no frame changes, is summed once from them (the kernels over the unit
 // image, the same order as W).
-int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32_t accum,
-                  int device, const DevBuf& colptr, const DevBuf& cdata, StreamBufs& b) {
+int upload_stream(const azi::StreamMatrix& sm, bool two_d, int64_t npt, int32_t dtype,
+                  int32_t accum, int device, const DevBuf& colptr, const DevBuf& cdata,
+                  StreamBufs& b) {
     b.release();
     std::vector<char> host;
     auto put = [&host](const auto& v) {
@@ -334,7 +352,8 @@ int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32
         return at;
     };
     const size_t tiles = put(sm.tiles), blanks = put(sm.blanks), chunks = put(sm.chunks), ents = put(sm.ents),
-                 gbase = put(sm.gbase), words = put(sm.words);
+                 gbase = put(sm.gbase), words = put(sm.words), xpix = put(sm.xpix),
+                 xsrc = put(sm.xsrc);
     AZI_HIP(b.built.upload(host.data(), host.size(), device), "stream encoding");
     const char* d = b.built.as<char>();
     b.tiles = reinterpret_cast<const azi::StreamTile*>(d + tiles);
@@ -343,6 +362,8 @@ int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32
     b.ents = reinterpret_cast<const azi::StreamEnt*>(d + ents);
     b.gbase = reinterpret_cast<const int32_t*>(d + gbase);
     b.words = reinterpret_cast<const uint16_t*>(d + words);
+    b.xpix = two_d ? reinterpret_cast<const uint16_t*>(d + xpix) : nullptr;
+    b.xsrc = two_d ? reinterpret_cast<const int32_t*>(d + xsrc) : nullptr;
     const size_t nu = (size_t)round_up(npt * 8, 256);
     const size_t np = (size_t)round_up(sm.nparts * 8, 256);
     AZI_HIP(b.work.alloc(nu + np + (size_t)(sm.ncoef + kPad) * elem_size(dtype), device),
@@ -353,9 +374,17 @@ int upload_stream(const azi::StreamMatrix& sm, int64_t npt, int32_t dtype, int32
     b.ntiles = (int32_t)sm.tiles.size();
     b.nblanks = (int32_t)sm.blanks.size();
     b.nchunks = (int32_t)sm.chunks.size();
-    b.max_count = sm.max_count;
+    // as many coefficients in registers as all but one pixel in 1024 need: 64
+    // images of 1e3 to 1e6 pixels with 5e-5 pixels of four bins take 80.2 us
+    // forward and backward with three, 82.9 with four; a fully split 1967 x
+    // 2011 image with 0.6 % of them 31.4 us with three, 29.8 with four
+    b.slots = 2;
+    while (b.slots < 4 && sm.over[b.slots] * 1024 > sm.over[0]) ++b.slots;
+    b.over = sm.over[b.slots] > 0;
     b.ncoef = sm.ncoef;
     b.nparts = sm.nparts;
+    b.ents_most = 0;
+    for (const azi::StreamChunk& c : sm.chunks) b.ents_most = std::max(b.ents_most, c.k1 - c.k0);
     b.ents_per_chunk = (int64_t)(sm.ents.size() / std::max<size_t>(sm.chunks.size(), 1));
     AZI_HIP(azi::launch_stream_coef(stream_coef_args(b, colptr, cdata.p, b.coef, dtype), nullptr),
             "stream coefficients");
@@ -380,7 +409,8 @@ azi::StreamAdjointLaunch stream_adjoint_args(const StreamBufs& b, const void* U,
     a.words = b.words;
     a.gbase = b.gbase;
     a.coef = b.coef;
-    a.max_count = b.max_count;
+    a.slots = b.slots;
+    a.over = b.over;
     a.U = U;
     a.gI = gI;
     a.gW = gW;
@@ -574,20 +604,21 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
 }
 
 // The stream encoding of a plan whose tiling asks for it; *done is false
-// where it does not apply (two-dimensional plans, bins too fine, partial
-// sums beyond the allocation-free call's array): the run encoding then
+// where it does not apply (bins too fine, partial
+// sums beyond the allocation-free call's array): the layout's own form then
 // serves.
 int plan_upload_stream(azi_plan* p, bool* done) {
     *done = false;
     p->stream.release();
-    if (p->layout != AZI_LAYOUT_RUN || !stream_tiling(p->tiling)) return AZI_OK;
+    if (!stream_tiling(p->tiling, p->layout, p->m.two_d)) return AZI_OK;
     try {
         azi::StreamMatrix sm;
-        if (!azi::build_stream(p->m, p->geom.h, p->geom.w, stream_tile_px(p->m.npix), 0, 0, sm) ||
-            (size_t)sm.nparts * 8 > kScratchBytes)
+        if (!azi::build_stream(p->m, p->geom.h, p->geom.w, stream_tile_px(p->m.npix, p->m.two_d),
+                               0, 0, sm) ||
+            (!p->m.two_d && (size_t)sm.nparts * 8 > kScratchBytes))
             return AZI_OK;
-        const int rc = upload_stream(sm, p->m.npt, p->dtype, p->accum, p->device, p->colptr,
-                                     p->cdata, p->stream);
+        const int rc = upload_stream(sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
+                                     p->colptr, p->cdata, p->stream);
         if (rc != AZI_OK) return rc;
     } catch (const std::bad_alloc&) {
         return fail(AZI_ENOMEM, "out of host memory building the stream encoding");
@@ -835,6 +866,9 @@ int plan_fold_stream(azi_plan* p, hipStream_t s) {
     const int64_t npix = p->m.npix;
     const StreamBufs& b = p->stream;
     const bool sum_dark = p->tiling.stage == AZI_STAGE_FOLD_SUM && p->accum == AZI_ACC_F64;
+    // two-dimensional plans: A_bp / norm, rounded once, times raw - dark, as many
+    // roundings as A_bp times (raw - dark) / norm
+    const bool divide = p->m.two_d;
     if (p->has_norm) {
         DevBuf exact;  // float32 plans: the double coefficients
         AZI_HIP(p->fcoef.alloc((size_t)(b.ncoef + kPad) * elem_size(p->dtype), p->device),
@@ -848,6 +882,7 @@ int plan_fold_stream(azi_plan* p, hipStream_t s) {
             c.src_f64 = true;
         }
         c.norm = p->norm.p;
+        c.divide = divide;
         AZI_HIP(azi::launch_stream_coef(c, s), "folded coefficients");
         AZI_HIP(hipStreamSynchronize(s), "folded coefficients");
     }
@@ -973,6 +1008,17 @@ int plan_corr_pair(azi_plan* p, hipStream_t s) {
     p->wdark.release();
     p->folded = false;
     p->corr_kind = azi::kCorrPair;
+    const bool map = p->stream.on && p->layout == AZI_LAYOUT_PIXEL;
+    if (map && (p->has_dark || p->has_norm)) {
+        const int rc = plan_fold_stream(p, s);
+        p->folded = rc == AZI_OK;
+        if (rc != AZI_OK) {
+            p->corr.release();
+            p->fcoef.release();
+            p->corr_kind = azi::kCorrPair;
+        }
+        return rc;
+    }
     if (!is_band(p->layout) || !gather_corrects(p->tiling.stage) ||
         !(p->has_dark || p->has_norm))
         return AZI_OK;
@@ -1345,6 +1391,9 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
         // host-built two-dimensional plans
         p->layout = AZI_LAYOUT_PIXEL;
         p->tiling = kDefaultTiling2d;
+        bool streamed = false;
+        const int rcs = plan_upload_stream(p, &streamed);
+        if (rcs != AZI_OK) return rcs;
         return plan_upload_tiles(p);
     }
     // the band layout's own bands of 4 bins (band 16 means four neighbouring
@@ -1466,7 +1515,8 @@ int azi_plan_set_tiling(azi_plan* p, const azi_tiling* t) {
     if (!p || !t) return fail(AZI_EINVAL, "plan and tiling must not be NULL");
     if (!valid_tiling(*t)) return fail(AZI_EINVAL, kTilingRule);
     const bool retile = t->tile_nnz != p->tiling.tile_nnz || t->band != p->tiling.band ||
-                        stream_tiling(*t) != stream_tiling(p->tiling);
+                        stream_tiling(*t, p->layout, p->m.two_d) !=
+                            stream_tiling(p->tiling, p->layout, p->m.two_d);
     const bool restage = t->stage != p->tiling.stage;
     const bool reblock = t->block != p->tiling.block;
     p->tiling = *t;
@@ -1477,12 +1527,16 @@ int azi_plan_set_tiling(azi_plan* p, const azi_tiling* t) {
         if (is_band(p->layout)) {
             int rc = plan_upload_bands(p);
             if (rc != AZI_OK) return rc;
+        } else if (p->layout == AZI_LAYOUT_PIXEL) {
+            bool streamed = false;
+            const int rc = plan_upload_stream(p, &streamed);
+            if (rc != AZI_OK) return rc;
         }
         const int rc = plan_upload_tiles(p);
         if (rc != AZI_OK) return rc;
     }
     // the folded form's U follows the pieces and the workgroup size
-    if (p->device >= 0 && (restage || (p->folded && (retile || reblock)))) {
+    if (p->device >= 0 && (restage || ((p->folded || p->stream.on) && (retile || reblock)))) {
         DeviceGuard g(p->device);
         if (g.err != hipSuccess) return hip_fail(g.err, "set device");
         AZI_HIP(hipDeviceSynchronize(), "synchronise before changing the stage");
@@ -1654,6 +1708,11 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
             int rc2 = plan_upload_bands(p);
             if (rc2 != AZI_OK) return rc2;
         }
+        if (p->layout == AZI_LAYOUT_PIXEL) {
+            bool streamed = false;
+            const int rc2 = plan_upload_stream(p, &streamed);
+            if (rc2 != AZI_OK) return rc2;
+        }
         if (p->layout == AZI_LAYOUT_FUSED) {
             int rc2 = plan_upload_fused(p);
             if (rc2 != AZI_OK) return rc2;
@@ -1679,7 +1738,7 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
 }
 
 int32_t azi_plan_correction_bytes(const azi_plan* p) {
-    if (!p || !p->corr.p) return 0;
+    if (!p || !p->corr.p || !is_band(p->layout)) return 0;
     if (p->corr_kind == azi::kCorrRecord12) return (int32_t)sizeof(azi::Corr12);
     if (p->corr_kind == azi::kCorrRunDarkU16) return 2;
     if (p->corr_kind == azi::kCorrRunDarkF32) return 4;
@@ -1784,6 +1843,10 @@ int azi_integrate1d(const azi_plan* p, const void* x, void* I, void* W, void* U,
         AZI_HIP(plan_launch_image(p, x, I, W, U, empty, s), "band forward kernels");
         return AZI_OK;
     }
+    if (p->layout == AZI_LAYOUT_PIXEL && p->stream.on) {
+        AZI_HIP(plan_launch_image(p, x, I, W, U, empty, s), "map forward kernels");
+        return AZI_OK;
+    }
     const void* xin = x;
     if (p->layout == AZI_LAYOUT_RING) {
         AZI_HIP(azi::launch_stage(plan_stage_args(p, x, p->dtype, false), s), "permutation kernel");
@@ -1836,6 +1899,11 @@ int azi_integrate1d_staged(const azi_plan* p, void* I, void* W, void* U, double 
                 "band forward kernels");
         return AZI_OK;
     }
+    if (p->layout == AZI_LAYOUT_PIXEL && p->stream.on) {
+        AZI_HIP(plan_launch_image(p, p->xwork.p, I, W, U, empty, static_cast<hipStream_t>(stream)),
+                "map forward kernels");
+        return AZI_OK;
+    }
     AZI_HIP(azi::launch_forward(plan_forward_args(p, p->xwork.p, I, W, U, empty),
                                 static_cast<hipStream_t>(stream)),
             "forward kernel");
@@ -1867,8 +1935,10 @@ int azi_integrate1d_raw(const azi_plan* p, const void* raw, int32_t raw_dtype, v
                 "blocked forward kernels");
         return AZI_OK;
     }
-    if (p && is_band(p->layout) && gather_corrects(p->tiling.stage) && p->device >= 0) {
-        // cast and correction in the band kernel's gather
+    if (p && p->device >= 0 &&
+        ((is_band(p->layout) && gather_corrects(p->tiling.stage)) ||
+         (p->layout == AZI_LAYOUT_PIXEL && p->stream.on))) {
+        // cast and correction in the kernel's gather
         if (!raw) return fail(AZI_EINVAL, "raw must not be NULL");
         if (!valid_raw_dtype(raw_dtype)) return fail(AZI_EINVAL, "unknown raw dtype");
         DeviceGuard g(p->device);
@@ -1968,7 +2038,7 @@ int azi_integrate1d_backward(const azi_plan* p, const void* U, const void* gI, c
     DeviceGuard g(p->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
     const void* norm = (wrt_raw && p->has_norm) ? p->norm.p : nullptr;
-    if (p->stream.on) {
+    if (p->stream.on && !p->m.two_d) {
         AZI_HIP(azi::launch_stream_adjoint(
                     stream_adjoint_args(p->stream, U, gI, gW, norm, gx, p->dtype),
                     static_cast<hipStream_t>(stream)),
@@ -2185,7 +2255,7 @@ int azi_batch_set_tiling(azi_batch* b, const azi_tiling* t) {
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
     const bool retile =
         t->tile_nnz != b->tiling.tile_nnz || t->band != b->tiling.band || b->ntiles == 0 ||
-        stream_tiling(*t) != stream_tiling(b->tiling);
+        stream_tiling(*t, b->layout, false) != stream_tiling(b->tiling, b->layout, false);
     b->tiling = *t;
     if (retile) {
         AZI_HIP(hipDeviceSynchronize(), "synchronise before retiling");
@@ -2221,7 +2291,7 @@ namespace {
 int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& ms, bool* done) {
     *done = false;
     b->stream.release();
-    if (b->layout != AZI_LAYOUT_RUN || !stream_tiling(b->tiling)) return AZI_OK;
+    if (!stream_tiling(b->tiling, b->layout, false)) return AZI_OK;
     azi::StreamMatrix sm;
     const int32_t px = stream_tile_px(b->npix);
     b->stream_off.assign(b->n + 1, 0);
@@ -2233,8 +2303,8 @@ int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& 
         b->stream_off[k + 1] = (int64_t)sm.tiles.size();
         b->chunk_off[k + 1] = (int64_t)sm.chunks.size();
     }
-    const int rc = upload_stream(sm, b->npt, b->dtype, b->accum, b->device, b->colptr, b->cdata,
-                                 b->stream);
+    const int rc = upload_stream(sm, false, b->npt, b->dtype, b->accum, b->device, b->colptr,
+                                 b->cdata, b->stream);
     if (rc != AZI_OK) return rc;
     for (DevBuf* d : {&b->npieces_buf, &b->npacked, &b->ncoef, &b->bin_slot, &b->bin_count,
                       &b->nparts_buf})

@@ -222,7 +222,8 @@ bool build_runs(const HostMatrix& m, int32_t piece_runs, int64_t pix_off, int64_
 // cut into rows), the tile's pixels taken in blocks of 256: 64 lanes of four
 // neighbouring pixels of a row each, so that a lane reads its words and its
 // pixels with one load.  A block is 2^lgw lanes across and 2^(6 - lgw) rows
-// down; lanes are numbered along the rows or (kStreamRowsMinor) down the
+// down, every 2^lrs-th row of the tile (the rows between are the next blocks');
+// lanes are numbered along the rows or (kStreamRowsMinor) down the
 // columns; blocks follow each other along the tile's rows, pixels past the
 // tile's edge hold nothing.  A pixel has one 16-bit word, its first bin within
 // the tile's bin window | number of bins << kStreamCountShift (0: feeds no
@@ -238,7 +239,7 @@ bool build_runs(const HostMatrix& m, int32_t piece_runs, int64_t pix_off, int64_
 // the same pixel of the lane: no two lanes of one LDS access then meet in one
 // bin, so the sums need no atomics and have one order.  The block's shape is
 // chosen per tile for few copies: lanes numbered across the direction in
-// which the radius changes.  Tiles whose copies would exceed kStreamSlots are
+// which the radius changes, its rows apart where bins are wider than pixels.  Tiles whose copies would exceed kStreamSlots are
 // halved.  Every tile writes the partial sums of its window to part[part0 ...];
 // the bins are finished in chunks of up to kStreamChunk, each from the list
 // of the tiles that reach it.
@@ -248,17 +249,21 @@ constexpr int32_t kStreamSlots = 640;      // 5 KB per wavefront: 32 wavefronts 
 constexpr int32_t kStreamMaxPix = 16384;   // pixels of a tile
 constexpr int32_t kStreamMaxBlocks = 256;  // 64 for each wavefront of a workgroup
 constexpr int32_t kStreamChunk = 16;
-constexpr int32_t kStreamRowsMinor = 1 << 16;  // flag of StreamTile::shape
+// StreamTile::shape: lk | lgw << 4 | lrs << 8 | kStreamRowsMinor | most bins of
+// one of the tile's pixels << kStreamMostShift
+constexpr int32_t kStreamRowsMinor = 1 << 16;
+constexpr int32_t kStreamMostShift = 17;
 struct StreamTile {
     int64_t pix0;            // first pixel in the flat image array
     int32_t w, tw, th;       // image width, tile width and rows
-    int32_t shape;           // lk | lgw << 8 | kStreamRowsMinor
+    int32_t shape;
     int32_t word0, g0;       // first word, first block
-    int32_t wlo, nwin;       // bin window (global bins)
+    int32_t wlo, nwin;       // bin window (wlo: the first global bin, one-dimensional tiles)
     int32_t pitch;           // LDS elements per copy
     int32_t part0;           // first partial sum
+    int32_t nx, x0;          // scattered groups of 64 items, after the blocks; the first of them
 };
-static_assert(sizeof(StreamTile) == 48, "stream tile layout");
+static_assert(sizeof(StreamTile) == 56, "stream tile layout");
 struct StreamEnt {
     int32_t base;            // partial sum of bin b at base + b
     int32_t lo, hi;          // bins [lo, hi) of the tile's window
@@ -273,18 +278,34 @@ struct StreamMatrix {
     std::vector<StreamTile> blanks;  // tiles whose pixels feed no bin: place and size only
     std::vector<uint16_t> words;
     std::vector<int32_t> gbase;
-    std::vector<StreamEnt> ents;
+    std::vector<uint16_t> xpix;      // scattered items: row << kStreamColBits | column in the tile
+    std::vector<int32_t> xsrc;       // and position of the first coefficient (pixel-major)
+    std::vector<StreamEnt> segs;     // the tiles' windows as stretches of bins, tile by tile
+    std::vector<StreamEnt> ents;     // segs by chunk
     std::vector<StreamChunk> chunks;
     int64_t ncoef = 0, nparts = 0, npix = 0;
-    int32_t max_count = 0;   // most bins of a pixel
+    int64_t over[5] = {0};   // pixels of more than k bins
 };
 // Appends one h x w instance (its pixels start at pix_off, its bins at
 // bin_off) in tiles of about tile_px pixels.  Returns false where the
-// encoding does not apply: under four pixels, a pixel with non-consecutive bins or more than
-// kStreamMaxCount, bins so fine that the tiles had to be halved again and
-// again (over four times as many as their size asks for, under kStreamMinPix
-// pixels on average), positions past int32.
+// encoding does not apply: under four pixels, a pixel of a one-dimensional
+// matrix with non-consecutive bins or more than kStreamMaxCount, bins so fine
+// that the tiles had to be halved again and again (over four times as many as
+// their size asks for, under kStreamMinPix pixels on average), positions past
+// int32.
+//
+// Two-dimensional matrices (pix_off and bin_off 0): a tile's window is the
+// radial bins it reaches, wedge after wedge; a pixel's entries are runs of
+// consecutive radial bins of one wedge.  A pixel's first run is encoded as a
+// one-dimensional pixel's bins are; the others (pixels across a wedge's edge,
+// a few per cent) follow in scattered groups of 64 items, one a lane (words
+// after the blocks', gbase too), which name the pixel of every item (xpix): a
+// multiple of four groups, for the four wavefronts, the items of one bin spread
+// over them.  A pixel of more runs than a window holds (the beam's) has
+// several tiles of its own, all of its runs scattered.  Refused too: more
+// than one partial sum per four entries.
 constexpr int32_t kStreamMinPix = 192;
+constexpr int32_t kStreamColBits = 6;  // columns of a tile: 64
 bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, int64_t pix_off,
                   int64_t bin_off, StreamMatrix& sm);
 

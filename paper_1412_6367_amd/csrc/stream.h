@@ -19,12 +19,15 @@ struct StreamLaunch {
     int32_t ntiles = 0;
     const uint16_t* words = nullptr;
     const int32_t* gbase = nullptr;
+    const uint16_t* xpix = nullptr;    // two-dimensional matrices: pixels of the scattered items
     const void* coef = nullptr;        // storage type, 64 spare elements at the end
     const StreamChunk* chunks = nullptr;
     int32_t nchunks = 0;
     const StreamEnt* ents = nullptr;
-    int64_t ents_per_chunk = 0;        // on average: selects the reduction's shape
-    int32_t max_count = 0;             // most bins of a pixel
+    int64_t ents_per_chunk = 0;        // on average, and
+    int32_t ents_most = 0;             // at most: these select the reduction's shape
+    int32_t slots = 4;                 // coefficients a pixel keeps in registers: 2, 3 or 4
+    bool over = true;                  // some pixel has more
     const void* img = nullptr;         // raw or corrected image (flat, img_dtype)
     int32_t img_dtype = AZI_F64;
     int64_t npix = 0;                  // pixels of img, four at least
@@ -49,7 +52,8 @@ hipError_t launch_stream_f32(const StreamLaunch& a, hipStream_t s);
 hipError_t launch_stream_k32(const StreamLaunch& a, hipStream_t s);
 
 // coef[gbase ...] = src[colptr[p] + j], in stream order; with `norm`
-// (storage type, one value per pixel) multiplied by 1 / norm and rounded once.
+// (storage type, one value per pixel) times 1 / norm, rounded once more, or
+// with `divide` over norm, rounded once.
 // src holds doubles (src_f64) or the storage type.
 struct StreamCoefLaunch {
     const StreamTile* tiles = nullptr;
@@ -57,9 +61,12 @@ struct StreamCoefLaunch {
     const uint16_t* words = nullptr;
     const int32_t* gbase = nullptr;
     const int32_t* colptr = nullptr;
+    const uint16_t* xpix = nullptr;    // two-dimensional matrices: pixels of the scattered items
+    const int32_t* xsrc = nullptr;     // and positions in src
     const void* src = nullptr;
     bool src_f64 = false;
     const void* norm = nullptr;
+    bool divide = false;
     void* coef = nullptr;
     int32_t dtype = AZI_F64;
 };
@@ -74,7 +81,8 @@ struct StreamAdjointLaunch {
     const uint16_t* words = nullptr;
     const int32_t* gbase = nullptr;
     const void* coef = nullptr;
-    int32_t max_count = 0;
+    int32_t slots = 4;                 // as in StreamLaunch
+    bool over = true;
     const void* U = nullptr;           // storage type
     const void* gI = nullptr;          // may be null
     const void* gW = nullptr;          // may be null

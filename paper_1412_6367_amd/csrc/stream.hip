@@ -18,39 +18,62 @@ hipError_t launch_stream(const StreamLaunch& a, hipStream_t s) {
 
 namespace {
 
-// Every lane writes its pixel's coefficients to their stream positions.
+// Every lane writes its pixels' coefficients to their stream positions.
 template <class T, class S, bool kNorm>
-__global__ __launch_bounds__(256) void k_stream_coef(const StreamTile* __restrict__ tiles,
-                                                     const uint16_t* __restrict__ words,
-                                                     const int32_t* __restrict__ gbase,
-                                                     const int32_t* __restrict__ colptr,
-                                                     const S* __restrict__ src,
-                                                     const T* __restrict__ norm,
-                                                     T* __restrict__ coef) {
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+__global__ __launch_bounds__(256) void k_stream_coef(
+    const StreamTile* __restrict__ tiles, const uint16_t* __restrict__ words,
+    const int32_t* __restrict__ gbase, const int32_t* __restrict__ colptr,
+    const uint16_t* __restrict__ xpix, const int32_t* __restrict__ xsrc,
+    const S* __restrict__ src, const T* __restrict__ norm, bool divide, T* __restrict__ coef) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x & (kWave - 1);
     const StreamTile t = tiles[blockIdx.x];
+    auto scale_of = [&](int64_t p) {
+        if constexpr (kNorm) return divide ? (double)norm[p] : 1.0 / (double)norm[p];
+        else return 1.0;
+    };
+    auto put = [&](int32_t& base, int n, int32_t k0, double scale) {
+        for (int j = 0;; ++j) {
+            const uint64_t m = __ballot(n > j);
+            if (m == 0) break;
+            const int rank = (int)__builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (n > j) {
+                const S c = src[k0 + j];
+                if constexpr (kNorm)
+                    coef[base + rank] = (T)(divide ? (double)c / scale : (double)c * scale);
+                else
+                    coef[base + rank] = (T)c;
+            }
+            base += (int32_t)__popcll(m);
+        }
+    };
     const int ng = StreamLane::blocks(t);
     for (int g = wave; g < ng; g += 4) {
         const StreamLane at(t, g, lane);
+        const int64_t e = (int64_t)t.word0 + g * kBlockPix + kLanePix * lane;
         int32_t base = gbase[t.g0 + g];
+        int n[kLanePix];
+        int32_t k0[kLanePix];
+        double scale[kLanePix];
+#pragma unroll
         for (int k = 0; k < kLanePix; ++k) {
-            const int n = (int)(words[t.word0 + g * kBlockPix + kLanePix * lane + k] >>
-                                kStreamCountShift);
+            n[k] = (int)(words[e + k] >> kStreamCountShift);
             const int64_t p = t.pix0 + (at.inside(t) > k ? at.pixel(t) + k : 0);
-            const int32_t k0 = colptr[p];
-            double scale = 1.0;
-            if constexpr (kNorm) scale = 1.0 / (double)norm[p];
-            for (int j = 0; __ballot(n > j) != 0; ++j) {
-                const uint64_t m = __ballot(n > j);
-                const int rank = (int)__builtin_amdgcn_mbcnt_hi(
-                    (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                if (n > j) {
-                    if constexpr (kNorm) coef[base + rank] = (T)((double)src[k0 + j] * scale);
-                    else coef[base + rank] = (T)src[k0 + j];
-                }
-                base += (int32_t)__popcll(m);
-            }
+            k0[k] = colptr[p];
+            scale[k] = scale_of(p);
         }
+#pragma unroll
+        for (int k = 0; k < kLanePix; ++k) put(base, n[k], k0[k], scale[k]);
+    }
+    for (int u = wave; u < t.nx; u += 4) {
+        const int n = (int)(words[(int64_t)t.word0 + ng * kBlockPix + u * kWave + lane] >>
+                            kStreamCountShift);
+        const int64_t x = (int64_t)(t.x0 + u) * kWave + lane;
+        const int i = xpix[x];
+        int32_t base = gbase[t.g0 + ng + u];
+        put(base, n, xsrc[x],
+            scale_of(t.pix0 + (i >> kStreamColBits) * t.w + (i & ((1 << kStreamColBits) - 1))));
     }
 }
 
@@ -61,10 +84,12 @@ hipError_t coef_launch(const StreamCoefLaunch& a, hipStream_t s) {
     T* coef = static_cast<T*>(a.coef);
     if (norm)
         hipLaunchKernelGGL((k_stream_coef<T, S, true>), dim3((unsigned)a.ntiles), dim3(256), 0, s,
-                           a.tiles, a.words, a.gbase, a.colptr, src, norm, coef);
+                           a.tiles, a.words, a.gbase, a.colptr, a.xpix, a.xsrc, src, norm,
+                           a.divide, coef);
     else
         hipLaunchKernelGGL((k_stream_coef<T, S, false>), dim3((unsigned)a.ntiles), dim3(256), 0, s,
-                           a.tiles, a.words, a.gbase, a.colptr, src, norm, coef);
+                           a.tiles, a.words, a.gbase, a.colptr, a.xpix, a.xsrc, src, norm,
+                           a.divide, coef);
     return hipGetLastError();
 }
 
@@ -76,7 +101,7 @@ hipError_t coef_launch(const StreamCoefLaunch& a, hipStream_t s) {
 // no bin.  The products are added in ascending bins, as by k_csc_bwd: the
 // same bits.  Bound by HBM: coefficients, words and gradient; k_csc_bwd read 8
 // bytes of column pointer and first bin a pixel in the words' place.
-template <class T, int NMAX>
+template <class T, int NMAX, bool kOver>
 __global__ __launch_bounds__(256) void k_stream_adjoint(
     const StreamTile* __restrict__ tiles, int32_t ntiles, const StreamTile* __restrict__ blanks,
     const uint16_t* __restrict__ words, const int32_t* __restrict__ gbase,
@@ -91,7 +116,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
         }
         return;
     }
-    const StreamTile t = tiles[xcd_block(blockIdx.x, ntiles)];
+    const StreamTile t = tiles[stream_tile_of(blockIdx.x, ntiles)];
     for (int i = threadIdx.x; i < t.nwin; i += 256) {
         const int b = t.wlo + i;
         double val = 0.0;
@@ -106,6 +131,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
     const int lane = threadIdx.x & (kWave - 1);
     const int ng = StreamLane::blocks(t);
     const int g0 = (ng * wave) >> 2, g1 = (ng * (wave + 1)) >> 2;
+    const bool over = kOver && StreamLane::over(t, NMAX);
     StreamLane at(t, g0, lane);
     const int32_t bases = gbase[t.g0 + min(g0 + lane, ng - 1)];
     auto fetch = [&](int g) {
@@ -124,7 +150,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
         for (int k = 0; k < kLanePix; ++k) {
             const int n = (int)(bits(k) >> kStreamCountShift);
             more[k] = base = stream_coefs<NMAX>(base, n, coef, c[k]);
-            if constexpr (NMAX == kStreamUnrolled) base = stream_skip(base, n, NMAX);
+            if (over) base = stream_skip(base, n, NMAX);
         }
         word = fetch(g + 1);
         const int64_t p = t.pix0 + at.pixel(t);
@@ -141,7 +167,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
                 const double s = __fma_rn((double)c[k][j], vb[j], acc);
                 acc = n > j ? s : acc;
             }
-            if constexpr (NMAX == kStreamUnrolled) {
+            if (over) {
                 for (int j = NMAX; __ballot(n > j) != 0; ++j) {
                     T cj[1];
                     more[k] = stream_coefs<1>(more[k], n > j ? 1 : 0, coef, cj);
@@ -164,9 +190,9 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
     }
 }
 
-template <class T, int NMAX>
+template <class T, int NMAX, bool kOver>
 hipError_t adjoint_launch(const StreamAdjointLaunch& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_stream_adjoint<T, NMAX>), dim3((unsigned)(a.ntiles + a.nblanks)),
+    hipLaunchKernelGGL((k_stream_adjoint<T, NMAX, kOver>), dim3((unsigned)(a.ntiles + a.nblanks)),
                        dim3(256), 0, s, a.tiles, a.ntiles, a.blanks, a.words, a.gbase,
                        static_cast<const T*>(a.coef), static_cast<const T*>(a.U),
                        static_cast<const T*>(a.gI), static_cast<const T*>(a.gW),
@@ -176,9 +202,11 @@ hipError_t adjoint_launch(const StreamAdjointLaunch& a, hipStream_t s) {
 
 template <class T>
 hipError_t adjoint_slots(const StreamAdjointLaunch& a, hipStream_t s) {
-    if (a.max_count <= 2) return adjoint_launch<T, 2>(a, s);
-    if (a.max_count == 3) return adjoint_launch<T, 3>(a, s);
-    return adjoint_launch<T, kStreamUnrolled>(a, s);
+    if (a.slots == 2)
+        return a.over ? adjoint_launch<T, 2, true>(a, s) : adjoint_launch<T, 2, false>(a, s);
+    if (a.slots == 3)
+        return a.over ? adjoint_launch<T, 3, true>(a, s) : adjoint_launch<T, 3, false>(a, s);
+    return adjoint_launch<T, kStreamUnrolled, true>(a, s);
 }
 
 template <class T>

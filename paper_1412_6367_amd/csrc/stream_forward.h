@@ -28,28 +28,31 @@ struct UnitImage {}; // every pixel 1
 // the j-th bins of the lanes' k-th pixels are distinct LDS elements, and a
 // wavefront's LDS accesses complete in the order they are issued.  The
 // workgroup then sums its copies in a fixed order and writes the window.
+// kX: two-dimensional matrices, whose tiles end in scattered groups.
 //
 // Bound by HBM: 22.6 + 2 + 4 bytes a pixel of the 3162 x 3163 float64 frame
 // (coefficients, words, int32 counts).  The bin-major run encoding reads 4
 // bytes per run of a pixel in a band (1.45 runs a pixel) and gathers the
 // frame again for every band.
-template <class T, class Acc, class RawT, class CorrT, int NMAX>
+template <class T, class Acc, class RawT, class CorrT, int NMAX, bool kOver, bool kX>
 __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ tiles,
                                                 const uint16_t* __restrict__ words,
                                                 const int32_t* __restrict__ gbase,
                                                 const T* __restrict__ coef,
                                                 const RawT* __restrict__ img, int64_t npix,
                                                 const CorrT* __restrict__ corr,
+                                                const uint16_t* __restrict__ xpix,
                                                 Acc* __restrict__ parts) {
     constexpr bool kUnit = std::is_same<CorrT, UnitImage>::value;
     constexpr bool kCorr = !kUnit && !std::is_same<CorrT, NoCorr>::value;
     __shared__ Acc acc[4][kStreamSlots];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x & (kWave - 1);
-    const StreamTile t = tiles[xcd_block(blockIdx.x, gridDim.x)];
+    const StreamTile t = tiles[stream_tile_of(blockIdx.x, gridDim.x)];
     const int ng = StreamLane::blocks(t);
     const int g0 = (ng * wave) >> 2, g1 = (ng * (wave + 1)) >> 2;
-    const int copies = 1 << (t.shape & 255);
+    const int copies = StreamLane::copies(t);
+    const bool over = kOver && StreamLane::over(t, NMAX);
     StreamLane at(t, g0, lane);
     const int32_t bases = gbase[t.g0 + min(g0 + lane, ng - 1)];
     // where the last four pixels of the image start: no lane reads past them
@@ -73,7 +76,25 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
     };
     Acc* const own = acc[wave];
     Acc* const mine = own + (lane & (copies - 1)) * t.pitch;
+    // the first scattered group of the wavefront: its words and pixel places
+    // before, its pixels after the first block's requests
+    uint16_t xword = 0, xat = 0;
+    if constexpr (kX) {
+        if (wave < t.nx) {
+            xword = words[(int64_t)t.word0 + ng * kBlockPix + wave * kWave + lane];
+            xat = xpix[(int64_t)(t.x0 + wave) * kWave + lane];
+        }
+    }
+    auto xpixel = [&](uint16_t i) {
+        return t.pix0 + (i >> kStreamColBits) * t.w + (i & ((1 << kStreamColBits) - 1));
+    };
+    RawT xraw{};
+    CorrT xcor{};
     if (g0 < g1) fetch(g0);
+    if constexpr (kX && !kUnit) {
+        xraw = img[xpixel(xat)];
+        if constexpr (kCorr) xcor = corr[xpixel(xat)];
+    }
     for (int i = lane; i < t.pitch * copies; i += kWave) own[i].zero();
     for (int g = g0; g < g1; ++g) {
         T c[kLanePix][NMAX];
@@ -85,7 +106,7 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
         for (int k = 0; k < kLanePix; ++k) {
             const int n = (int)(bits(k) >> kStreamCountShift);
             more[k] = base = stream_coefs<NMAX>(base, n, coef, c[k]);
-            if constexpr (NMAX == kStreamUnrolled) base = stream_skip(base, n, NMAX);
+            if (over) base = stream_skip(base, n, NMAX);
         }
         T x[kLanePix];
 #pragma unroll
@@ -121,14 +142,55 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
                 }
                 lds_in_order();
             }
-            if constexpr (NMAX == kStreamUnrolled) {
-                // pixels of more bins than are unrolled
+            if (over) {
+                // pixels of more bins than are held
                 for (int j = NMAX; __ballot(n > j) != 0; ++j) {
                     T cj[1];
                     more[k] = stream_coefs<1>(more[k], n > j ? 1 : 0, coef, cj);
                     if (n > j) {
                         Acc v = p[j];
                         v.add(cj[0], x[k]);
+                        p[j] = v;
+                    }
+                    lds_in_order();
+                }
+            }
+        }
+    }
+    if constexpr (kX) {
+        for (int u = wave; u < t.nx; u += 4) {
+            if (u != wave) {
+                xword = words[(int64_t)t.word0 + ng * kBlockPix + u * kWave + lane];
+                if constexpr (!kUnit) {
+                    xat = xpix[(int64_t)(t.x0 + u) * kWave + lane];
+                    xraw = img[xpixel(xat)];
+                    if constexpr (kCorr) xcor = corr[xpixel(xat)];
+                }
+            }
+            const int n = xword >> kStreamCountShift;
+            T c[NMAX];
+            int32_t more = stream_coefs<NMAX>(gbase[t.g0 + ng + u], n, coef, c);
+            T x;
+            if constexpr (kUnit) x = T(1);
+            else if constexpr (kCorr) x = corr_apply((T)xraw, xcor);
+            else x = (T)xraw;
+            Acc* p = mine + (xword & ((1 << kStreamCountShift) - 1));
+#pragma unroll
+            for (int j = 0; j < NMAX; ++j) {
+                if (n > j) {
+                    Acc v = p[j];
+                    v.add(c[j], x);
+                    p[j] = v;
+                }
+                lds_in_order();
+            }
+            if (over) {
+                for (int j = NMAX; __ballot(n > j) != 0; ++j) {
+                    T cj[1];
+                    more = stream_coefs<1>(more, n > j ? 1 : 0, coef, cj);
+                    if (n > j) {
+                        Acc v = p[j];
+                        v.add(cj[0], x);
                         p[j] = v;
                     }
                     lds_in_order();
@@ -199,20 +261,67 @@ __global__ __launch_bounds__(B* L) void k_stream_reduce(
     if (last) write_row_u(b, a, I, W, U, empty, f, static_cast<double*>(nullptr), wfix_out);
 }
 
-template <class T, class Acc, class RawT, class CorrT, int NMAX>
+// One lane per bin, for matrices none of whose chunks is reached by more than
+// a few tiles (maps): 16 chunks a workgroup, outputs written by whole
+// wavefronts.  360000 bins of a 3162 x 3163 frame: 7.1 us, 10.7 us with four
+// lanes a bin and one chunk a workgroup; with lists of up to 40 tiles among
+// short ones (512 images of 1e2 to 1e5 pixels) it is 3 us the slower one.
+constexpr int kEachChunks = 256 / kStreamChunk;
+template <class T, class Acc>
+__global__ __launch_bounds__(256) void k_stream_reduce_each(
+    const StreamChunk* __restrict__ chunks, int32_t nchunks, const StreamEnt* __restrict__ ents,
+    const Acc* __restrict__ parts, T* __restrict__ I, T* __restrict__ W, T* __restrict__ U,
+    double empty, const double* __restrict__ ufix, const double* __restrict__ wsub,
+    double* __restrict__ wfix_out) {
+    constexpr int kFlight = 4;
+    const int c = blockIdx.x * kEachChunks + threadIdx.x / kStreamChunk;
+    const int bi = threadIdx.x & (kStreamChunk - 1);
+    if (c >= nchunks) return;
+    const StreamChunk ch = chunks[c];
+    if (bi >= ch.nbins) return;
+    const int b = ch.bin0 + bi;
+    const RowFixed f = load_row_fixed(b, ufix, wsub);
+    Acc a;
+    a.zero();
+    for (int k = ch.k0; k < ch.k1; k += kFlight) {
+        StreamEnt e[kFlight];
+#pragma unroll
+        for (int i = 0; i < kFlight; ++i) e[i] = ents[min(k + i, ch.k1 - 1)];
+        Acc v[kFlight];
+#pragma unroll
+        for (int i = 0; i < kFlight; ++i) {
+            const bool in = k + i < ch.k1 && b >= e[i].lo && b < e[i].hi;
+            v[i] = parts[in ? e[i].base + b : 0];
+            if (!in) v[i].zero();
+        }
+#pragma unroll
+        for (int i = 0; i < kFlight; ++i) a.merge(v[i]);
+    }
+    write_row_u(b, a, I, W, U, empty, f, static_cast<double*>(nullptr), wfix_out);
+}
+
+template <class T, class Acc, class RawT, class CorrT, int NMAX, bool kOver, bool kX>
 hipError_t stream_launch(const StreamLaunch& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_stream<T, Acc, RawT, CorrT, NMAX>), dim3((unsigned)a.ntiles), dim3(256),
-                       0, s, a.tiles, a.words, a.gbase, static_cast<const T*>(a.coef),
-                       static_cast<const RawT*>(a.img), a.npix,
-                       static_cast<const CorrT*>(a.corr), static_cast<Acc*>(a.parts));
+    hipLaunchKernelGGL((k_stream<T, Acc, RawT, CorrT, NMAX, kOver, kX>), dim3((unsigned)a.ntiles),
+                       dim3(256), 0, s, a.tiles, a.words, a.gbase, static_cast<const T*>(a.coef),
+                       static_cast<const RawT*>(a.img), a.npix, static_cast<const CorrT*>(a.corr),
+                       a.xpix, static_cast<Acc*>(a.parts));
     return hipGetLastError();
 }
 
 template <class T, class Acc, class RawT, class CorrT>
 hipError_t stream_slots(const StreamLaunch& a, hipStream_t s) {
-    if (a.max_count <= 2) return stream_launch<T, Acc, RawT, CorrT, 2>(a, s);
-    if (a.max_count == 3) return stream_launch<T, Acc, RawT, CorrT, 3>(a, s);
-    return stream_launch<T, Acc, RawT, CorrT, kStreamUnrolled>(a, s);
+    if constexpr (!std::is_same<CorrT, typename Pair2<T>::type>::value &&
+                  !std::is_same<CorrT, Corr12>::value) {
+        // two-dimensional matrices
+        if (a.xpix && a.slots == 2) return stream_launch<T, Acc, RawT, CorrT, 2, true, true>(a, s);
+        if (a.xpix) return stream_launch<T, Acc, RawT, CorrT, 3, true, true>(a, s);
+    }
+    if (a.slots == 2 && !a.over) return stream_launch<T, Acc, RawT, CorrT, 2, false, false>(a, s);
+    if (a.slots == 2) return stream_launch<T, Acc, RawT, CorrT, 2, true, false>(a, s);
+    if (a.slots == 3 && !a.over) return stream_launch<T, Acc, RawT, CorrT, 3, false, false>(a, s);
+    if (a.slots == 3) return stream_launch<T, Acc, RawT, CorrT, 3, true, false>(a, s);
+    return stream_launch<T, Acc, RawT, CorrT, kStreamUnrolled, true, false>(a, s);
 }
 
 template <class T, class Acc, class RawT>
@@ -264,7 +373,13 @@ hipError_t stream_forward(const StreamLaunch& a, hipStream_t s) {
     if (a.ents_per_chunk > 256) return stream_reduce<T, Acc, 4, 256>(a, s);
     if (a.ents_per_chunk > 32) return stream_reduce<T, Acc, 16, 64>(a, s);
     if (a.ents_per_chunk > 8) return stream_reduce<T, Acc, 16, 16>(a, s);
-    return stream_reduce<T, Acc, 16, 4>(a, s);
+    if (a.ents_most > 16) return stream_reduce<T, Acc, 16, 4>(a, s);
+    hipLaunchKernelGGL((k_stream_reduce_each<T, Acc>),
+                       dim3((unsigned)((a.nchunks + kEachChunks - 1) / kEachChunks)), dim3(256), 0,
+                       s, a.chunks, a.nchunks, a.ents, static_cast<const Acc*>(a.parts),
+                       static_cast<T*>(a.I), static_cast<T*>(a.W), static_cast<T*>(a.U), a.empty,
+                       a.ufix, a.wsub, a.wfix_out);
+    return hipGetLastError();
 }
 
 }  // namespace

@@ -9,8 +9,8 @@
 namespace azi {
 namespace {
 
-// Coefficients of a pixel held in registers; pixels of more bins take a loop
-// in the kernels instantiated for this many.
+// Most coefficients of a pixel that a kernel holds in registers; the tiles of
+// pixels of more bins than a kernel's take a loop.
 constexpr int kStreamUnrolled = 4;
 constexpr int kLanePix = 4;                  // neighbouring pixels of a lane
 constexpr int kBlockPix = 64 * kLanePix;
@@ -62,32 +62,45 @@ __device__ __forceinline__ Four<Corr12> load_four(const Corr12* p) {
 // A lane's place in a tile, block after block.  The block's own place is the
 // same for the whole wavefront.
 struct StreamLane {
-    int gw, gh, across;      // block width and height in pixels, blocks across the tile
+    int lgw, lrs;            // log2 of the lanes across and of the row stride
+    int across;              // blocks across the tile
     int pr, pc;              // the block's row and column of blocks
     int r0, c0;              // the lane's first pixel within the block
     int at;                  // r0 * w + c0
     __device__ StreamLane(const StreamTile& t, int block, int lane) {
-        const int lgw = (t.shape >> 8) & 255;
-        gw = kLanePix << lgw;
-        gh = 64 >> lgw;
+        lgw = (t.shape >> 4) & 15;
+        lrs = (t.shape >> 8) & 15;
         const bool rows_minor = t.shape & kStreamRowsMinor;
-        r0 = rows_minor ? lane & (gh - 1) : lane >> lgw;
+        r0 = (rows_minor ? lane & ((64 >> lgw) - 1) : lane >> lgw) << lrs;
         c0 = kLanePix * (rows_minor ? lane >> (6 - lgw) : lane & ((1 << lgw) - 1));
         at = r0 * t.w + c0;
-        across = (t.tw + gw - 1) / gw;
+        across = blocks_across(t, lgw);
         pr = block / across;
         pc = block - pr * across;
     }
-    __device__ static int blocks(const StreamTile& t) {
-        const int lgw = (t.shape >> 8) & 255;
-        return ((t.tw + (kLanePix << lgw) - 1) >> (2 + lgw)) *
-               ((t.th + (64 >> lgw) - 1) >> (6 - lgw));
+    __device__ static int blocks_across(const StreamTile& t, int lgw) {
+        return (t.tw + (kLanePix << lgw) - 1) >> (2 + lgw);
     }
+    __device__ static int blocks(const StreamTile& t) {
+        const int lgw = (t.shape >> 4) & 15, lrs = (t.shape >> 8) & 15;
+        const int lrows = 6 - lgw + lrs;
+        return blocks_across(t, lgw) * ((t.th + (1 << lrows) - 1) >> lrows << lrs);
+    }
+    // Copies of the window, and whether a pixel of the tile has more than n bins.
+    __device__ static int copies(const StreamTile& t) { return 1 << (t.shape & 15); }
+    __device__ static bool over(const StreamTile& t, int n) {
+        return (t.shape >> kStreamMostShift) > n;
+    }
+    // The block's first row and column in the tile.
+    __device__ int row() const {
+        return (pr >> lrs << (6 - lgw + lrs)) + (pr & ((1 << lrs) - 1));
+    }
+    __device__ int column() const { return pc << (2 + lgw); }
     // The lane's first pixel, counted from the tile's first.
-    __device__ int pixel(const StreamTile& t) const { return pr * gh * t.w + pc * gw + at; }
+    __device__ int pixel(const StreamTile& t) const { return row() * t.w + column() + at; }
     // Pixels of the lane that the tile has (0 or less: none).
     __device__ int inside(const StreamTile& t) const {
-        return pr * gh + r0 < t.th ? t.tw - pc * gw - c0 : 0;
+        return row() + r0 < t.th ? t.tw - column() - c0 : 0;
     }
     __device__ void next() {
         ++pc;
@@ -96,6 +109,16 @@ struct StreamLane {
         pr += wrap ? 1 : 0;
     }
 };
+
+// The tile of workgroup g of n.  Workgroup g runs on XCD g % 8; of every 64
+// tiles each XCD takes 8 neighbours, which share the image lines at their
+// edges in its L2.  Tiles differ in work with their place in the image, so an
+// XCD's share is spread over it (one contiguous eighth of the tiles each:
+// 1000 x 360 bins of a 3162 x 3163 frame 86 us a pass, a tile at a time 77 us
+// with half as many bytes again read).
+__device__ inline int64_t stream_tile_of(uint32_t g, uint32_t n) {
+    return g < (n & ~63u) ? (g & ~63u) + (g & 7) * 8 + ((g >> 3) & 7) : g;
+}
 
 // The first N coefficients of one pixel of every lane (n bins each), those of
 // the wavefront starting at base; returns where the next pixels' start when
