@@ -40,17 +40,20 @@ int hip_fail(hipError_t e, const char* what) {
         if (e_ != hipSuccess) return hip_fail(e_, what); \
     } while (0)
 
-// Device allocation owned by a plan or batch.
+int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
+
+// Device allocation owned by a plan or batch, or (view) a part of one.
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
     int device = -1;
+    bool view = false;
     DevBuf() = default;
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
     ~DevBuf() { release(); }
     void release() {
-        if (p) {
+        if (p && !view) {
             int cur = -1;
             (void)hipGetDevice(&cur);
             if (cur != device) (void)hipSetDevice(device);
@@ -59,6 +62,7 @@ struct DevBuf {
         }
         p = nullptr;
         bytes = 0;
+        view = false;
     }
     hipError_t alloc(size_t n, int dev) {
         release();
@@ -79,6 +83,47 @@ struct DevBuf {
     }
     template <class T>
     T* as() const { return static_cast<T*>(p); }
+};
+
+// Several buffers cut from one allocation: the device plan builder's arrays
+// (an allocation freed costs about 0.1 ms, 32 of them a third of the build of
+// a 1e6-pixel plan).
+struct Slab {
+    struct Part {
+        DevBuf* buf;
+        size_t at, bytes;
+        const void* src;
+    };
+    std::vector<Part> parts;
+    size_t bytes = 0;
+    // A buffer of n bytes; with src, holding the n host bytes there.
+    void add(DevBuf& b, size_t n, const void* src = nullptr) {
+        if (n == 0) n = 256, src = nullptr;
+        parts.push_back(Part{&b, bytes, n, src});
+        bytes += (size_t)round_up((int64_t)n, 256);
+    }
+    // Allocates them in `own`; the ones with host data go up in one copy.
+    hipError_t place(DevBuf& own, int dev) {
+        const hipError_t e = own.alloc(bytes, dev);
+        if (e != hipSuccess) return e;
+        size_t lo = bytes, hi = 0;
+        for (const Part& q : parts) {
+            q.buf->release();
+            q.buf->p = own.as<char>() + q.at;
+            q.buf->bytes = q.bytes;
+            q.buf->device = dev;
+            q.buf->view = true;
+            if (q.src) {
+                lo = std::min(lo, q.at);
+                hi = std::max(hi, q.at + q.bytes);
+            }
+        }
+        if (lo >= hi) return hipSuccess;
+        std::vector<char> host(hi - lo, 0);
+        for (const Part& q : parts)
+            if (q.src) std::memcpy(host.data() + (q.at - lo), q.src, q.bytes);
+        return hipMemcpy(own.as<char>() + lo, host.data(), hi - lo, hipMemcpyHostToDevice);
+    }
 };
 
 // Makes `dev` current for the lifetime of the guard, restoring the caller's.
@@ -103,8 +148,6 @@ constexpr int64_t kPad = 64;  // nonzero arrays: instance starts on 64, 64 spare
 // with two vector loads whatever the pixel's count: its coefficient array
 // and bin-value vector keep this many spare elements at the end.
 constexpr int64_t kAdjPad = 4;
-
-int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 size_t elem_size(int32_t dtype) { return dtype == AZI_F64 ? 8 : 4; }
 
@@ -436,6 +479,7 @@ struct azi_plan {
         fbin_ptr, fparts, corr, cfirst, rgbase, fcoef, ufix, wdark;
     int32_t nstiles = 0, nbtiles = 0, npieces = 0, band_rows = 8, nftiles = 0;
     StreamBufs stream;    // run layout, library-sized tilings: replaces the run encoding
+    DevBuf slab, slab2;   // a device-built plan's arrays, until it is uploaded again
     bool folded = false;  // run layout, AZI_STAGE_FOLD(_SUM), corrections set
     int32_t max_count = INT32_MAX;  // largest number of band partials of a bin
     int32_t corr_kind = azi::kCorrPair;
@@ -1229,50 +1273,39 @@ int download(std::vector<T>& dst, const void* src, int64_t n, hipStream_t s) {
 }
 }  // extern "C++"
 
-// Band layout from the pixel-major entries: a stable sort by band orders
-// each band's entries by (pixel, bin); the pieces come from the band starts,
-// which are the row pointers of the bands' first rows.
-int plan_device_bands(azi_plan* p, const int32_t* rowidx, const int32_t* pix, const double* cdata,
-                      int64_t nnz, DevBuf& work, DevBuf& skeys, DevBuf& perm, hipStream_t s) {
-    const int32_t R = band_rows_of(p->tiling);
-    p->band_rows = R;
-    if (p->m.npix >= ((int64_t)1 << azi::kBandShift))
-        return fail(AZI_EOVERFLOW, "the band layout takes images below 2^27 pixels");
-    if (nnz + kPad >= (int64_t)INT32_MAX)
-        return fail(AZI_EOVERFLOW, "band matrix exceeds 2^31 entries or pieces");
-    const int32_t npt = p->m.npt;
-    const int32_t nbands = (npt + R - 1) / R;
-    const int dev = p->device;
-    const size_t es = elem_size(p->dtype);
-    DevBuf keys;
-    AZI_HIP(keys.alloc((size_t)std::max<int64_t>(nnz, 1) * 4, dev), "band keys");
-    AZI_HIP(azi::launch_div(rowidx, nnz, R, keys.as<int32_t>(), s), "band keys");
-    AZI_HIP(azi::launch_sort(keys.as<int32_t>(), nnz, bit_length(nbands - 1), skeys.as<int32_t>(),
-                             perm.as<int32_t>(), work.p, s), "band sort");
-    AZI_HIP(p->npacked.alloc((size_t)(nnz + kPad) * 4, dev), "band entries");
-    AZI_HIP(p->ncoef.alloc((size_t)(nnz + kPad) * es, dev), "band coefficients");
-    AZI_HIP(azi::launch_band_entries(perm.as<int32_t>(), nnz, nnz + kPad, rowidx, pix, cdata, R,
-                                     p->npacked.as<int32_t>(), p->ncoef.p, p->dtype, s),
-            "band entries");
-    try {
+// The pieces of a device-built plan's band layout (the bands' starts are the
+// row pointers of their first rows) and its tile schedule, placed together.
+int plan_device_schedules(azi_plan* p, int64_t nnz, bool bands) {
+    azi::BandMatrix bm;
+    std::vector<azi::Tile> tiles;
+    std::vector<azi::Split> splits;
+    int32_t nparts = 0;
+    Slab slab;
+    if (bands) {
+        const int32_t R = p->band_rows, nbands = (p->m.npt + R - 1) / R;
         std::vector<int64_t> start((size_t)nbands + 1);
         for (int32_t b = 0; b < nbands; ++b) start[b] = p->m.indptr[(size_t)b * R];
         start[nbands] = nnz;
-        azi::BandMatrix bm;
-        azi::band_pieces(start.data(), nbands, npt, R, piece_nnz(p->tiling, nnz), 0, 0, 0, bm);
-        AZI_HIP(p->npieces_buf.upload(bm.pieces.data(), bm.pieces.size() * sizeof(azi::BandPiece),
-                                      dev), "band pieces");
-        AZI_HIP(p->bin_slot.upload(bm.bin_slot.data(), bm.bin_slot.size() * 4, dev), "bin slots");
-        p->max_count = INT32_MAX;
-        AZI_HIP(p->bin_count.upload(bm.bin_count.data(), bm.bin_count.size() * 4, dev),
-                "bin counts");
-        p->max_count = max_count_of(bm.bin_count);
-        AZI_HIP(p->nparts_buf.alloc((size_t)std::max(bm.nslots, 1) * 16, dev), "band partials");
-        p->npieces = (int32_t)bm.pieces.size();
-    } catch (const std::bad_alloc&) {
-        return fail(AZI_ENOMEM, "out of host memory building the band pieces");
+        azi::band_pieces(start.data(), nbands, p->m.npt, R, piece_nnz(p->tiling, nnz), 0, 0, 0, bm);
+        slab.add(p->npieces_buf, bm.pieces.size() * sizeof(azi::BandPiece), bm.pieces.data());
+        slab.add(p->bin_slot, bm.bin_slot.size() * 4, bm.bin_slot.data());
+        slab.add(p->bin_count, bm.bin_count.size() * 4, bm.bin_count.data());
     }
-    AZI_HIP(hipStreamSynchronize(s), "band layout");
+    azi::build_tiles(p->m.indptr.data(), p->m.npt, 0, 0, 0, piece_nnz(p->tiling, nnz),
+                     p->tiling.band, tiles, splits, nparts);
+    slab.add(p->tiles, tiles.size() * sizeof(azi::Tile), tiles.data());
+    slab.add(p->splits, splits.size() * sizeof(azi::Split), splits.data());
+    slab.add(p->parts, (size_t)std::max(nparts, 1) * 16);
+    if (bands) slab.add(p->nparts_buf, (size_t)std::max(bm.nslots, 1) * 16);
+    p->max_count = INT32_MAX;
+    AZI_HIP(slab.place(p->slab2, p->device), "schedules");
+    if (bands) {
+        p->max_count = max_count_of(bm.bin_count);
+        p->npieces = (int32_t)bm.pieces.size();
+    }
+    p->ntiles = (int32_t)tiles.size();
+    p->nsplits = (int32_t)splits.size();
+    p->nparts = nparts;
     return AZI_OK;
 }
 
@@ -1299,11 +1332,17 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     m.npix = npix;
     const bool boxes = p->split != AZI_SPLIT_NONE;
     const int64_t nblk = (npix + azi::kBuildBlock - 1) / azi::kBuildBlock;
-    DevBuf lo, hi, bmin, bmax, r2, cnt, scanw, tot;
-    AZI_HIP(lo.alloc((size_t)npix * 8, device), "extents");
-    AZI_HIP(hi.alloc(boxes ? (size_t)npix * 8 : 8, device), "extents");
-    AZI_HIP(bmin.alloc((size_t)nblk * 8, device), "block minima");
-    AZI_HIP(bmax.alloc((size_t)nblk * 8, device), "block maxima");
+    DevBuf temp, lo, hi, bmin, bmax, r2, cnt, scanw, tot;
+    Slab first;
+    first.add(lo, (size_t)npix * 8);
+    first.add(hi, boxes ? (size_t)npix * 8 : 8);
+    first.add(bmin, (size_t)nblk * 8);
+    first.add(bmax, (size_t)nblk * 8);
+    first.add(r2, 16);
+    first.add(cnt, (size_t)npix * 4);
+    first.add(scanw, azi::scan_work_bytes(npix));
+    first.add(tot, 16);  // entries, then the flag of launch_first
+    AZI_HIP(first.place(temp, device), "extents and counts");
     AZI_HIP(azi::launch_extents(g, p->unit, p->split, lo.as<double>(), hi.as<double>(),
                                 bmin.as<double>(), bmax.as<double>(), s), "extents");
     double pr[2];
@@ -1311,7 +1350,6 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
         pr[0] = range2[0];
         pr[1] = range2[1];
     } else {
-        AZI_HIP(r2.alloc(16, device), "range");
         AZI_HIP(azi::launch_minmax(bmin.as<double>(), bmax.as<double>(), nblk, r2.as<double>(), s),
                 "range");
         AZI_HIP(hipMemcpyAsync(pr, r2.p, 16, hipMemcpyDeviceToHost, s), "range");
@@ -1322,13 +1360,10 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     m.pmin = pr[0];
     m.pmax = pr[1];
     const double delta = (m.pmax - m.pmin) / npt;
-    AZI_HIP(cnt.alloc((size_t)npix * 4, device), "entry counts");
     const int32_t nazim = two_d ? npt_azim : 0;
     AZI_HIP(azi::launch_count(g, p->unit, p->split, lo.as<double>(), hi.as<double>(), m.pmin, delta,
                               npt, nazim, cnt.as<int32_t>(), s), "entry counts");
     AZI_HIP(p->colptr.alloc((size_t)(npix + 1) * 4, device), "colptr");
-    AZI_HIP(scanw.alloc(azi::scan_work_bytes(npix), device), "scan work");
-    AZI_HIP(tot.alloc(8, device), "scan total");
     AZI_HIP(azi::launch_scan(cnt.as<int32_t>(), npix, p->colptr.as<int32_t>(), tot.as<int64_t>(),
                              scanw.p, s), "scan");
     int64_t nnz = 0;
@@ -1336,74 +1371,108 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     AZI_HIP(hipStreamSynchronize(s), "scan total");
     if (nnz >= (int64_t)INT32_MAX - 2 * kPad)
         return fail(AZI_EOVERFLOW, "matrix has 2^31 nonzeros or more");
-    cnt.release();
+    // the band layout's own bands of 4 bins for one-dimensional plans (band 16
+    // means four neighbouring bands per workgroup only in the run layout);
+    // two-dimensional ones, whose rows are short, as host-built ones
+    if (two_d) {
+        p->layout = AZI_LAYOUT_PIXEL;
+        p->tiling = kDefaultTiling2d;
+    } else {
+        p->layout = AZI_LAYOUT_BAND;
+        p->tiling.band = 4;
+        p->band_rows = band_rows_of(p->tiling);
+        if (npix >= ((int64_t)1 << azi::kBandShift))
+            return fail(AZI_EOVERFLOW, "the band layout takes images below 2^27 pixels");
+    }
+    const int32_t R = p->band_rows;
     const int64_t nnz_alloc = round_up(nnz, kPad) + kPad;
     const size_t es = elem_size(p->dtype);
     const size_t n1 = (size_t)std::max<int64_t>(nnz, 1);
-    DevBuf cdata64, pix, work, skeys, perm, data64;
-    AZI_HIP(p->rowidx.alloc(n1 * 4, device), "rowidx");
-    AZI_HIP(cdata64.alloc(n1 * 8, device), "coefficients");
-    AZI_HIP(pix.alloc(n1 * 4, device), "pixel ids");
+    const bool f64 = p->dtype == AZI_F64;
+    Slab kept, work_parts;
+    kept.add(p->rowidx, n1 * 4);
+    kept.add(p->rowptr, (size_t)(m.npt + 1) * 4);
+    kept.add(p->indices, (size_t)nnz_alloc * 4);
+    kept.add(p->data, (size_t)nnz_alloc * es);
+    kept.add(p->cdata, (n1 + kAdjPad) * es);
+    if (!two_d) {
+        kept.add(p->cfirst, (size_t)npix * 4);
+        kept.add(p->npacked, (size_t)(nnz + kPad) * 4);
+        kept.add(p->ncoef, (size_t)(nnz + kPad) * es);
+    }
+    kept.add(p->xwork, (size_t)npix * es);
+    kept.add(p->vwork, (size_t)(m.npt + kAdjPad) * 8);
+    AZI_HIP(kept.place(p->slab, device), "matrix");
+    DevBuf temp2, cdata64, pix, work, skeys, perm, data64, keys;
+    if (!f64) work_parts.add(cdata64, n1 * 8);
+    if (!f64) work_parts.add(data64, n1 * 8);
+    work_parts.add(pix, n1 * 4);
+    work_parts.add(work, azi::sort_work_bytes(nnz));
+    work_parts.add(skeys, n1 * 4);
+    work_parts.add(perm, n1 * 4);
+    if (!two_d) work_parts.add(keys, n1 * 4);
+    AZI_HIP(work_parts.place(temp2, device), "sort work");
+    // float64 plans: the doubles are the storage copy
+    double* c64 = f64 ? p->cdata.as<double>() : cdata64.as<double>();
     AZI_HIP(azi::launch_fill(g, p->unit, p->split, lo.as<double>(), hi.as<double>(), m.pmin, delta,
-                             npt, nazim, p->colptr.as<int32_t>(), p->rowidx.as<int32_t>(),
-                             cdata64.as<double>(), pix.as<int32_t>(), s), "fill");
+                             npt, nazim, p->colptr.as<int32_t>(), p->rowidx.as<int32_t>(), c64,
+                             pix.as<int32_t>(), s), "fill");
+    if (!f64) AZI_HIP(azi::launch_to_storage(c64, nnz, p->cdata.p, p->dtype, s), "cdata");
+    int32_t* flag = reinterpret_cast<int32_t*>(tot.as<char>() + 8);
+    if (!two_d) {
+        AZI_HIP(hipMemsetAsync(flag, 0, 4, s), "first bins");
+        AZI_HIP(azi::launch_first(p->colptr.as<int32_t>(), p->rowidx.as<int32_t>(), npix,
+                                  p->cfirst.as<int32_t>(), flag, s), "first bins");
+    }
     // bin-major order: stable sort of the pixel-major entries by bin
-    AZI_HIP(work.alloc(azi::sort_work_bytes(nnz), device), "sort work");
-    AZI_HIP(skeys.alloc(n1 * 4, device), "sorted bins");
-    AZI_HIP(perm.alloc(n1 * 4, device), "permutation");
     AZI_HIP(azi::launch_sort(p->rowidx.as<int32_t>(), nnz, bit_length(m.npt - 1),
                              skeys.as<int32_t>(), perm.as<int32_t>(), work.p, s), "sort");
-    AZI_HIP(p->rowptr.alloc((size_t)(m.npt + 1) * 4, device), "indptr");
     AZI_HIP(azi::launch_bounds(skeys.as<int32_t>(), nnz, m.npt, p->rowptr.as<int32_t>(), s),
             "indptr");
-    AZI_HIP(p->indices.alloc((size_t)nnz_alloc * 4, device), "indices");
-    AZI_HIP(p->data.alloc((size_t)nnz_alloc * es, device), "data");
-    if (p->dtype != AZI_F64) AZI_HIP(data64.alloc(n1 * 8, device), "data (double)");
-    AZI_HIP(azi::launch_gather(perm.as<int32_t>(), nnz, nnz_alloc, pix.as<int32_t>(),
-                               cdata64.as<double>(), p->indices.as<int32_t>(), p->data.p,
-                               p->dtype, p->dtype != AZI_F64 ? data64.as<double>() : nullptr, s),
-            "gather");
-    AZI_HIP(p->cdata.alloc((n1 + kAdjPad) * es, device), "cdata");
-    AZI_HIP(azi::launch_to_storage(cdata64.as<double>(), nnz, p->cdata.p, p->dtype, s), "cdata");
+    AZI_HIP(azi::launch_gather(perm.as<int32_t>(), nnz, nnz_alloc, pix.as<int32_t>(), c64,
+                               p->indices.as<int32_t>(), p->data.p, p->dtype,
+                               f64 ? nullptr : data64.as<double>(), s), "gather");
+    if (!two_d) {
+        // band order: a stable sort by band leaves each band's entries in
+        // (pixel, bin) order
+        AZI_HIP(azi::launch_div(p->rowidx.as<int32_t>(), nnz, R, keys.as<int32_t>(), s),
+                "band keys");
+        AZI_HIP(azi::launch_sort(keys.as<int32_t>(), nnz, bit_length((m.npt + R - 1) / R - 1),
+                                 skeys.as<int32_t>(), perm.as<int32_t>(), work.p, s), "band sort");
+        AZI_HIP(azi::launch_band_entries(perm.as<int32_t>(), nnz, nnz + kPad,
+                                         p->rowidx.as<int32_t>(), pix.as<int32_t>(), c64, R,
+                                         p->npacked.as<int32_t>(), p->ncoef.p, p->dtype, s),
+                "band entries");
+    }
     // host copy of the matrix, for export and for the host-side layouts
+    int32_t scattered = 0;
     try {
         int rc = download(m.colptr, p->colptr.p, npix + 1, s);
         if (rc == AZI_OK) rc = download(m.rowidx, p->rowidx.p, nnz, s);
-        if (rc == AZI_OK) rc = download(m.cdata, cdata64.p, nnz, s);
+        if (rc == AZI_OK) rc = download(m.cdata, c64, nnz, s);
         if (rc == AZI_OK) rc = download(m.indptr, p->rowptr.p, (int64_t)m.npt + 1, s);
         if (rc == AZI_OK) rc = download(m.indices, p->indices.p, nnz, s);
-        if (rc == AZI_OK)
-            rc = download(m.data, p->dtype == AZI_F64 ? p->data.p : data64.p, nnz, s);
+        if (rc == AZI_OK) rc = download(m.data, f64 ? p->data.p : data64.p, nnz, s);
         if (rc != AZI_OK) return rc;
+        if (!two_d)
+            AZI_HIP(hipMemcpyAsync(&scattered, flag, 4, hipMemcpyDeviceToHost, s), "first bins");
         AZI_HIP(hipStreamSynchronize(s), "download the matrix");
-        rc = upload_first(m, device, p->cfirst);
-        if (rc != AZI_OK) return rc;
     } catch (const std::bad_alloc&) {
         return fail(AZI_ENOMEM, "out of host memory for the matrix copy");
     }
-    data64.release();
+    if (scattered) p->cfirst.release();
     p->order.release();
     p->used = npix;
-    AZI_HIP(p->xwork.alloc((size_t)npix * es, device), "work image");
-    AZI_HIP(p->vwork.alloc((size_t)(m.npt + kAdjPad) * 8, device), "work vector");
-    if (two_d) {
-        // short rows: the plain CSR with whole rows per tile, as for
-        // host-built two-dimensional plans
-        p->layout = AZI_LAYOUT_PIXEL;
-        p->tiling = kDefaultTiling2d;
-        bool streamed = false;
-        const int rcs = plan_upload_stream(p, &streamed);
-        if (rcs != AZI_OK) return rcs;
-        return plan_upload_tiles(p);
+    try {
+        if (two_d) {
+            bool streamed = false;
+            const int rc = plan_upload_stream(p, &streamed);
+            if (rc != AZI_OK) return rc;
+        }
+        return plan_device_schedules(p, nnz, !two_d);
+    } catch (const std::bad_alloc&) {
+        return fail(AZI_ENOMEM, "out of host memory building the schedules");
     }
-    // the band layout's own bands of 4 bins (band 16 means four neighbouring
-    // bands per workgroup only in the run layout)
-    p->layout = AZI_LAYOUT_BAND;
-    p->tiling.band = 4;
-    int rc = plan_device_bands(p, p->rowidx.as<int32_t>(), pix.as<int32_t>(), cdata64.as<double>(),
-                               nnz, work, skeys, perm, s);
-    if (rc != AZI_OK) return rc;
-    return plan_upload_tiles(p);
 }
 }  // namespace
 
@@ -1658,6 +1727,13 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
     DeviceGuard g(device);
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
     p->device = device;
+    for (DevBuf* b : {&p->colptr, &p->rowidx, &p->rowptr, &p->indices, &p->data, &p->cdata,
+                      &p->cfirst, &p->npacked, &p->ncoef, &p->xwork, &p->vwork, &p->npieces_buf,
+                      &p->bin_slot, &p->bin_count, &p->tiles, &p->splits, &p->parts,
+                      &p->nparts_buf})
+        if (b->view) b->release();
+    p->slab.release();
+    p->slab2.release();
     auto body = [&]() -> int {
         const int64_t nnz = p->m.nnz();
         const int64_t nnz_alloc = round_up(nnz, kPad) + kPad;

@@ -62,6 +62,10 @@ hipError_t launch_band_entries(const int32_t* perm, int64_t n, int64_t n_alloc,
                                const int32_t* rowidx, const int32_t* pix, const double* cdata,
                                int32_t R, int32_t* packed, void* coef, int32_t dtype,
                                hipStream_t s);
+// first[p] = bin of pixel p's first entry (0 without entries); *flag
+// (device int32, zero before) = 1 where some pixel's bins are not consecutive.
+hipError_t launch_first(const int32_t* colptr, const int32_t* rowidx, int64_t npix,
+                        int32_t* first, int32_t* flag, hipStream_t s);
 // Storage copy of double values (float or double).
 hipError_t launch_to_storage(const double* in, int64_t n, void* out, int32_t dtype,
                              hipStream_t s);

@@ -313,6 +313,22 @@ __global__ void k_band_entries(const int32_t* perm, int64_t n, int64_t n_alloc,
     }
 }
 
+// The bins of a pixel ascend, so they are consecutive when the last is as far
+// from the first as the entries are many. One lane per pixel; bound by the
+// scattered read of a pixel's first and last bin, a few us at 1e6 pixels,
+// where the host pass over the downloaded matrix and the upload of its result
+// took about 1.5 ms of a 1024 x 1024 plan's build (23.4 ms before, 18.1 ms
+// with this and the buffers cut from five allocations instead of 24).
+__global__ void k_first(const int32_t* colptr, const int32_t* rowidx, int64_t npix,
+                        int32_t* first, int32_t* flag) {
+    const int64_t p = (int64_t)blockIdx.x * kB + threadIdx.x;
+    if (p >= npix) return;
+    const int32_t k0 = colptr[p], k1 = colptr[p + 1];
+    const int32_t b = k1 > k0 ? rowidx[k0] : 0;
+    first[p] = b;
+    if (k1 > k0 && rowidx[k1 - 1] - b != k1 - 1 - k0) *flag = 1;  // every writer the same 1
+}
+
 template <class T>
 __global__ void k_to_storage(const double* in, int64_t n, T* out) {
     const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
@@ -466,6 +482,14 @@ hipError_t launch_band_entries(const int32_t* perm, int64_t n, int64_t n_alloc,
         hipLaunchKernelGGL(k_band_entries<float>, dim3(blocks_for(n_alloc)), dim3(kB), 0, s,
                            perm, n, n_alloc, rowidx, pix, cdata, R, packed,
                            static_cast<float*>(coef));
+    return hipGetLastError();
+}
+
+hipError_t launch_first(const int32_t* colptr, const int32_t* rowidx, int64_t npix,
+                        int32_t* first, int32_t* flag, hipStream_t s) {
+    if (!grid_fits(npix)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_first, dim3(blocks_for(npix)), dim3(kB), 0, s, colptr, rowidx, npix,
+                       first, flag);
     return hipGetLastError();
 }
 
