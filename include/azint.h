@@ -622,7 +622,12 @@ int azi_graph_create_batch(azi_batch* batch, const void* x, void* out_I, void* o
                            const void* grad_W, void* grad_x, void* stream,
                            azi_graph** out);
 
-/* Capture one plan's raw-image pipeline (azi_integrate1d_raw) into a graph. */
+/*
+ * Capture one plan's raw-image pipeline (azi_integrate1d_raw) into a graph.
+ * A pass of two kernels (the stream encoding) is recorded as their launches
+ * with these arguments, which costs less to replay; it may be replayed into
+ * a capturing stream.
+ */
 int azi_graph_create_plan(const azi_plan* plan, const void* raw, int32_t raw_dtype,
                           void* out_I, void* out_W, void* out_U, double empty,
                           void* stream, azi_graph** out);

@@ -146,3 +146,50 @@ def test_stream_adjoint_bits_equal_entry_adjoint(g, dtype, dev):
             b = entries.backward(U, *grads, wrt_raw=wrt_raw, out=out[1])
             torch.cuda.synchronize()
             assert torch.equal(a, b), (grads[0] is None, grads[1] is None, wrt_raw)
+
+
+@pytest.mark.parametrize("dim", ["1d-fold_sum", "1d-fuse", "2d"])
+def test_stream_graph_replays(dim, dev):
+    """A captured frame pass replays on what its buffers hold now: with eager
+    work between, on other streams, from another thread, and recorded into a
+    torch graph; each replay gives the eager bits."""
+    import threading
+    az = azint()
+    h, w, npt = 130, 141, 100
+    kw = dict(npt_azim=12) if dim == "2d" else {}
+    plan = az.Plan(h, w, npt, device=dev, **kw)
+    rng = np.random.default_rng(11)
+    t = lambda a: torch.from_numpy(a).to(dev)
+    if dim != "2d":
+        plan.set_tiling(stage=dim[3:])
+    plan.set_corrections(dark=t(rng.integers(0, 60, h * w).astype(np.float64)),
+                         flat=t(rng.uniform(0.9, 1.1, h * w)))
+    frames = [t(rng.integers(60, 30000, h * w).astype(np.int32)) for _ in range(5)]
+    want = [[o.clone() for o in plan.integrate_raw(f, empty=7.0)] for f in frames]
+    raw, outs = frames[0].clone(), [torch.empty_like(o) for o in want[0]]
+    graph = plan.graph(raw, *outs, empty=7.0)
+    side = torch.cuda.Stream()
+
+    def replay(k, how):
+        raw.copy_(frames[k])
+        for o in outs:
+            o.zero_()
+        torch.cuda.synchronize()
+        how()
+        torch.cuda.synchronize()
+        for a, b in zip(outs, want[k]):
+            assert torch.equal(a, b), (k, how)
+
+    def thread():
+        worker = threading.Thread(target=graph.launch)
+        worker.start()
+        worker.join()
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        graph.launch()
+    for k, how in enumerate((graph.launch, lambda: graph.launch(side), thread, g.replay, g.replay)):
+        replay(k, how)
+        _ = (raw * 2).sum().item()
+    with pytest.raises(az.AzintError):
+        plan.graph(raw, None)
