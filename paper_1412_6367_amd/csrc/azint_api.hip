@@ -387,17 +387,34 @@ int upload_stream(const azi::StreamMatrix& sm, bool two_d, int64_t npt, int32_t 
                   int32_t accum, int device, const DevBuf& colptr, const DevBuf& cdata,
                   StreamBufs& b) {
     b.release();
-    std::vector<char> host;
-    auto put = [&host](const auto& v) {
-        const size_t at = host.size(), n = v.size() * sizeof(v[0]);
-        host.resize(at + round_up((int64_t)n, 16));
-        if (n) std::memcpy(host.data() + at, v.data(), n);
+    struct Part {
+        const void* src;
+        size_t at, bytes;
+    };
+    std::vector<Part> host;
+    size_t total = 0;
+    auto put = [&](const auto& v) {
+        const size_t at = total, n = v.size() * sizeof(v[0]);
+        host.push_back(Part{v.data(), at, n});
+        total += round_up((int64_t)n, 16);
         return at;
     };
     const size_t tiles = put(sm.tiles), blanks = put(sm.blanks), chunks = put(sm.chunks), ents = put(sm.ents),
                  gbase = put(sm.gbase), words = put(sm.words), xpix = put(sm.xpix),
                  xsrc = put(sm.xsrc);
-    AZI_HIP(b.built.upload(host.data(), host.size(), device), "stream encoding");
+    // small ones in one copy, the large without another copy on the host
+    if (total <= ((size_t)1 << 20)) {
+        std::vector<char> one(total);
+        for (const Part& q : host)
+            if (q.bytes) std::memcpy(one.data() + q.at, q.src, q.bytes);
+        AZI_HIP(b.built.upload(one.data(), total, device), "stream encoding");
+    } else {
+        AZI_HIP(b.built.alloc(total, device), "stream encoding");
+        for (const Part& q : host)
+            if (q.bytes)
+                AZI_HIP(hipMemcpy(b.built.as<char>() + q.at, q.src, q.bytes, hipMemcpyHostToDevice),
+                        "stream encoding");
+    }
     const char* d = b.built.as<char>();
     b.tiles = reinterpret_cast<const azi::StreamTile*>(d + tiles);
     b.blanks = reinterpret_cast<const azi::StreamTile*>(d + blanks);

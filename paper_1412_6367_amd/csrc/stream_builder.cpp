@@ -57,6 +57,8 @@ struct Builder {
     StreamMatrix sm;
     std::vector<uint64_t> lanes;          // per bin of the window: lanes whose pixel starts there
     std::vector<int32_t> touched;
+    std::vector<uint64_t> seen;           // per bin and copy: the last access that met it
+    uint64_t access = 0;
     std::vector<int32_t> first;           // the current tile's pixels, row-major: first bin of
     std::vector<int32_t> count;           // the window and number of bins,
     std::vector<int32_t> radial;          // first radial bin
@@ -64,10 +66,12 @@ struct Builder {
     std::vector<int32_t> wedges;
     std::vector<Item> items;
     int32_t th = 0, tw = 0;
+    int32_t wlast = 0, wrow = 0;          // a wedge and its first row
 
     Builder(const HostMatrix& m, int32_t w, int64_t pix_off, int64_t bin_off)
         : m(m), w(w), pix_off(pix_off), bin_off(bin_off) {
         lanes.assign((size_t)kStreamSlots + kStreamMaxCount, 0);
+        seen.assign(lanes.size() << 6, 0);
         if (m.two_d) widx.assign((size_t)m.npt_azim, -1);
     }
 
@@ -108,8 +112,24 @@ struct Builder {
         touched.clear();
         return lk;
     }
+    // Whether 2^lk copies are too few for block g.  Most blocks need no more
+    // than those before them, and this costs a fifth of finding the number.
+    bool clashes(Shape s, int32_t g, int32_t lk) {
+        const int32_t low = (1 << lk) - 1;
+        bool clash = false;
+        for (int32_t k = 0; k < 4 && !clash; ++k) {
+            ++access;
+            each(s, g, k, [&](int32_t e, int32_t lane) {
+                uint64_t& last = seen[(size_t)(first[e] << lk | (lane & low))];
+                clash |= last == access;
+                last = access;
+            });
+        }
+        return clash;
+    }
     // The copies block g needs, at least lk.
     int32_t block_copies(Shape s, int32_t g, int32_t lk) {
+        if (!clashes(s, g, lk)) return lk;
         for (int32_t k = 0; k < 4; ++k) {
             each(s, g, k, [&](int32_t e, int32_t lane) { touch(first[e], lane); });
             lk = settle(lk);
@@ -117,11 +137,22 @@ struct Builder {
         return lk;
     }
 
+    // Wedge of a row; the last one's rows are kept, neighbours mostly share it
+    // (a division per entry was a third of this pass).
+    int32_t wedge_of(int32_t row) {
+        if (row < wrow || row - wrow >= m.npt_rad) {
+            wlast = row / m.npt_rad;
+            wrow = wlast * m.npt_rad;
+        }
+        return wlast;
+    }
     // End of the run of a two-dimensional pixel's entries starting at k.
-    int32_t run_end(int32_t k, int32_t k1) const {
-        int32_t e = k + 1;
-        while (e < k1 && m.rowidx[e] == m.rowidx[e - 1] + 1 && m.rowidx[e] % m.npt_rad != 0) ++e;
-        return e;
+    int32_t run_end(int32_t k, int32_t k1) {
+        wedge_of(m.rowidx[k]);
+        const int32_t row = m.rowidx[k], most = std::min(k1 - k, wrow + m.npt_rad - row);
+        int32_t n = 1;
+        while (n < most && m.rowidx[k + n] == row + n) ++n;
+        return k + n;
     }
 
     // Scattered groups of the sorted items: item i goes to group i % groups, so
@@ -167,7 +198,7 @@ struct Builder {
                 bool main = true;
                 while (k0 < k1) {
                     const int32_t z = run_end(k0, k1);
-                    const int32_t a = m.rowidx[k0] % m.npt_rad, wedge = m.rowidx[k0] / m.npt_rad;
+                    const int32_t wedge = wedge_of(m.rowidx[k0]), a = m.rowidx[k0] - wrow;
                     lo = std::min(lo, a);
                     hi = std::max(hi, a + z - k0);
                     most = std::max(most, z - k0);
@@ -204,7 +235,8 @@ struct Builder {
             std::sort(wedges.begin(), wedges.end());
             for (size_t k = 0; k < wedges.size(); ++k) widx[wedges[k]] = (int32_t)k * span;
             auto local = [&](int32_t row) {
-                return widx[row / m.npt_rad] + row % m.npt_rad - lo;
+                const int32_t at = widx[wedge_of(row)];
+                return at + row - wrow - lo;
             };
             for (int32_t e = 0; e < n; ++e)
                 if (count[e]) first[e] = local(first[e]);
@@ -299,12 +331,12 @@ struct Builder {
             most = 0;
         };
         for (int32_t k = m.colptr[p]; k < k1;) {
-            const int32_t z = run_end(k, k1), wedge = m.rowidx[k] / m.npt_rad;
+            const int32_t z = run_end(k, k1), wedge = wedge_of(m.rowidx[k]);
             if (wedges.empty() || wedges.back() != wedge) {
                 if ((int32_t)wedges.size() == most_wedges) flush();
                 wedges.push_back(wedge);
             }
-            items.push_back(Item{((int32_t)wedges.size() - 1) * span + m.rowidx[k] % m.npt_rad - lo,
+            items.push_back(Item{((int32_t)wedges.size() - 1) * span + m.rowidx[k] - wrow - lo,
                                  z - k, 0, k});
             most = std::max(most, z - k);
             k = z;
@@ -473,6 +505,20 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
     }
     const size_t t0 = sm.tiles.size(), s0 = sm.segs.size();
     const int64_t px0 = sm.npix, parts0 = sm.nparts;
+    if (threads > 1) {  // once, not as the parts come
+        size_t nt = 0, nw = 0, ng = 0, nx = 0;
+        for (const Builder& b : part) {
+            nt += b.sm.tiles.size();
+            nw += b.sm.words.size();
+            ng += b.sm.gbase.size();
+            nx += b.sm.xsrc.size();
+        }
+        sm.tiles.reserve(t0 + nt);
+        sm.words.reserve(sm.words.size() + nw);
+        sm.gbase.reserve(sm.gbase.size() + ng);
+        sm.xsrc.reserve(sm.xsrc.size() + nx);
+        sm.xpix.reserve(sm.xpix.size() + nx);
+    }
     for (Builder& b : part) {
         if (!append(b.sm, sm)) return false;
         b.sm = StreamMatrix();
