@@ -430,9 +430,10 @@ bool append(const StreamMatrix& part, StreamMatrix& sm) {
     return true;
 }
 
-// Below this many pixels one thread builds an instance; above, up to
-// kBuildThreads share its bands of rows (3162 x 3163: 0.55 s alone).
-constexpr int64_t kThreadPix = (int64_t)1 << 18;
+// One thread for every so many pixels of an instance, up to kBuildThreads
+// (about 0.1 us a pixel, so 0.8 ms a thread where starting one takes 0.03; a
+// 330 x 330 map of 100 x 36 bins takes 10 ms alone).
+constexpr int64_t kThreadPix = (int64_t)1 << 13;
 constexpr int32_t kBuildThreads = 16;
 
 }  // namespace
@@ -453,37 +454,37 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
     rows = std::max(1, std::min(h, rows >= unit ? rows / unit * unit : rows));
     const int32_t bands = (h + rows - 1) / rows;
     const int64_t per_band = (w + strip - 1) / strip;
-    int32_t threads = 1;
-    if (m.npix >= kThreadPix)
-        threads = std::max(1, std::min({(int32_t)std::thread::hardware_concurrency(),
-                                        kBuildThreads, bands}));
+    const int64_t units = bands * per_band;
+    const int32_t threads = (int32_t)std::max<int64_t>(
+        1, std::min({(int64_t)std::thread::hardware_concurrency(), (int64_t)kBuildThreads, units,
+                     m.npix / kThreadPix}));
     std::vector<Builder> part;
     part.reserve(threads);
     for (int32_t k = 0; k < threads; ++k) part.emplace_back(m, w, pix_off, bin_off);
     std::vector<char> bad(threads, 0);
-    // the k-th thread's bands; a matrix that will be refused is given up early
+    // the k-th thread's tiles, along the bands; a matrix that will be refused
+    // is given up early
     auto build = [&](int32_t k) {
         Builder& b = part[k];
-        const int32_t a = (int32_t)((int64_t)bands * k / threads);
-        const int32_t z = (int32_t)((int64_t)bands * (k + 1) / threads);
+        const int64_t a = units * k / threads, z = units * (k + 1) / threads;
         try {
-            for (int32_t i = a; i < z && !bad[k]; ++i) {
-                const int32_t i0 = i * rows;
-                if (!m.two_d)
-                    for (int64_t p = (int64_t)i0 * w, e = p + (int64_t)std::min(rows, h - i0) * w;
-                         p < e; ++p) {
+            for (int64_t u = a; u < z && !bad[k]; ++u) {
+                const int32_t i0 = (int32_t)(u / per_band) * rows;
+                const int32_t j0 = (int32_t)(u % per_band) * strip;
+                const int32_t i1 = std::min(i0 + rows, h), j1 = std::min(j0 + strip, w);
+                for (int32_t i = i0; i < i1 && !m.two_d; ++i)
+                    for (int64_t p = (int64_t)i * w + j0, e = p + (j1 - j0); p < e; ++p) {
                         const int32_t k0 = m.colptr[p], k1 = m.colptr[p + 1];
                         if (k1 - k0 > kStreamMaxCount ||
                             (k1 > k0 && m.rowidx[k1 - 1] != m.rowidx[k0] + (k1 - k0 - 1)))
                             bad[k] = 1;
                     }
-                for (int32_t j0 = 0; j0 < w && !bad[k]; j0 += strip) {
-                    b.tile(i0, j0, std::min(rows, h - i0), std::min(strip, w - j0));
-                    const int64_t nt = (int64_t)b.sm.tiles.size();
-                    if (nt > 4 * per_band * (z - a) && nt * (kStreamMinPix / 4) > b.sm.npix)
-                        bad[k] = 1;
-                    if ((int64_t)b.sm.words.size() >= kLimit || b.sm.nparts >= kLimit) bad[k] = 1;
-                }
+                if (bad[k]) break;
+                b.tile(i0, j0, i1 - i0, j1 - j0);
+                const int64_t nt = (int64_t)b.sm.tiles.size();
+                if (nt > 4 * std::max(z - a, per_band) && nt * (kStreamMinPix / 4) > b.sm.npix)
+                    bad[k] = 1;
+                if ((int64_t)b.sm.words.size() >= kLimit || b.sm.nparts >= kLimit) bad[k] = 1;
             }
         } catch (const std::bad_alloc&) {
             bad[k] = 2;
