@@ -482,8 +482,9 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
                 if (bad[k]) break;
                 b.tile(i0, j0, i1 - i0, j1 - j0);
                 const int64_t nt = (int64_t)b.sm.tiles.size();
-                if (nt > 4 * std::max(z - a, per_band) && nt * (kStreamMinPix / 4) > b.sm.npix)
-                    bad[k] = 1;
+                // what the whole matrix will be refused for, wherever its
+                // tiles are: the answer does not depend on the threads
+                if (nt > 4 * units && nt * kStreamMinPix > m.npix) bad[k] = 1;
                 if ((int64_t)b.sm.words.size() >= kLimit || b.sm.nparts >= kLimit) bad[k] = 1;
             }
         } catch (const std::bad_alloc&) {
