@@ -42,9 +42,25 @@ KERNEL_OF_LAYOUT = {
 }
 
 
+def streamed(layout, tiling):
+    """Whether a one-dimensional frame of this size goes through the stream
+    encoding (the run layout with the library's own tiling)."""
+    return layout == "run" and tiling["tile_nnz"] == 0 and tiling["band"] == 16 and \
+        tiling["grid"] == 0
+
+
 def kernel_of(line):
     """The step's dominant kernel, from the plan's layout and tiling."""
     t = line["tiling"]
+    if streamed(line["layout"], t):
+        k = ("k_stream (+k_stream_reduce): image tiles read once, a word per pixel, sums of the "
+             "tile's bins in LDS")
+        if t["stage"] == 5 and line.get("accum") == "f64":
+            return k + "; 1/norm folded into the coefficients, the dark term summed once per " \
+                       "correction set"
+        if t["stage"] in (4, 5):
+            return k + "; 1/norm folded into the coefficients, dark read per pixel"
+        return k + "; dark and 1/norm read per pixel"
     if line["layout"] == "run" and t["band"] in (16, 32):
         k = (f"k_runs_grouped (+k_band_reduce): run-encoded gather integration, "
              f"{t['band'] // 4} neighbouring bands of 4 bins per workgroup")
@@ -66,7 +82,8 @@ def log(*a):
 
 # the integration kernels and the schedule builder (the pieces a launch
 # walks decide which lines are fetched twice)
-TRAFFIC_SOURCES = ("kernels.hip", "accum.h", "plan_builder.cpp")
+TRAFFIC_SOURCES = ("stream_forward.h", "stream_lane.h", "stream_builder.cpp", "correct.h",
+                   "accum.h", "plan_builder.cpp")
 
 
 def kernel_source_hash():
@@ -160,6 +177,21 @@ def encoding_bytes(plan, np, npix, npt, es, cb):
     return runs * 4 + plan.nnz * es + npix * (4 + cb) + 3 * npt * es
 
 
+def stream_bytes(nnz, npix, npt, es, cb):
+    """Bytes of one raw-frame step over the stream encoding: a 16-bit word, the
+    int32 count and cb correction bytes per pixel, the coefficients, three
+    outputs.  Below the CSR figure of raw_bytes, so a step's share of the HBM
+    peak is taken from these."""
+    return nnz * es + npix * (2 + 4 + cb) + 3 * npt * es
+
+
+def step_bytes(plan, nnz, npix, npt, es, cb):
+    """Bytes a raw-frame step is credited with, for the plan's encoding."""
+    if streamed(plan.layout(), plan.tiling()):
+        return stream_bytes(nnz, npix, npt, es, cb)
+    return raw_bytes(nnz, npix, npt, es, cb)
+
+
 def pipeline_line(az, torch, np, synth, dev, dtype, steps, warmup, frames_n=4, accum="f64",
                   stage=None):
     """Step = one raw int32 frame -> I, W, U with the plan's corrections
@@ -203,7 +235,7 @@ def pipeline_line(az, torch, np, synth, dev, dtype, steps, warmup, frames_n=4, a
     es = 8 if dtype == "f64" else 4
     nnz = plan.nnz
     cb = plan.correction_bytes()
-    rb = raw_bytes(nnz, g.npix, inst.npt, es, cb)
+    rb = step_bytes(plan, nnz, g.npix, inst.npt, es, cb)
     enc = encoding_bytes(plan, np, g.npix, inst.npt, es, cb)
     # two-pass breakdown: correction kernel, then integration of the image
     # (its kernels' first launches untimed)
@@ -241,7 +273,8 @@ def pipeline_line(az, torch, np, synth, dev, dtype, steps, warmup, frames_n=4, a
                 tiling=plan.tiling(), ms_per_step=ms_step,
                 elements_per_s=g.npix / (ms_step * 1e-3),
                 correction_bytes_per_pixel=cb,
-                step_ms=step_ms, step_bytes=rb, step_gbs=rb / (step_ms * 1e6),
+                step_ms=step_ms, step_csr_bytes=raw_bytes(nnz, g.npix, inst.npt, es, cb),
+                step_bytes=rb, step_gbs=rb / (step_ms * 1e6),
                 step_encoding_bytes=enc, step_encoding_gbs=enc / (step_ms * 1e6),
                 step_frac=rb / (step_ms * 1e6) / HBM_PEAK_GBS,
                 graph_step_ms=graph_ms, graph_elements_per_s=g.npix / (graph_ms * 1e-3),
@@ -291,7 +324,7 @@ def cold_line(torch, plan, outs, frame, npix, npt, nnz, es, flush):
     """The step (raw frame, corrections in the gather) with the caches
     flushed before every launch."""
     ms, meds = flushed_ms(torch, lambda: plan.integrate_raw(frame, out=outs), flush)
-    by = raw_bytes(nnz, npix, npt, es, plan.correction_bytes())
+    by = step_bytes(plan, nnz, npix, npt, es, plan.correction_bytes())
     return dict(step_ms=ms, set_medians_ms=meds, step_bytes=by, step_gbs=by / (ms * 1e6),
                 step_frac=by / (ms * 1e6) / HBM_PEAK_GBS,
                 protocol="1 GiB read before each launch; median of 10, best of 3 sets")
@@ -578,7 +611,7 @@ def full_split_line(az, torch, np, synth, dev, reps=50):
     outs = tuple(torch.empty(inst.npt, dtype=torch.float64, device=dev) for _ in range(3))
     ms = _timed(torch, lambda: plan.integrate_raw(raw, out=outs), reps)
     nnz = plan.nnz
-    by = raw_bytes(nnz, g.npix, inst.npt, 8, plan.correction_bytes())
+    by = step_bytes(plan, nnz, g.npix, inst.npt, 8, plan.correction_bytes())
     line = dict(npix=g.npix, npt=inst.npt, nnz=nnz, layout=plan.layout(),
                 host_build_upload_s=host_s, device_build_s=dev_s, step_ms=ms,
                 step_bytes=by, step_gbs=by / (ms * 1e6), step_frac=by / (ms * 1e6) / HBM_PEAK_GBS,

@@ -1,7 +1,10 @@
 // HIP kernels for gfx950 (CDNA4): the per-frame hot path of azimuthal
 // integration.
 //
-//   k_band_runs  the default integration (run layout): bands of 4 bins
+//   (The default integration is k_stream, stream_forward.h; these serve the
+//   matrices that its encoding refuses and the tilings that ask for them.)
+//
+//   k_band_runs  the integration over the run layout: bands of 4 bins
 //              whose entries are ordered by pixel, stored as one word per
 //              run of a pixel's entries in the band, so a wavefront gathers
 //              nearly consecutive pixels of the row-major image once per run;
