@@ -298,7 +298,7 @@ struct StreamBufs {
     void* coef = nullptr;     // storage type
     int32_t ntiles = 0, nblanks = 0, nchunks = 0, slots = 4, ents_most = 0;
     int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
-    bool over = true, on = false;
+    bool over = true, cached = false, on = false;
     void release() {
         built.release();
         work.release();
@@ -352,6 +352,7 @@ azi::StreamLaunch stream_args(const StreamBufs& b, const void* img, int32_t img_
     a.ents_most = b.ents_most;
     a.slots = b.slots;
     a.over = b.over;
+    a.cached = b.cached;
     a.img = img;
     a.img_dtype = img_dtype;
     a.parts = b.parts;
@@ -379,6 +380,23 @@ azi::StreamCoefLaunch stream_coef_args(const StreamBufs& b, const DevBuf& colptr
     c.coef = coef;
     c.dtype = dtype;
     return c;
+}
+
+// Whether words and coefficients are read through the caches instead of past
+// them.  What fits the 256 MB memory-side cache beside the images is there for
+// the next pass (or the adjoint after the forward): us a pass, streamed and
+// cached, forward / adjoint of n x n pixels and n bins, one plan:
+//   float32  2048 (46 MB) 20.1 / 16.4 and 19.5 / 15.8
+//            3162 (133 MB) 39.5 / 37.5 and 36.6 / 33.6
+//            4500 (270 MB) 71.0 / 69.9 and 73.0 / 66.2
+//   float64  1500 (56 MB) 18.0 / 16.1 and 17.4 / 14.5
+//            4500 (500 MB) 99.4 / 126 and 110 / 144
+// and with three plans in turn: float32 46 MB 18.3 and 16.7, 86 MB 29.9 and
+// 30.0; float64 82 MB 29.0 and 29.4, 246 MB 53.0 and 57.6.  Doubles gain less,
+// their loads being whole lines more often, and lose sooner.
+bool stream_cached(const azi::StreamMatrix& sm, int32_t dtype) {
+    const int64_t bytes = (int64_t)sm.words.size() * 2 + sm.ncoef * (int64_t)elem_size(dtype);
+    return bytes <= ((int64_t)(dtype == AZI_F64 ? 64 : 160) << 20);
 }
 
 // Places a stream encoding on the device; its coefficients are gathered from
@@ -443,6 +461,7 @@ int upload_stream(const azi::StreamMatrix& sm, bool two_d, int64_t npt, int32_t 
     b.slots = 2;
     while (b.slots < 4 && sm.over[b.slots] * 1024 > sm.over[0]) ++b.slots;
     b.over = sm.over[b.slots] > 0;
+    b.cached = stream_cached(sm, dtype);
     b.ncoef = sm.ncoef;
     b.nparts = sm.nparts;
     b.ents_most = 0;
@@ -473,6 +492,7 @@ azi::StreamAdjointLaunch stream_adjoint_args(const StreamBufs& b, const void* U,
     a.coef = b.coef;
     a.slots = b.slots;
     a.over = b.over;
+    a.cached = b.cached;
     a.U = U;
     a.gI = gI;
     a.gW = gW;

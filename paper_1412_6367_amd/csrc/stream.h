@@ -28,6 +28,7 @@ struct StreamLaunch {
     int32_t ents_most = 0;             // at most: these select the reduction's shape
     int32_t slots = 4;                 // coefficients a pixel keeps in registers: 2, 3 or 4
     bool over = true;                  // some pixel has more
+    bool cached = false;               // words and coefficients through the caches (stream_cached)
     const void* img = nullptr;         // raw or corrected image (flat, img_dtype)
     int32_t img_dtype = AZI_F64;
     int64_t npix = 0;                  // pixels of img, four at least
@@ -82,7 +83,7 @@ struct StreamAdjointLaunch {
     const int32_t* gbase = nullptr;
     const void* coef = nullptr;
     int32_t slots = 4;                 // as in StreamLaunch
-    bool over = true;
+    bool over = true, cached = false;
     const void* U = nullptr;           // storage type
     const void* gI = nullptr;          // may be null
     const void* gW = nullptr;          // may be null

@@ -103,7 +103,7 @@ hipError_t coef_launch(const StreamCoefLaunch& a, hipStream_t s) {
 // bytes of column pointer and first bin a pixel in the words' place.  Forward
 // and gradient of 64 float32 images of 1e3 to 1e6 pixels: 98.3 us with
 // k_csc_bwd behind the stream forward, 82.9 with this.
-template <class T, int NMAX, bool kOver>
+template <class T, int NMAX, bool kOver, bool kNt>
 __global__ __launch_bounds__(256) void k_stream_adjoint(
     const StreamTile* __restrict__ tiles, int32_t ntiles, const StreamTile* __restrict__ blanks,
     const uint16_t* __restrict__ words, const int32_t* __restrict__ gbase,
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
     const int32_t bases = gbase[t.g0 + min(g0 + lane, ng - 1)];
     auto fetch = [&](int g) {
         const int e = t.word0 + min(g, ng - 1) * kBlockPix + kLanePix * lane;
-        return ld<true>(reinterpret_cast<const uint64_t*>(words + e));
+        return ld<kNt>(reinterpret_cast<const uint64_t*>(words + e));
     };
     uint64_t word = fetch(g0);
     __syncthreads();
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
 #pragma unroll
         for (int k = 0; k < kLanePix; ++k) {
             const int n = (int)(bits(k) >> kStreamCountShift);
-            more[k] = base = stream_coefs<NMAX>(base, n, coef, c[k]);
+            more[k] = base = stream_coefs<kNt, NMAX>(base, n, coef, c[k]);
             if (over) base = stream_skip(base, n, NMAX);
         }
         word = fetch(g + 1);
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
             if (over) {
                 for (int j = NMAX; __ballot(n > j) != 0; ++j) {
                     T cj[1];
-                    more[k] = stream_coefs<1>(more[k], n > j ? 1 : 0, coef, cj);
+                    more[k] = stream_coefs<kNt, 1>(more[k], n > j ? 1 : 0, coef, cj);
                     if (n > j) acc = __fma_rn((double)cj[0], vb[j], acc);
                 }
             }
@@ -192,9 +192,9 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
     }
 }
 
-template <class T, int NMAX, bool kOver>
+template <class T, int NMAX, bool kOver, bool kNt>
 hipError_t adjoint_launch(const StreamAdjointLaunch& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_stream_adjoint<T, NMAX, kOver>), dim3((unsigned)(a.ntiles + a.nblanks)),
+    hipLaunchKernelGGL((k_stream_adjoint<T, NMAX, kOver, kNt>), dim3((unsigned)(a.ntiles + a.nblanks)),
                        dim3(256), 0, s, a.tiles, a.ntiles, a.blanks, a.words, a.gbase,
                        static_cast<const T*>(a.coef), static_cast<const T*>(a.U),
                        static_cast<const T*>(a.gI), static_cast<const T*>(a.gW),
@@ -202,13 +202,20 @@ hipError_t adjoint_launch(const StreamAdjointLaunch& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <class T>
+template <class T, bool kNt>
 hipError_t adjoint_slots(const StreamAdjointLaunch& a, hipStream_t s) {
     if (a.slots == 2)
-        return a.over ? adjoint_launch<T, 2, true>(a, s) : adjoint_launch<T, 2, false>(a, s);
+        return a.over ? adjoint_launch<T, 2, true, kNt>(a, s)
+                      : adjoint_launch<T, 2, false, kNt>(a, s);
     if (a.slots == 3)
-        return a.over ? adjoint_launch<T, 3, true>(a, s) : adjoint_launch<T, 3, false>(a, s);
-    return adjoint_launch<T, kStreamUnrolled, true>(a, s);
+        return a.over ? adjoint_launch<T, 3, true, kNt>(a, s)
+                      : adjoint_launch<T, 3, false, kNt>(a, s);
+    return adjoint_launch<T, kStreamUnrolled, true, kNt>(a, s);
+}
+
+template <class T>
+hipError_t adjoint_cached(const StreamAdjointLaunch& a, hipStream_t s) {
+    return a.cached ? adjoint_slots<T, false>(a, s) : adjoint_slots<T, true>(a, s);
 }
 
 template <class T>
@@ -255,7 +262,7 @@ hipError_t launch_stream_coef(const StreamCoefLaunch& a, hipStream_t s) {
 
 hipError_t launch_stream_adjoint(const StreamAdjointLaunch& a, hipStream_t s) {
     if (a.ntiles + a.nblanks <= 0) return hipSuccess;
-    return a.dtype == AZI_F64 ? adjoint_slots<double>(a, s) : adjoint_slots<float>(a, s);
+    return a.dtype == AZI_F64 ? adjoint_cached<double>(a, s) : adjoint_cached<float>(a, s);
 }
 
 hipError_t launch_dark_kind(const void* dark, int32_t dtype, int64_t n, int32_t* flags,

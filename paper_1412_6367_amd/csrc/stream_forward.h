@@ -40,7 +40,7 @@ struct UnitImage {}; // every pixel 1
 // its own: finishing the bins in the last workgroup to arrive needs a release
 // at device scope per workgroup, an L2 write-back each, and takes 12.4 -> 136
 // us for 981 x 1043 pixels.
-template <class T, class Acc, class RawT, class CorrT, int NMAX, bool kOver, bool kX>
+template <class T, class Acc, class RawT, class CorrT, int NMAX, bool kOver, bool kX, bool kNt>
 __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ tiles,
                                                 const uint16_t* __restrict__ words,
                                                 const int32_t* __restrict__ gbase,
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
     auto fetch = [&](int g) {
         // past the wavefront's last block: the last one's words again, unused
         const int e = t.word0 + min(g, g1 - 1) * kBlockPix + kLanePix * lane;
-        word = ld<true>(reinterpret_cast<const uint64_t*>(words + e));
+        word = ld<kNt>(reinterpret_cast<const uint64_t*>(words + e));
         if constexpr (!kUnit) {
             const int64_t p = at.pixel(t);
             const int64_t q = p < end ? p : end;
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
 #pragma unroll
         for (int k = 0; k < kLanePix; ++k) {
             const int n = (int)(bits(k) >> kStreamCountShift);
-            more[k] = base = stream_coefs<NMAX>(base, n, coef, c[k]);
+            more[k] = base = stream_coefs<kNt, NMAX>(base, n, coef, c[k]);
             if (over) base = stream_skip(base, n, NMAX);
         }
         T x[kLanePix];
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
                 // pixels of more bins than are held
                 for (int j = NMAX; __ballot(n > j) != 0; ++j) {
                     T cj[1];
-                    more[k] = stream_coefs<1>(more[k], n > j ? 1 : 0, coef, cj);
+                    more[k] = stream_coefs<kNt, 1>(more[k], n > j ? 1 : 0, coef, cj);
                     if (n > j) {
                         Acc v = p[j];
                         v.add(cj[0], x[k]);
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
             }
             const int n = xword >> kStreamCountShift;
             T c[NMAX];
-            int32_t more = stream_coefs<NMAX>(gbase[t.g0 + ng + u], n, coef, c);
+            int32_t more = stream_coefs<kNt, NMAX>(gbase[t.g0 + ng + u], n, coef, c);
             T x;
             if constexpr (kUnit) x = T(1);
             else if constexpr (kCorr) x = corr_apply((T)xraw, xcor);
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void k_stream(const StreamTile* __restrict__ t
             if (over) {
                 for (int j = NMAX; __ballot(n > j) != 0; ++j) {
                     T cj[1];
-                    more = stream_coefs<1>(more, n > j ? 1 : 0, coef, cj);
+                    more = stream_coefs<kNt, 1>(more, n > j ? 1 : 0, coef, cj);
                     if (n > j) {
                         Acc v = p[j];
                         v.add(cj[0], x);
@@ -307,13 +307,24 @@ __global__ __launch_bounds__(256) void k_stream_reduce_each(
     write_row_u(b, a, I, W, U, empty, f, static_cast<double*>(nullptr), wfix_out);
 }
 
-template <class T, class Acc, class RawT, class CorrT, int NMAX, bool kOver, bool kX>
+template <class T, class Acc, class RawT, class CorrT, int NMAX, bool kOver, bool kX, bool kNt>
 hipError_t stream_launch(const StreamLaunch& a, hipStream_t s) {
-    hipLaunchKernelGGL((k_stream<T, Acc, RawT, CorrT, NMAX, kOver, kX>), dim3((unsigned)a.ntiles),
+    hipLaunchKernelGGL((k_stream<T, Acc, RawT, CorrT, NMAX, kOver, kX, kNt>), dim3((unsigned)a.ntiles),
                        dim3(256), 0, s, a.tiles, a.words, a.gbase, static_cast<const T*>(a.coef),
                        static_cast<const RawT*>(a.img), a.npix, static_cast<const CorrT*>(a.corr),
                        a.xpix, static_cast<Acc*>(a.parts));
     return hipGetLastError();
+}
+
+template <class T, class Acc, class RawT, class CorrT, bool kNt>
+hipError_t stream_slots_1d(const StreamLaunch& a, hipStream_t s) {
+    if (a.slots == 2 && !a.over)
+        return stream_launch<T, Acc, RawT, CorrT, 2, false, false, kNt>(a, s);
+    if (a.slots == 2) return stream_launch<T, Acc, RawT, CorrT, 2, true, false, kNt>(a, s);
+    if (a.slots == 3 && !a.over)
+        return stream_launch<T, Acc, RawT, CorrT, 3, false, false, kNt>(a, s);
+    if (a.slots == 3) return stream_launch<T, Acc, RawT, CorrT, 3, true, false, kNt>(a, s);
+    return stream_launch<T, Acc, RawT, CorrT, kStreamUnrolled, true, false, kNt>(a, s);
 }
 
 template <class T, class Acc, class RawT, class CorrT>
@@ -321,14 +332,13 @@ hipError_t stream_slots(const StreamLaunch& a, hipStream_t s) {
     if constexpr (!std::is_same<CorrT, typename Pair2<T>::type>::value &&
                   !std::is_same<CorrT, Corr12>::value) {
         // two-dimensional matrices
-        if (a.xpix && a.slots == 2) return stream_launch<T, Acc, RawT, CorrT, 2, true, true>(a, s);
-        if (a.xpix) return stream_launch<T, Acc, RawT, CorrT, 3, true, true>(a, s);
+        if (a.xpix && a.slots == 2)
+            return stream_launch<T, Acc, RawT, CorrT, 2, true, true, true>(a, s);
+        if (a.xpix) return stream_launch<T, Acc, RawT, CorrT, 3, true, true, true>(a, s);
+        if constexpr (!std::is_same<CorrT, UnitImage>::value)
+            if (a.cached) return stream_slots_1d<T, Acc, RawT, CorrT, false>(a, s);
     }
-    if (a.slots == 2 && !a.over) return stream_launch<T, Acc, RawT, CorrT, 2, false, false>(a, s);
-    if (a.slots == 2) return stream_launch<T, Acc, RawT, CorrT, 2, true, false>(a, s);
-    if (a.slots == 3 && !a.over) return stream_launch<T, Acc, RawT, CorrT, 3, false, false>(a, s);
-    if (a.slots == 3) return stream_launch<T, Acc, RawT, CorrT, 3, true, false>(a, s);
-    return stream_launch<T, Acc, RawT, CorrT, kStreamUnrolled, true, false>(a, s);
+    return stream_slots_1d<T, Acc, RawT, CorrT, true>(a, s);
 }
 
 template <class T, class Acc, class RawT>

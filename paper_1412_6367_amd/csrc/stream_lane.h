@@ -125,7 +125,8 @@ __device__ inline int64_t stream_tile_of(uint32_t g, uint32_t n) {
 // none has more than N bins.  Lanes without a j-th coefficient read their
 // neighbour's, unused: no branch, no address outside the array and its spare
 // elements.
-template <int N, class T>
+// kNt: streamed past the caches (stream_cached has the rule).
+template <bool kNt, int N, class T>
 __device__ __forceinline__ int32_t stream_coefs(int32_t base, int n, const T* __restrict__ coef,
                                                 T (&c)[N]) {
 #pragma unroll
@@ -133,7 +134,7 @@ __device__ __forceinline__ int32_t stream_coefs(int32_t base, int n, const T* __
         const uint64_t m = __ballot(n > j);
         const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
             (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        c[j] = ld<true>(coef + base + rank);
+        c[j] = ld<kNt>(coef + base + rank);
         base += (int32_t)__popcll(m);
     }
     return base;

@@ -193,3 +193,29 @@ def test_stream_graph_replays(dim, dev):
         _ = (raw * 2).sum().item()
     with pytest.raises(az.AzintError):
         plan.graph(raw, None)
+
+
+@pytest.mark.parametrize("n,dtype", [(1650, torch.float64), (1750, torch.float64),
+                                     (2300, torch.float64), (3000, torch.float32),
+                                     (3600, torch.float32)], ids=str)
+def test_stream_sizes_around_the_cache_rule(n, dtype, dev):
+    """Matrices read through the caches and past them (64 MiB in float64, 160
+    in float32): the sums of the run encoding to rounding, the adjoint of the
+    entries bit for bit."""
+    az = azint()
+    plan = az.Plan.on_device(n, n, n, device=dev, dtype=dtype)
+    gen = torch.Generator().manual_seed(n)
+    x = torch.rand(n * n, generator=gen, dtype=torch.float64).to(dtype).to(dev)
+    g = torch.randn(n, generator=gen, dtype=torch.float64).to(dtype).to(dev)
+    band = plan.integrate(x)
+    gx0 = plan.backward(band[2], g)
+    plan.set_layout("run")
+    plan.set_tiling(tile_nnz=0, band=16, grid=0)
+    out = plan.integrate(x)
+    gx = plan.backward(band[2], g)
+    # float64 sums of positive terms: a bin of n terms is off by n/2^53 at most
+    # either way; float32 outputs are rounded once more
+    tol = 2 * 4 * n * 2.0 ** -53 + (0.0 if dtype == torch.float64 else 2.0 ** -22)
+    for a, b in zip(out, band):
+        assert ((a - b).abs() <= tol * b.abs()).all()
+    assert torch.equal(gx, gx0)
