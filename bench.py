@@ -236,7 +236,8 @@ def pipeline_line(az, torch, np, synth, dev, dtype, steps, warmup, frames_n=4, a
     nnz = plan.nnz
     cb = plan.correction_bytes()
     rb = step_bytes(plan, nnz, g.npix, inst.npt, es, cb)
-    enc = encoding_bytes(plan, np, g.npix, inst.npt, es, cb)
+    enc = rb if streamed(plan.layout(), plan.tiling()) \
+        else encoding_bytes(plan, np, g.npix, inst.npt, es, cb)
     # two-pass breakdown: correction kernel, then integration of the image
     # (its kernels' first launches untimed)
     plan.stage(frames[0])
