@@ -291,8 +291,8 @@ struct StreamMatrix {
 // encoding does not apply: under four pixels, a pixel of a one-dimensional
 // matrix with non-consecutive bins or more than kStreamMaxCount, bins so fine
 // that the tiles had to be halved again and again (over four times as many as
-// their size asks for, under kStreamMinPix pixels on average), positions past
-// int32.
+// their size asks for, under kStreamMinPix pixels on average), images of 2^27
+// pixels or more (as in the band and run layouts), positions past int32.
 //
 // Two-dimensional matrices (pix_off and bin_off 0): a tile's window is the
 // radial bins it reaches, wedge after wedge; a pixel's entries are runs of
@@ -304,6 +304,11 @@ struct StreamMatrix {
 // over them.  A pixel of more runs than a window holds (the beam's) has
 // several tiles of its own, all of its runs scattered.  Refused too: more
 // than one partial sum per four entries.
+// Farthest position, from a tile's first pixel, that a lane of its kernels
+// forms in 32 bits: rows are padded to blocks of up to 64, the words and
+// pixels of one block past the last are asked for too (their addresses are
+// brought back into the image afterwards), and columns to under 128.
+inline int64_t stream_reach(int32_t th, int32_t w) { return (int64_t)(th + 127) * w + 128; }
 constexpr int32_t kStreamMinPix = 192;
 constexpr int32_t kStreamColBits = 6;  // columns of a tile: 64
 bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, int64_t pix_off,

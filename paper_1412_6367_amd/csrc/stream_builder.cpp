@@ -452,6 +452,7 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
     rows = std::min(rows, 1 << (16 - kStreamColBits));
     const int32_t unit = m.two_d && rows >= 64 ? 64 : 16;
     rows = std::max(1, std::min(h, rows >= unit ? rows / unit * unit : rows));
+    if (m.npix >= (int64_t)1 << kBandShift || stream_reach(rows, w) > kLimit) return false;
     const int32_t bands = (h + rows - 1) / rows;
     const int64_t per_band = (w + strip - 1) / strip;
     const int64_t units = bands * per_band;
