@@ -452,6 +452,9 @@ int64_t azi_plan_device_bytes(const azi_plan* plan);
  * the results are the same bits, the gather reads 4 bytes less per pixel.
  * Passing all NULL removes the corrections.  Runs on `stream` and
  * synchronises it.  Needs an uploaded plan.
+ * If the forms that the one-pass kernels read cannot be placed (an error),
+ * raw frames are corrected in a pass of their own, and the allocation-free
+ * call gives AZI_ESTATE, until a later call places them.
  */
 int azi_plan_set_corrections(azi_plan* plan, const void* dark, const void* flat,
                              const void* solid, const void* polar, void* stream);

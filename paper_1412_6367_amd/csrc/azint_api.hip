@@ -845,11 +845,18 @@ azi::StreamLaunch plan_stream_raw_args(const azi_plan* p, const void* raw, int32
     return a;
 }
 
+// Whether the forms that the gather corrects with are in place: not after a
+// call that set dark or norm and then failed to form them (memory).
+bool plan_corr_formed(const azi_plan* p) {
+    return !(p->has_dark || p->has_norm) || p->folded || p->corr.p;
+}
+
 // Whether a raw frame is cast and corrected in the gather of the band, run
 // or stream encoding.
 bool plan_raw_in_gather(const azi_plan* p) {
-    return (is_band(p->layout) && gather_corrects(p->tiling.stage)) ||
-           (p->layout == AZI_LAYOUT_PIXEL && p->stream.on);
+    return ((is_band(p->layout) && gather_corrects(p->tiling.stage)) ||
+            (p->layout == AZI_LAYOUT_PIXEL && p->stream.on)) &&
+           plan_corr_formed(p);
 }
 
 // A raw frame (see plan_band_raw_args); `parts` replaces the plan's own
@@ -1119,6 +1126,7 @@ int plan_corr_pair(azi_plan* p, hipStream_t s) {
         if (rc != AZI_OK) {
             p->corr.release();
             p->fcoef.release();
+            p->wdark.release();
             p->corr_kind = azi::kCorrPair;
         }
         return rc;
@@ -2130,6 +2138,8 @@ int azi_integrate1d_raw_noalloc(const azi_plan* p, const void* raw, int32_t raw_
     if (!valid_raw_dtype(raw_dtype)) return fail(AZI_EINVAL, "unknown raw dtype");
     // the layouts whose raw-frame path needs partial sums and nothing else
     size_t need = 0;
+    if (is_band(p->layout) && gather_corrects(p->tiling.stage) && !plan_corr_formed(p))
+        return fail(AZI_ESTATE, "the plan's corrections were not formed: set them again");
     if (is_band(p->layout) && gather_corrects(p->tiling.stage))
         need = p->stream.on ? (size_t)p->stream.nparts * 8 : p->nparts_buf.bytes;
     else if (p->layout == AZI_LAYOUT_TILE) need = p->bparts.bytes;
