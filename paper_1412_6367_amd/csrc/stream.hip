@@ -97,8 +97,9 @@ hipError_t coef_launch(const StreamCoefLaunch& a, hipStream_t s) {
 // formed once into LDS (one pass less than a vector formed beforehand, and
 // the pixels' bins then come from LDS instead of the caches), the words and
 // coefficients read as in the forward, every lane writing its four pixels'
-// gradients together.  Workgroups past the tiles clear the pixels that feed
-// no bin.  The products are added in ascending bins, as by k_csc_bwd: the
+// gradients together.  Workgroups past the tiles write the empty sums of the
+// tiles whose pixels feed no bin (over the norm, as every pixel's: a masked
+// pixel's norm of 0 gives NaN wherever it lies).  The products are added in ascending bins, as by k_csc_bwd: the
 // same bits.  Bound by HBM: coefficients, words and gradient; k_csc_bwd read 8
 // bytes of column pointer and first bin a pixel in the words' place.  Forward
 // and gradient of 64 float32 images of 1e3 to 1e6 pixels: 98.3 us with
@@ -114,7 +115,8 @@ __global__ __launch_bounds__(256) void k_stream_adjoint(
         const StreamTile t = blanks[blockIdx.x - ntiles];
         for (int e = threadIdx.x; e < t.tw * t.th; e += 256) {
             const int r = e / t.tw;
-            gx[t.pix0 + r * t.w + e - r * t.tw] = T(0);
+            const int64_t p = t.pix0 + r * t.w + e - r * t.tw;
+            gx[p] = norm ? (T)(0.0 / (double)norm[p]) : T(0);
         }
         return;
     }
