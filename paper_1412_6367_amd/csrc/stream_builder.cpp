@@ -6,7 +6,6 @@
 #include <iterator>
 #include <limits>
 #include <new>
-#include <system_error>
 #include <thread>
 
 #include "internal.h"
@@ -488,15 +487,17 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
                 if (nt > 4 * units && nt * kStreamMinPix > m.npix) bad[k] = 1;
                 if ((int64_t)b.sm.words.size() >= kLimit || b.sm.nparts >= kLimit) bad[k] = 1;
             }
-        } catch (const std::bad_alloc&) {
+        } catch (...) {  // memory
             bad[k] = 2;
         }
     };
+    // room first: nothing may throw past threads that run
     std::vector<std::thread> run;
+    run.reserve(threads);
     for (int32_t k = 1; k < threads; ++k) {
         try {
             run.emplace_back(build, k);
-        } catch (const std::system_error&) {  // no thread to be had: this one does it
+        } catch (...) {  // no thread to be had: this one does it
             build(k);
         }
     }
