@@ -40,6 +40,16 @@ int hip_fail(hipError_t e, const char* what) {
         if (e_ != hipSuccess) return hip_fail(e_, what); \
     } while (0)
 
+// f(), with AZI_ENOMEM in the place of an exception: none leaves a C entry.
+template <class F>
+int no_throw(F&& f) {
+    try {
+        return f();
+    } catch (const std::exception&) {
+        return fail(AZI_ENOMEM, "out of host memory");
+    }
+}
+
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // Device allocation owned by a plan or batch, or (view) a part of one.
@@ -51,6 +61,12 @@ struct DevBuf {
     DevBuf() = default;
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
+    DevBuf(DevBuf&& o) noexcept { swap(o); }
+    DevBuf& operator=(DevBuf&& o) noexcept {
+        release();
+        swap(o);
+        return *this;
+    }
     ~DevBuf() { release(); }
     void release() {
         if (p && !view) {
@@ -80,6 +96,12 @@ struct DevBuf {
         hipError_t e = alloc(n, dev);
         if (e != hipSuccess || n == 0) return e;
         return hipMemcpy(p, src, n, hipMemcpyHostToDevice);
+    }
+    void swap(DevBuf& o) {
+        std::swap(p, o.p);
+        std::swap(bytes, o.bytes);
+        std::swap(device, o.device);
+        std::swap(view, o.view);
     }
     template <class T>
     T* as() const { return static_cast<T*>(p); }
@@ -694,12 +716,11 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
 }
 
 // The stream encoding of a plan whose tiling asks for it; *done is false
-// where it does not apply (bins too fine, partial
-// sums beyond the allocation-free call's array): the layout's own form then
-// serves.
+// where it does not apply (bins too fine, partial sums beyond the
+// allocation-free call's array): the layout's own form then serves.  The
+// encoding in use, this one or the layout's, goes once the new one is placed.
 int plan_upload_stream(azi_plan* p, bool* done) {
     *done = false;
-    p->stream.release();
     if (!stream_tiling(p->tiling, p->layout, p->m.two_d)) return AZI_OK;
     try {
         azi::StreamMatrix sm;
@@ -707,14 +728,16 @@ int plan_upload_stream(azi_plan* p, bool* done) {
                                0, 0, sm) ||
             (!p->m.two_d && (size_t)sm.nparts * 8 > kScratchBytes))
             return AZI_OK;
+        StreamBufs b;
         const int rc = upload_stream(sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
-                                     p->colptr, p->cdata, p->stream);
+                                     p->colptr, p->cdata, b);
         if (rc != AZI_OK) return rc;
+        p->stream = std::move(b);
     } catch (const std::bad_alloc&) {
         return fail(AZI_ENOMEM, "out of host memory building the stream encoding");
     }
     for (DevBuf* b : {&p->npieces_buf, &p->npacked, &p->ncoef, &p->bin_slot, &p->bin_count,
-                      &p->nparts_buf})
+                      &p->nparts_buf, &p->rgbase})
         b->release();
     p->npieces = 0;
     *done = true;
@@ -722,7 +745,6 @@ int plan_upload_stream(azi_plan* p, bool* done) {
 }
 
 int plan_upload_bands(azi_plan* p) {
-    p->rgbase.release();
     bool streamed = false;
     const int rcs = plan_upload_stream(p, &streamed);
     if (rcs != AZI_OK || streamed) return rcs;
@@ -744,6 +766,7 @@ int plan_upload_bands(azi_plan* p) {
             bm.bin_count.swap(rm.bin_count);
             bm.nslots = rm.nslots;
             p->band_rows = azi::kRunRows;
+            p->rgbase.release();
             int rc = upload_bands(bm, p->dtype, p->device, p->npieces_buf, p->npacked, p->ncoef,
                                   p->bin_slot, p->bin_count, p->nparts_buf, p->max_count);
             if (rc != AZI_OK) return rc;
@@ -753,13 +776,16 @@ int plan_upload_bands(azi_plan* p) {
         } catch (const std::bad_alloc&) {
             return fail(AZI_ENOMEM, "out of host memory building the run matrix");
         }
+        p->stream.release();
         return AZI_OK;
     }
     try {
         azi::BandMatrix bm;
-        p->band_rows = band_rows_of(p->tiling);
-        if (!azi::build_bands(p->m, p->band_rows, piece_nnz(p->tiling, p->m.nnz()), 0, 0, bm))
+        if (!azi::build_bands(p->m, band_rows_of(p->tiling), piece_nnz(p->tiling, p->m.nnz()), 0, 0,
+                              bm))
             return fail(AZI_EOVERFLOW, "the band layout takes images below 2^27 pixels");
+        p->band_rows = band_rows_of(p->tiling);
+        p->rgbase.release();
         int rc = upload_bands(bm, p->dtype, p->device, p->npieces_buf, p->npacked, p->ncoef,
                               p->bin_slot, p->bin_count, p->nparts_buf, p->max_count);
         if (rc != AZI_OK) return rc;
@@ -767,6 +793,7 @@ int plan_upload_bands(azi_plan* p) {
     } catch (const std::bad_alloc&) {
         return fail(AZI_ENOMEM, "out of host memory building the band matrix");
     }
+    p->stream.release();
     return AZI_OK;
 }
 
@@ -1112,23 +1139,23 @@ int plan_fold(azi_plan* p, hipStream_t s) {
     return AZI_OK;
 }
 
-int plan_corr_pair(azi_plan* p, hipStream_t s) {
+// Without what plan_corr_pair forms: raw frames take the correction pass.
+void plan_drop_forms(azi_plan* p) {
     p->corr.release();
     p->fcoef.release();
     p->ufix.release();
     p->wdark.release();
     p->folded = false;
     p->corr_kind = azi::kCorrPair;
+}
+
+int plan_corr_pair(azi_plan* p, hipStream_t s) {
+    plan_drop_forms(p);
     const bool map = p->stream.on && p->layout == AZI_LAYOUT_PIXEL;
     if (map && (p->has_dark || p->has_norm)) {
         const int rc = plan_fold_stream(p, s);
         p->folded = rc == AZI_OK;
-        if (rc != AZI_OK) {
-            p->corr.release();
-            p->fcoef.release();
-            p->wdark.release();
-            p->corr_kind = azi::kCorrPair;
-        }
+        if (rc != AZI_OK) plan_drop_forms(p);
         return rc;
     }
     if (!is_band(p->layout) || !gather_corrects(p->tiling.stage) ||
@@ -1137,11 +1164,7 @@ int plan_corr_pair(azi_plan* p, hipStream_t s) {
     if (p->layout == AZI_LAYOUT_RUN && folds(p->tiling.stage)) {
         const int rc = plan_fold(p, s);
         if (rc != AZI_OK) {
-            p->corr.release();
-            p->fcoef.release();
-            p->ufix.release();
-            p->wdark.release();
-            p->corr_kind = azi::kCorrPair;
+            plan_drop_forms(p);
             return rc;
         }
         p->folded = true;
@@ -1295,7 +1318,9 @@ int plan_create(const azi_geom* geom, int32_t npt, int32_t npt_azim, int32_t uni
     p->unit = unit;
     p->split = split;
     if (device >= 0) {
-        const int rc = plan_build_device(p.get(), npt, npt_azim, range2, device, stream);
+        const int rc = no_throw([&] {
+            return plan_build_device(p.get(), npt, npt_azim, range2, device, stream);
+        });
         if (rc != AZI_OK) return rc;
         *out = p.release();
         return AZI_OK;
@@ -1649,38 +1674,51 @@ int azi_plan_export_csc(const azi_plan* p, void* data, int32_t* bins, int32_t* c
 }
 
 int azi_plan_set_tiling(azi_plan* p, const azi_tiling* t) {
-    if (!p || !t) return fail(AZI_EINVAL, "plan and tiling must not be NULL");
-    if (!valid_tiling(*t)) return fail(AZI_EINVAL, kTilingRule);
-    const bool retile = t->tile_nnz != p->tiling.tile_nnz || t->band != p->tiling.band ||
-                        stream_tiling(*t, p->layout, p->m.two_d) !=
-                            stream_tiling(p->tiling, p->layout, p->m.two_d);
-    const bool restage = t->stage != p->tiling.stage;
-    const bool reblock = t->block != p->tiling.block;
-    p->tiling = *t;
-    if (p->device >= 0 && retile) {
-        DeviceGuard g(p->device);
-        if (g.err != hipSuccess) return hip_fail(g.err, "set device");
-        AZI_HIP(hipDeviceSynchronize(), "synchronise before retiling");
-        if (is_band(p->layout)) {
-            int rc = plan_upload_bands(p);
-            if (rc != AZI_OK) return rc;
-        } else if (p->layout == AZI_LAYOUT_PIXEL) {
-            bool streamed = false;
-            const int rc = plan_upload_stream(p, &streamed);
+    return no_throw([&]() -> int {
+        if (!p || !t) return fail(AZI_EINVAL, "plan and tiling must not be NULL");
+        if (!valid_tiling(*t)) return fail(AZI_EINVAL, kTilingRule);
+        const bool retile = t->tile_nnz != p->tiling.tile_nnz || t->band != p->tiling.band ||
+                            stream_tiling(*t, p->layout, p->m.two_d) !=
+                                stream_tiling(p->tiling, p->layout, p->m.two_d);
+        const bool restage = t->stage != p->tiling.stage;
+        const bool reblock = t->block != p->tiling.block;
+        const bool folded = p->folded || p->stream.on;
+        const azi_tiling old = p->tiling;
+        p->tiling = *t;
+        if (p->device >= 0 && retile) {
+            DeviceGuard g(p->device);
+            if (g.err != hipSuccess) return hip_fail(g.err, "set device");
+            AZI_HIP(hipDeviceSynchronize(), "synchronise before retiling");
+            // folded forms are in the order of the encoding that goes
+            if (p->folded) plan_drop_forms(p);
+            const int rce = no_throw([&]() -> int {
+                if (is_band(p->layout)) return plan_upload_bands(p);
+                bool streamed = false;
+                const int rc = p->layout == AZI_LAYOUT_PIXEL ? plan_upload_stream(p, &streamed)
+                                                             : AZI_OK;
+                if (rc == AZI_OK && !streamed) p->stream.release();
+                return rc;
+            });
+            if (rce != AZI_OK) {  // the encoding in use stays, with its tiling
+                const std::string why = azi_last_error();
+                p->tiling = old;
+                if (folded) (void)plan_corr_pair(p, nullptr);
+                return fail(rce, why);
+            }
+            const int rc = plan_upload_tiles(p);
             if (rc != AZI_OK) return rc;
         }
-        const int rc = plan_upload_tiles(p);
-        if (rc != AZI_OK) return rc;
-    }
-    // the folded form's U follows the pieces and the workgroup size
-    if (p->device >= 0 && (restage || ((p->folded || p->stream.on) && (retile || reblock)))) {
-        DeviceGuard g(p->device);
-        if (g.err != hipSuccess) return hip_fail(g.err, "set device");
-        AZI_HIP(hipDeviceSynchronize(), "synchronise before changing the stage");
-        const int rc = plan_corr_pair(p, nullptr);
-        if (rc != AZI_OK) return rc;
-    }
-    return AZI_OK;
+        // the folded form's U follows the pieces and the workgroup size
+        if (p->device >= 0 &&
+            (restage || ((folded || p->stream.on) && (retile || reblock)))) {
+            DeviceGuard g(p->device);
+            if (g.err != hipSuccess) return hip_fail(g.err, "set device");
+            AZI_HIP(hipDeviceSynchronize(), "synchronise before changing the stage");
+            const int rc = plan_corr_pair(p, nullptr);
+            if (rc != AZI_OK) return rc;
+        }
+        return AZI_OK;
+    });
 }
 
 int azi_plan_get_tiling(const azi_plan* p, azi_tiling* t, int32_t* ntiles) {
@@ -1876,7 +1914,7 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
         }
         return plan_upload_tiles(p);
     };
-    const int rc = body();
+    const int rc = no_throw(body);
     if (rc != AZI_OK) p->device = -1;
     return rc;
 }
@@ -2393,27 +2431,33 @@ int azi_batch_info(const azi_batch* b, int32_t* n, int64_t* npix, int64_t* npt, 
 }
 
 int azi_batch_set_tiling(azi_batch* b, const azi_tiling* t) {
-    if (!b || !t) return fail(AZI_EINVAL, "batch and tiling must not be NULL");
-    if (!valid_tiling(*t)) return fail(AZI_EINVAL, kTilingRule);
-    DeviceGuard g(b->device);
-    if (g.err != hipSuccess) return hip_fail(g.err, "set device");
-    const bool retile =
-        t->tile_nnz != b->tiling.tile_nnz || t->band != b->tiling.band || b->ntiles == 0 ||
-        stream_tiling(*t, b->layout, false) != stream_tiling(b->tiling, b->layout, false);
-    b->tiling = *t;
-    if (retile) {
-        AZI_HIP(hipDeviceSynchronize(), "synchronise before retiling");
-        if (is_band(b->layout) && (b->npieces_buf.p || b->stream.on)) {
-            int rc = batch_rebuild_bands(b);
-            if (rc != AZI_OK) return rc;
+    return no_throw([&]() -> int {
+        if (!b || !t) return fail(AZI_EINVAL, "batch and tiling must not be NULL");
+        if (!valid_tiling(*t)) return fail(AZI_EINVAL, kTilingRule);
+        DeviceGuard g(b->device);
+        if (g.err != hipSuccess) return hip_fail(g.err, "set device");
+        const bool retile =
+            t->tile_nnz != b->tiling.tile_nnz || t->band != b->tiling.band || b->ntiles == 0 ||
+            stream_tiling(*t, b->layout, false) != stream_tiling(b->tiling, b->layout, false);
+        const azi_tiling old = b->tiling;
+        b->tiling = *t;
+        if (retile) {
+            AZI_HIP(hipDeviceSynchronize(), "synchronise before retiling");
+            if (is_band(b->layout) && (b->npieces_buf.p || b->stream.on)) {
+                const int rc = no_throw([&] { return batch_rebuild_bands(b); });
+                if (rc != AZI_OK) {  // the encoding in use stays, with its tiling
+                    b->tiling = old;
+                    return rc;
+                }
+            }
+            std::vector<std::vector<int32_t>> store;
+            std::vector<const int32_t*> ptrs;
+            std::vector<int32_t> npts;
+            batch_local_indptr(b, store, ptrs, npts);
+            return batch_upload_tiles(b, ptrs, npts);
         }
-        std::vector<std::vector<int32_t>> store;
-        std::vector<const int32_t*> ptrs;
-        std::vector<int32_t> npts;
-        batch_local_indptr(b, store, ptrs, npts);
-        return batch_upload_tiles(b, ptrs, npts);
-    }
-    return AZI_OK;
+        return AZI_OK;
+    });
 }
 
 int azi_batch_get_tiling(const azi_batch* b, azi_tiling* t, int32_t* ntiles) {
@@ -2434,24 +2478,26 @@ namespace {
 // not take it.
 int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& ms, bool* done) {
     *done = false;
-    b->stream.release();
     if (!stream_tiling(b->tiling, b->layout, false)) return AZI_OK;
     azi::StreamMatrix sm;
     const int32_t px = stream_tile_px(b->npix);
-    b->stream_off.assign(b->n + 1, 0);
-    b->chunk_off.assign(b->n + 1, 0);
+    std::vector<int64_t> stream_off(b->n + 1, 0), chunk_off(b->n + 1, 0);
     for (int32_t k = 0; k < b->n; ++k) {
         if (b->two_d[k] || !azi::build_stream(*ms[k], b->hw[k].first, b->hw[k].second, px,
                                               b->pix_off[k], b->bin_off[k], sm))
             return AZI_OK;
-        b->stream_off[k + 1] = (int64_t)sm.tiles.size();
-        b->chunk_off[k + 1] = (int64_t)sm.chunks.size();
+        stream_off[k + 1] = (int64_t)sm.tiles.size();
+        chunk_off[k + 1] = (int64_t)sm.chunks.size();
     }
+    StreamBufs sb;
     const int rc = upload_stream(sm, false, b->npt, b->dtype, b->accum, b->device, b->colptr,
-                                 b->cdata, b->stream);
+                                 b->cdata, sb);
     if (rc != AZI_OK) return rc;
+    b->stream = std::move(sb);
+    b->stream_off.swap(stream_off);
+    b->chunk_off.swap(chunk_off);
     for (DevBuf* d : {&b->npieces_buf, &b->npacked, &b->ncoef, &b->bin_slot, &b->bin_count,
-                      &b->nparts_buf})
+                      &b->nparts_buf, &b->rgbase})
         d->release();
     b->npieces = 0;
     *done = true;
@@ -2483,16 +2529,14 @@ hipError_t batch_launch(const azi_batch* b, const void* img, int32_t img_dtype, 
 }
 
 int batch_build_bands(azi_batch* b, const std::vector<const azi::HostMatrix*>& ms) {
-    b->rgbase.release();
     bool streamed = false;
     const int rcs = batch_build_stream(b, ms, &streamed);
     if (rcs != AZI_OK || streamed) return rcs;
     if (b->layout == AZI_LAYOUT_RUN) {
         azi::RunMatrix rm;
-        b->band_rows = azi::kRunRows;
-        b->piece_off.assign(b->n + 1, 0);
+        std::vector<int64_t> piece_off(b->n + 1, 0);
         for (int32_t k = 0; k < b->n; ++k) {
-            b->piece_off[k] = (int64_t)rm.pieces.size();
+            piece_off[k] = (int64_t)rm.pieces.size();
             if (!azi::build_runs(*ms[k], std::max(64, piece_nnz(b->tiling, ms[k]->nnz()) / 2),
                                  b->pix_off[k], b->bin_off[k], rm, nullptr,
                                  run_waves(b->tiling)))
@@ -2500,7 +2544,7 @@ int batch_build_bands(azi_batch* b, const std::vector<const azi::HostMatrix*>& m
                             "the run layout takes images below 2^27 pixels and 2^31 runs and "
                             "entries per batch");
         }
-        b->piece_off[b->n] = (int64_t)rm.pieces.size();
+        piece_off[b->n] = (int64_t)rm.pieces.size();
         azi::BandMatrix bm;
         bm.pieces.swap(rm.pieces);
         bm.packed.swap(rm.runs);
@@ -2508,28 +2552,36 @@ int batch_build_bands(azi_batch* b, const std::vector<const azi::HostMatrix*>& m
         bm.bin_slot.swap(rm.bin_slot);
         bm.bin_count.swap(rm.bin_count);
         bm.nslots = rm.nslots;
+        b->band_rows = azi::kRunRows;
+        b->rgbase.release();
         int rc = upload_bands(bm, b->dtype, b->device, b->npieces_buf, b->npacked, b->ncoef,
                               b->bin_slot, b->bin_count, b->nparts_buf, b->max_count);
         if (rc != AZI_OK) return rc;
         AZI_HIP(b->rgbase.upload(rm.gbase.data(), rm.gbase.size() * 4, b->device), "run groups");
         b->npieces = (int32_t)bm.pieces.size();
+        b->piece_off.swap(piece_off);
+        b->stream.release();
         return AZI_OK;
     }
     azi::BandMatrix bm;
-    b->band_rows = band_rows_of(b->tiling);
-    b->piece_off.assign(b->n + 1, 0);
+    const int32_t rows = band_rows_of(b->tiling);
+    std::vector<int64_t> piece_off(b->n + 1, 0);
     for (int32_t k = 0; k < b->n; ++k) {
-        b->piece_off[k] = (int64_t)bm.pieces.size();
-        if (!azi::build_bands(*ms[k], b->band_rows, piece_nnz(b->tiling, ms[k]->nnz()),
+        piece_off[k] = (int64_t)bm.pieces.size();
+        if (!azi::build_bands(*ms[k], rows, piece_nnz(b->tiling, ms[k]->nnz()),
                               b->pix_off[k],
                               b->bin_off[k], bm))
             return fail(AZI_EOVERFLOW, "the band layout takes images below 2^27 pixels");
     }
-    b->piece_off[b->n] = (int64_t)bm.pieces.size();
+    piece_off[b->n] = (int64_t)bm.pieces.size();
+    b->band_rows = rows;
+    b->rgbase.release();
     int rc = upload_bands(bm, b->dtype, b->device, b->npieces_buf, b->npacked, b->ncoef,
                           b->bin_slot, b->bin_count, b->nparts_buf, b->max_count);
     if (rc != AZI_OK) return rc;
     b->npieces = (int32_t)bm.pieces.size();
+    b->piece_off.swap(piece_off);
+    b->stream.release();
     return AZI_OK;
 }
 

@@ -13,10 +13,10 @@ int main(int argc, char** argv) {
     const bool two_d = std::atoi(argv[1]) != 0;
     const int32_t dtype = std::atoi(argv[2]) ? AZI_F32 : AZI_F64;
     azi_geom g{};
-    g.h = 1536;
-    g.w = 1500;
-    g.center_y_px = 700.3;
-    g.center_x_px = 800.6;
+    g.h = two_d ? 1536 : 300;
+    g.w = two_d ? 1500 : 280;
+    g.center_y_px = g.h * 0.45;
+    g.center_x_px = g.w * 0.55;
     g.pixel_y_m = g.pixel_x_m = 1e-4;
     g.dist_m = 0.1;
     g.wavelength_m = 1e-10;
@@ -28,7 +28,7 @@ int main(int argc, char** argv) {
     azi_plan* p = nullptr;
     const int rc0 = two_d ? azi_plan_create2d(&g, 40, 12, AZI_UNIT_R_M, AZI_SPLIT_BBOX, nullptr,
                                               dtype, AZI_ACC_F64, &p)
-                          : azi_plan_create(&g, 400, AZI_UNIT_R_M, AZI_SPLIT_BBOX, nullptr, dtype,
+                          : azi_plan_create(&g, 90, AZI_UNIT_R_M, AZI_SPLIT_BBOX, nullptr, dtype,
                                             AZI_ACC_F64, &p);
     if (rc0 != AZI_OK || azi_plan_upload(p, 0) != AZI_OK) return 2;
     if (std::atoi(argv[3]) >= 0) {

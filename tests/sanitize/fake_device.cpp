@@ -10,9 +10,16 @@
 namespace fake {
 std::vector<std::string> calls;
 azi::StreamLaunch stream;
+azi::BandLaunch band;
 const void *dark = nullptr, *norm = nullptr;
 int64_t fail_in = -1, live = 0;
 static std::map<void*, size_t> sizes;
+bool held(const void* p) {
+    auto i = sizes.upper_bound(const_cast<void*>(p));
+    if (i == sizes.begin()) return false;
+    --i;
+    return (const char*)p < (const char*)i->first + i->second;
+}
 static hipError_t note(const char* name) {
     calls.push_back(name);
     return hipSuccess;
@@ -94,7 +101,10 @@ hipError_t launch_correct(const void*, int32_t, const int32_t*, const void* dark
     fake::norm = norm;
     return note("correct");
 }
-hipError_t launch_band(const BandLaunch&, hipStream_t) { return note("band"); }
+hipError_t launch_band(const BandLaunch& a, hipStream_t) {
+    fake::band = a;
+    return note("band");
+}
 int32_t runs_resident_per_cu(int32_t, int32_t, int32_t waves) { return 32 / waves; }
 hipError_t launch_corr_pair(const void*, const void*, void*, int32_t, int64_t, hipStream_t) {
     return note("corr_pair");

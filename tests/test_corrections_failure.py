@@ -3,6 +3,7 @@ over a fake device): frames integrated afterwards are still corrected."""
 import os
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -12,27 +13,41 @@ CSRC = os.path.join(ROOT, "paper_1412_6367_amd", "csrc")
 SANITIZE = os.path.join(ROOT, "tests", "sanitize")
 
 
-def compile_over_fake_device(exe, *sources):
+@pytest.fixture(scope="module")
+def over_fake_device(tmp_path_factory):
+    """Links a harness with the C ABI's host code and the fake device."""
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
-    r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-pthread", "-w",
-                        "-D__HIP_PLATFORM_AMD__", "-D__align__(x)=", "-DHIP_SYMBOL(x)=(&x)",
-                        "-I/opt/rocm/include", "-fsanitize=address,undefined",
-                        "-fno-sanitize-recover=all", "-x", "c++",
-                        os.path.join(CSRC, "azint_api.hip"),
-                        os.path.join(CSRC, "plan_builder.cpp"),
-                        os.path.join(CSRC, "stream_builder.cpp"),
-                        os.path.join(SANITIZE, "fake_device.cpp"),
-                        *(os.path.join(SANITIZE, s) for s in sources), "-o", exe],
-                       capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr
-    return exe
+    tmp = tmp_path_factory.mktemp("fake")
+
+    def compile_one(src):
+        obj = str(tmp / (os.path.basename(src) + ".o"))
+        r = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-w",
+                            "-D__HIP_PLATFORM_AMD__", "-D__align__(x)=", "-DHIP_SYMBOL(x)=(&x)",
+                            "-I/opt/rocm/include", "-fsanitize=address", "-x", "c++", "-c", src,
+                            "-o", obj], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return obj
+
+    common = [os.path.join(CSRC, "azint_api.hip"), os.path.join(CSRC, "plan_builder.cpp"),
+              os.path.join(CSRC, "stream_builder.cpp"), os.path.join(SANITIZE, "fake_device.cpp")]
+    with ThreadPoolExecutor(4) as pool:
+        objects = list(pool.map(compile_one, common))
+
+    def link(harness):
+        exe = str(tmp / harness)
+        r = subprocess.run(["g++", "-fsanitize=address", "-pthread", *objects,
+                            compile_one(os.path.join(SANITIZE, harness + ".cpp")), "-o", exe],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return exe
+
+    return link
 
 
 @pytest.fixture(scope="module")
-def harness(tmp_path_factory):
-    return compile_over_fake_device(str(tmp_path_factory.mktemp("corr") / "harness"),
-                                    "corrections_harness.cpp")
+def harness(over_fake_device):
+    return over_fake_device("corrections_harness")
 
 
 @pytest.mark.parametrize("two_d,dtype,stage", [
@@ -42,3 +57,14 @@ def test_frames_after_a_failed_call_are_corrected(two_d, dtype, stage, harness):
     r = subprocess.run([harness, str(two_d), str(dtype), str(stage)], capture_output=True,
                        text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+
+
+@pytest.fixture(scope="module")
+def encodings(over_fake_device):
+    return over_fake_device("encodings_harness")
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2], ids=["map", "profile", "batch"])
+def test_a_failed_retiling_leaves_a_whole_encoding(kind, encodings):
+    r = subprocess.run([encodings, str(kind)], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), (r.returncode, r.stdout + r.stderr)
