@@ -410,9 +410,10 @@ int azi_plan_run_schedule(const azi_plan* plan, int32_t tile_nnz, int64_t* nruns
  * average, more than 8 MiB of partial sums (a batch: one instance of these, or
  * positions past 2^31).  The per-run dark values of AZI_STAGE_FOLD are
  * per-pixel ones there, in the same types.
- * Two-dimensional plans in AZI_LAYOUT_PIXEL with their default tiling are
- * integrated from the stream encoding too (their tiles' bins are radial bins
- * of a few wedges), unless a partial sum would stand for under four nonzeros.
+ * Two-dimensional plans of 1e6 pixels or more in AZI_LAYOUT_PIXEL with their
+ * default tiling are integrated from the stream encoding too (their tiles' bins
+ * are radial bins of a few wedges), unless a partial sum would stand for under
+ * four nonzeros; smaller ones would take longer to encode than to build.
  * Raw frames are then integrated in one pass: A_bp / norm, rounded once when
  * the corrections are set, times raw - dark (as many roundings as A_bp times
  * (raw - dark) / norm), and the work image is not written.  azi_plan_stage and
@@ -627,9 +628,9 @@ int azi_graph_create_batch(azi_batch* batch, const void* x, void* out_I, void* o
 
 /*
  * Capture one plan's raw-image pipeline (azi_integrate1d_raw) into a graph.
- * A pass of two kernels (the stream encoding) is recorded as their launches
- * with these arguments, which costs less to replay; it may be replayed into
- * a capturing stream.
+ * A pass of two kernels (the stream encoding; two-dimensional plans in the
+ * pixel layout) is recorded as their launches with these arguments, which
+ * costs less to replay; it may be replayed into a capturing stream.
  */
 int azi_graph_create_plan(const azi_plan* plan, const void* raw, int32_t raw_dtype,
                           void* out_I, void* out_W, void* out_U, double empty,

@@ -11,6 +11,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -342,6 +343,19 @@ int32_t stream_tile_px(int64_t npix, bool two_d = false) {
     return (int32_t)std::max<int64_t>(1024, std::min<int64_t>(3072, npix / 2048));
 }
 
+// Pixels from which a two-dimensional plan is encoded.  The encoder runs on the
+// host, beside the copies of the matrix that the plan's set-up makes anyway;
+// from here on they hide it, below they are too short.  Set-up of a plan built
+// on the device, in us, without and with the encoding, 16 host threads:
+//                  36 wedges          360 wedges
+//   330 x 330      620 and 1880       1000 and 4200
+//   720 x 720      2100 and 5800      2800 and 9900
+//   1000 x 1000    4200 and 4000      13200 and 13400
+//   3162 x 3162    98000 and 99000    105000 and 107000
+// (14000 and 20500, 115000 and 160000 for the latter two with the encoder
+// after the copies.)
+constexpr int64_t kStreamMapPix = 1000000;
+
 // The tilings that take the stream encoding where it applies: in the run
 // layout, one-dimensional plans, those sized by the library (tile_nnz 0, four
 // bands per workgroup, no persistent grid); in the pixel layout,
@@ -572,15 +586,25 @@ struct azi_batch {
     std::vector<int64_t> stile_off;  // stage tiles of instance k: [stile_off[k], stile_off[k+1])
 };
 
-// A captured pass.  One over the stream encoding is two kernels: its frozen
-// arguments are kept instead, and a replay launches them (a graph launch of
-// two nodes costs the host about 17 us on ROCm 7, two kernel launches 5; a
-// 512 x 512 frame's replay 18.9 -> 9.0 us).  Passes of other encodings and of
-// batches are graphs: there the device is the slower side, or the nodes many.
+struct azi_raw_pass {
+    const void* raw = nullptr;
+    int32_t raw_dtype = AZI_I32;
+    const void *dark = nullptr, *norm = nullptr;
+    void* x = nullptr;
+    int64_t npix = 0;
+};
+// A captured pass.  One over the stream encoding, or of a map without it, is
+// two kernels: its frozen arguments are kept instead, and a replay launches
+// them (a graph launch of two nodes costs the host about 17 us on ROCm 7, two
+// kernel launches 5; a 512 x 512 frame's replay 18.9 -> 9.0 us).  Passes of
+// other encodings and of batches are graphs: there the device is the slower
+// side, or the nodes many.
 struct azi_graph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     azi::StreamLaunch pass;
+    azi::ForwardLaunch rows;   // a map without the encoding: the row kernel,
+    azi_raw_pass raw;          // after its correction pass (x set)
     bool direct = false;
     int device = -1;
 };
@@ -715,21 +739,61 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
     return AZI_OK;
 }
 
+// Whether a plan is to have the stream encoding, where that applies.
+bool plan_streams(const azi_plan* p) {
+    return stream_tiling(p->tiling, p->layout, p->m.two_d) &&
+           (!p->m.two_d || p->m.npix >= kStreamMapPix);
+}
+
+// The stream encoding of a plan's matrix, built by a thread of its own from
+// its pixel-major positions while the caller copies the rest of the matrix.
+struct StreamJob {
+    azi::StreamMatrix sm;
+    bool built = false, started = false, memory = false;
+    std::thread thread;
+    StreamJob() = default;
+    StreamJob(const StreamJob&) = delete;
+    StreamJob& operator=(const StreamJob&) = delete;
+    ~StreamJob() { wait(); }
+    void build(const azi_plan* p) {
+        built = azi::build_stream(p->m, p->geom.h, p->geom.w,
+                                  stream_tile_px(p->m.npix, p->m.two_d), 0, 0, sm);
+    }
+    void start(const azi_plan* p) {
+        try {
+            thread = std::thread([this, p] {
+                try {
+                    build(p);
+                } catch (...) {
+                    memory = true;
+                }
+            });
+            started = true;
+        } catch (...) {  // no thread to be had: built when it is asked for
+        }
+    }
+    void wait() {
+        if (thread.joinable()) thread.join();
+    }
+};
+
 // The stream encoding of a plan whose tiling asks for it; *done is false
 // where it does not apply (bins too fine, partial sums beyond the
 // allocation-free call's array): the layout's own form then serves.  The
 // encoding in use, this one or the layout's, goes once the new one is placed.
-int plan_upload_stream(azi_plan* p, bool* done) {
+int plan_upload_stream(azi_plan* p, bool* done, StreamJob* job = nullptr) {
     *done = false;
-    if (!stream_tiling(p->tiling, p->layout, p->m.two_d)) return AZI_OK;
+    if (!plan_streams(p)) return AZI_OK;
     try {
-        azi::StreamMatrix sm;
-        if (!azi::build_stream(p->m, p->geom.h, p->geom.w, stream_tile_px(p->m.npix, p->m.two_d),
-                               0, 0, sm) ||
-            (!p->m.two_d && (size_t)sm.nparts * 8 > kScratchBytes))
+        StreamJob own;
+        if (!job) job = &own;
+        if (job->started) job->wait();
+        else job->build(p);
+        if (job->memory) throw std::bad_alloc();
+        if (!job->built || (!p->m.two_d && (size_t)job->sm.nparts * 8 > kScratchBytes))
             return AZI_OK;
         StreamBufs b;
-        const int rc = upload_stream(sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
+        const int rc = upload_stream(job->sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
                                      p->colptr, p->cdata, b);
         if (rc != AZI_OK) return rc;
         p->stream = std::move(b);
@@ -1517,6 +1581,17 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
         AZI_HIP(azi::launch_first(p->colptr.as<int32_t>(), p->rowidx.as<int32_t>(), npix,
                                   p->cfirst.as<int32_t>(), flag, s), "first bins");
     }
+    // maps: the positions come to the host first, and are encoded there while
+    // the rest of the matrix is ordered and copied
+    StreamJob job;
+    const bool streams = two_d && plan_streams(p);
+    if (streams) {
+        int rc = download(m.colptr, p->colptr.p, npix + 1, s);
+        if (rc == AZI_OK) rc = download(m.rowidx, p->rowidx.p, nnz, s);
+        if (rc != AZI_OK) return rc;
+        AZI_HIP(hipStreamSynchronize(s), "download the matrix");
+        job.start(p);
+    }
     // bin-major order: stable sort of the pixel-major entries by bin
     AZI_HIP(azi::launch_sort(p->rowidx.as<int32_t>(), nnz, bit_length(m.npt - 1),
                              skeys.as<int32_t>(), perm.as<int32_t>(), work.p, s), "sort");
@@ -1540,8 +1615,8 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     // host copy of the matrix, for export and for the host-side layouts
     int32_t scattered = 0;
     try {
-        int rc = download(m.colptr, p->colptr.p, npix + 1, s);
-        if (rc == AZI_OK) rc = download(m.rowidx, p->rowidx.p, nnz, s);
+        int rc = streams ? AZI_OK : download(m.colptr, p->colptr.p, npix + 1, s);
+        if (rc == AZI_OK && !streams) rc = download(m.rowidx, p->rowidx.p, nnz, s);
         if (rc == AZI_OK) rc = download(m.cdata, c64, nnz, s);
         if (rc == AZI_OK) rc = download(m.indptr, p->rowptr.p, (int64_t)m.npt + 1, s);
         if (rc == AZI_OK) rc = download(m.indices, p->indices.p, nnz, s);
@@ -1559,7 +1634,7 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     try {
         if (two_d) {
             bool streamed = false;
-            const int rc = plan_upload_stream(p, &streamed);
+            const int rc = plan_upload_stream(p, &streamed, &job);
             if (rc != AZI_OK) return rc;
         }
         return plan_device_schedules(p, nnz, !two_d);
@@ -1844,6 +1919,8 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
         const int64_t nnz = p->m.nnz();
         const int64_t nnz_alloc = round_up(nnz, kPad) + kPad;
         const size_t es = elem_size(p->dtype);
+        StreamJob job;  // beside the copies below
+        if (p->m.two_d && plan_streams(p)) job.start(p);
         try {
             std::vector<int32_t> idx((size_t)nnz_alloc, 0);
             const double* coef = p->m.data.data();
@@ -1892,7 +1969,7 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
         }
         if (p->layout == AZI_LAYOUT_PIXEL) {
             bool streamed = false;
-            const int rc2 = plan_upload_stream(p, &streamed);
+            const int rc2 = plan_upload_stream(p, &streamed, &job);
             if (rc2 != AZI_OK) return rc2;
         }
         if (p->layout == AZI_LAYOUT_FUSED) {
@@ -3123,13 +3200,20 @@ int azi_graph_create_plan(const azi_plan* p, const void* raw, int32_t raw_dtype,
     *out = nullptr;
     int rc = check_plan_ready(p);
     if (rc != AZI_OK) return rc;
-    if (p->stream.on && plan_raw_in_gather(p)) {
+    const bool streamed = p->stream.on && plan_raw_in_gather(p);
+    if (streamed || (p->m.two_d && p->layout == AZI_LAYOUT_PIXEL)) {
         if (!I) return fail(AZI_EINVAL, "out_I must not be NULL");
         if (!raw) return fail(AZI_EINVAL, "raw must not be NULL");
         if (!valid_raw_dtype(raw_dtype)) return fail(AZI_EINVAL, "unknown raw dtype");
         azi_graph* gr = new (std::nothrow) azi_graph;
         if (!gr) return fail(AZI_ENOMEM, "out of host memory");
-        gr->pass = plan_stream_raw_args(p, raw, raw_dtype, I, W, U, empty);
+        if (streamed) {
+            gr->pass = plan_stream_raw_args(p, raw, raw_dtype, I, W, U, empty);
+        } else {
+            gr->raw = azi_raw_pass{raw, raw_dtype, p->has_dark ? p->dark.p : nullptr,
+                                   p->has_norm ? p->norm.p : nullptr, p->xwork.p, p->m.npix};
+            gr->rows = plan_forward_args(p, p->xwork.p, I, W, U, empty);
+        }
         gr->direct = true;
         gr->device = p->device;
         *out = gr;
@@ -3146,6 +3230,14 @@ int azi_graph_launch(azi_graph* gr, void* stream) {
     if (!gr) return fail(AZI_EINVAL, "graph is NULL");
     DeviceGuard g(gr->device);
     if (g.err != hipSuccess) return hip_fail(g.err, "set device");
+    if (gr->direct && gr->raw.x) {
+        const azi_raw_pass& r = gr->raw;
+        AZI_HIP(azi::launch_correct(r.raw, r.raw_dtype, nullptr, r.dark, r.norm, r.x, gr->rows.dtype,
+                                    r.npix, static_cast<hipStream_t>(stream)),
+                "graph launch");
+        AZI_HIP(azi::launch_forward(gr->rows, static_cast<hipStream_t>(stream)), "graph launch");
+        return AZI_OK;
+    }
     if (gr->direct) {
         AZI_HIP(azi::launch_stream(gr->pass, static_cast<hipStream_t>(stream)), "graph launch");
         return AZI_OK;

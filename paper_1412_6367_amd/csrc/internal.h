@@ -311,6 +311,8 @@ struct StreamMatrix {
 inline int64_t stream_reach(int32_t th, int32_t w) { return (int64_t)(th + 127) * w + 128; }
 constexpr int32_t kStreamMinPix = 192;
 constexpr int32_t kStreamColBits = 6;  // columns of a tile: 64
+//
+// Reads the pixel-major positions alone (colptr, rowidx) of m's arrays.
 bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, int64_t pix_off,
                   int64_t bin_off, StreamMatrix& sm);
 

@@ -439,7 +439,8 @@ constexpr int32_t kBuildThreads = 16;
 
 bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, int64_t pix_off,
                   int64_t bin_off, StreamMatrix& sm) {
-    if (m.npix < 4 || sm.ncoef + m.nnz() >= kLimit) return false;
+    const int64_t nnz = (int64_t)m.rowidx.size();
+    if (m.npix < 4 || sm.ncoef + nnz >= kLimit) return false;
     if (m.two_d && (m.npt_rad < 1 || pix_off || bin_off)) return false;
     // strips of equal width but for the rounding to 8 columns, and rows of
     // about tile_px pixels, a multiple of 16 (four blocks of 64 x 4 pixels,
@@ -529,7 +530,7 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
     }
     const int64_t ntiles = (int64_t)(sm.tiles.size() - t0);
     if (ntiles > 4 * per_band * bands && ntiles * kStreamMinPix > sm.npix - px0) return false;
-    if (m.two_d && (sm.nparts - parts0) * 4 > m.nnz()) return false;
+    if (m.two_d && (sm.nparts - parts0) * 4 > nnz) return false;
     // the windows that reach each chunk of bins, in tile order
     const int32_t nch = (m.npt + kStreamChunk - 1) / kStreamChunk;
     const size_t e0 = sm.ents.size();

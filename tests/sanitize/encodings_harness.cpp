@@ -66,8 +66,8 @@ int main(int argc, char** argv) {
     if (argc != 2) return 2;
     kind = std::atoi(argv[1]);
     azi_geom g{};
-    g.h = kind == 0 ? 1536 : 200;
-    g.w = kind == 0 ? 1500 : 180;
+    g.h = kind == 0 ? 1000 : 200;
+    g.w = kind == 0 ? 1000 : 180;
     g.center_y_px = g.h * 0.45;
     g.center_x_px = g.w * 0.55;
     g.pixel_y_m = g.pixel_x_m = 1e-4;
@@ -122,6 +122,23 @@ int main(int argc, char** argv) {
                 if (over) break;
             }
         }
+    for (long k = 0; kind == 0; k += 5) {  // an upload: the encoder beside the copies
+        new_in = k;
+        int rc = AZI_OK;
+        try {
+            rc = azi_plan_upload(p, 0);
+        } catch (const std::exception&) {
+            std::printf("thrown out of the upload\n");
+            return 1;
+        }
+        const bool over = new_in.exchange(-1) >= 0;
+        if (rc != AZI_OK && rc != AZI_ENOMEM) return 2;
+        if (azi_plan_upload(p, 0) != AZI_OK || pass(true)) {
+            std::printf("not uploaded again after host allocation %ld\n", k);
+            return 1;
+        }
+        if (over) break;
+    }
     azi_batch_destroy(b);
     azi_plan_destroy(p);
     std::free(image);

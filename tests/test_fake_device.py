@@ -1,5 +1,5 @@
-"""Corrections whose set-up runs out of memory half-way (CPU only, the C ABI
-over a fake device): frames integrated afterwards are still corrected."""
+"""The C ABI's host code over a fake device (CPU only): what is left after a
+set-up that runs out of memory half-way, and which kernels a pass takes."""
 import os
 import shutil
 import subprocess
@@ -68,3 +68,18 @@ def encodings(over_fake_device):
 def test_a_failed_retiling_leaves_a_whole_encoding(kind, encodings):
     r = subprocess.run([encodings, str(kind)], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0 and r.stdout.startswith("ok"), (r.returncode, r.stdout + r.stderr)
+
+
+@pytest.fixture(scope="module")
+def routes(over_fake_device):
+    return over_fake_device("routes_harness")
+
+
+@pytest.mark.parametrize("shape,image,raw", [
+    ((330, 330, 100, 36), "forward", "correct forward"),    # set up in a few us: no encoding
+    ((999, 1000, 100, 12), "forward", "correct forward"),   # a row short of the line
+    ((1000, 1000, 100, 12), "stream", "stream"),
+], ids=str)
+def test_maps_are_encoded_from_a_million_pixels(shape, image, raw, routes):
+    r = subprocess.run([routes, *map(str, shape)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip() == f"image {image}, raw {raw}", r.stdout + r.stderr

@@ -6,7 +6,10 @@ import numpy as np
 import pytest
 import torch
 
-from tests.helpers import azint
+import oracle
+from tests.helpers import azint, norm_err
+from tests.test_gpu_2d import oracle2d
+from tests.test_gpu_forward import TOL32_F64, TOL64, check
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +48,124 @@ def test_gradient_towards_raw_of_masked_pixels(dtype, dev):
     assert torch.equal(a[keep], b[keep])
     assert torch.equal(torch.signbit(a[keep]), torch.signbit(b[keep]))
     assert bool(torch.isnan(a).any())
+
+
+# Maps of a million pixels or more, which are encoded: h, w, center_y, center_x,
+# npt, npt_azim, split
+MAPS = [
+    (1000, 1000, 500.3, 480.2, 60, 36, "bbox"),
+    (1001, 1003, 500.5, 501.5, 400, 360, "bbox"),    # the beam inside a pixel: it lies in all wedges
+    (997, 1009, -20.0, 400.0, 80, 90, "bbox"),       # the beam off the detector
+    (1024, 980, 500.0, 490.0, 50, 24, "full"),
+]
+KINDS = [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "kahan32")]
+
+
+@pytest.fixture(scope="module")
+def map_matrix():
+    made = {}
+
+    def get(g):
+        if g not in made:
+            made.clear()
+            made[g] = oracle2d(*g[:6], "r_m", g[6])
+        return made[g]
+
+    return get
+
+
+def map_plan(g, dtype, accum, dev, on_device=False):
+    az = azint()
+    kw = dict(npt_azim=g[5], center=g[2:4], split=g[6], dtype=dtype, accum=accum)
+    if on_device:
+        return az.Plan.on_device(g[0], g[1], g[4], device=dev, **kw)
+    return az.Plan(g[0], g[1], g[4], device=dev, **kw)
+
+
+@pytest.mark.parametrize("dtype,accum", KINDS, ids=["f64", "f32", "k32"])
+@pytest.mark.parametrize("g", MAPS, ids=lambda g: f"{g[0]}x{g[1]}-{g[5]}-{g[6]}")
+def test_encoded_map_corrections_and_raw_types(g, dtype, accum, dev, map_matrix):
+    """Every raw type, and every kind of correction: dark counts of 16 bits, as
+    floats, as doubles; dark or norm alone; neither."""
+    say("map", g, dtype, accum)
+    m, n = map_matrix(g), g[0] * g[1]
+    npd = np.float64 if dtype == torch.float64 else np.float32
+    tol = TOL64 if dtype == torch.float64 else TOL32_F64
+    plan = map_plan(g, dtype, accum, dev)
+    bytes_encoded = plan.device_bytes()
+    gen = np.random.default_rng(g[0])
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    flat = gen.uniform(0.9, 1.1, n).astype(npd)
+    counts = gen.integers(0, 60, n)
+    raws = [gen.integers(60, 30000, n).astype(k) for k in
+            (np.int32, np.int16, np.uint16, np.uint32, np.float32, np.float64)]
+
+    def run(raw, dark, flat, what):
+        plan.set_corrections(dark=None if dark is None else t(dark),
+                             flat=None if flat is None else t(flat))
+        out = plan.integrate_raw(t(raw), empty=7.0)
+        torch.cuda.synchronize()
+        f = lambda a: None if a is None else a.astype(np.float64)
+        check(out, m, oracle.correct(raw, f(dark), f(flat), None, None), tol, empty=7.0, what=what)
+
+    for raw in raws:
+        run(raw, counts.astype(npd), flat, f"raw {raw.dtype}")
+    for add in (0.25, 0.1, 70000.0):
+        run(raws[0] + 70000, (counts + add).astype(npd), flat, f"dark + {add}")
+    run(raws[0], (counts + 0.1).astype(npd), None, "dark alone")
+    run(raws[0], None, flat, "norm alone")
+    run(raws[0], None, None, "neither")
+    x = raws[5].astype(npd)
+    check(plan.integrate(t(x), empty=7.0), m, x.astype(np.float64), tol, empty=7.0, what="image")
+    plan.set_tiling(variant=0)  # out of the encoding: the row kernel
+    assert plan.device_bytes() < bytes_encoded
+    check(plan.integrate(t(x), empty=7.0), m, x.astype(np.float64), tol, empty=7.0, what="rows")
+
+
+@pytest.mark.parametrize("g", MAPS[:3], ids=lambda g: f"{g[0]}x{g[1]}-{g[5]}")
+def test_map_built_on_the_device(g, dev):
+    """Encoded from the downloaded positions beside the other copies: the sums
+    of the matrix that it exports, the same bits from every build.  (Its azimuths
+    are the device's atan2, so a host-built plan's bits may differ.)"""
+    say("map on the device", g)
+    x = np.random.default_rng(5).integers(0, 1 << 20, g[0] * g[1]).astype(np.int32)
+    raw = torch.from_numpy(x).to(dev)
+    first = None
+    for _ in range(3):
+        plan = map_plan(g, torch.float64, "f64", dev, on_device=True)
+        out = plan.integrate_raw(raw)
+        torch.cuda.synchronize()
+        first = first or out
+        for u, v in zip(out, first):
+            assert torch.equal(u, v)
+    data, bins, colptr = plan.export_csc()
+    per_pixel = np.repeat(x.astype(np.float64), np.diff(colptr))
+    W = np.bincount(bins, weights=data * per_pixel, minlength=plan.npt)
+    U = np.bincount(bins, weights=data, minlength=plan.npt)
+    assert norm_err(first[1].cpu().numpy(), W, W) <= TOL64
+    assert norm_err(first[2].cpu().numpy(), U, U) <= TOL64
+
+
+def test_encoded_map_keeps_special_values_in_their_bins(dev):
+    """NaN and infinite pixels, one of them in several wedges, reach their own
+    bins only; so do those of a raw float frame."""
+    say("map special values")
+    g = MAPS[0]
+    plan = map_plan(g, torch.float64, "f64", dev)
+    data, bins, colptr = plan.export_csc()
+    n = g[0] * g[1]
+    x = np.random.default_rng(3).uniform(1, 50, n)
+    ref = plan.integrate(torch.from_numpy(x).to(dev))[1].cpu().numpy()
+    beam = 500 * g[1] + 480
+    many = beam + 5  # a few pixels from the beam: in several wedges
+    bad = {7 * g[1] + 13: np.nan, 600 * g[1] + 41: np.inf, many: -np.inf, n - 1: np.nan}
+    for p, v in bad.items():
+        x[p] = v
+    hit = np.zeros(plan.npt, bool)
+    for p in bad:
+        hit[bins[colptr[p]:colptr[p + 1]]] = True
+    xt = torch.from_numpy(x).to(dev)
+    for W in (plan.integrate(xt)[1], plan.integrate_raw(xt)[1]):
+        W = W.cpu().numpy()
+        assert np.all(~np.isfinite(W[hit]))
+        assert np.array_equal(W[~hit], ref[~hit])
