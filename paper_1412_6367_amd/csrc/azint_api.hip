@@ -322,6 +322,7 @@ struct StreamBufs {
     int32_t ntiles = 0, nblanks = 0, nchunks = 0, slots = 4, ents_most = 0;
     int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
     bool over = true, cached = false, on = false;
+    bool images = true;       // images too, not raw frames alone (maps: stream_images)
     void release() {
         built.release();
         work.release();
@@ -433,6 +434,22 @@ azi::StreamCoefLaunch stream_coef_args(const StreamBufs& b, const DevBuf& colptr
 bool stream_cached(const azi::StreamMatrix& sm, int32_t dtype) {
     const int64_t bytes = (int64_t)sm.words.size() * 2 + sm.ncoef * (int64_t)elem_size(dtype);
     return bytes <= ((int64_t)(dtype == AZI_F64 ? 64 : 160) << 20);
+}
+
+// Whether images that are corrected already take a map's encoding too.  The row
+// kernel reads such an image as it is, and its time follows the entries; the
+// stream kernel's follows the partial sums as well, which many wedges over
+// few pixels multiply (a raw frame always gains: the row kernel takes a
+// correction pass before it).  us an image, rows and stream, by entries per
+// partial sum (n x n pixels, one plan):
+//   float64  9.4 (1000)  14.9 and 19.1     float32  9.4 (1000)  11.9 and 16.7
+//            13.6 (1800) 27.4 and 31.0              13.6 (1800) 22.2 and 24.0
+//            17.0 (2300) 35.8 and 40.5              15.4 (2048) 31.1 and 27.7
+//            19.0 (2600) 42.7 and 46.2              19.0 (2600) 40.1 and 34.9
+//            22.9 (1800) 37.3 and 33.9              30.4 (2600) 70.4 and 40.4
+//            30.4 (2600) 89.1 and 55.4              61 (1000)   13.7 and 12.2
+bool stream_images(int64_t nnz, int64_t nparts, int32_t dtype) {
+    return nnz >= (dtype == AZI_F64 ? 20 : 14) * nparts;
 }
 
 // Places a stream encoding on the device; its coefficients are gathered from
@@ -796,6 +813,7 @@ int plan_upload_stream(azi_plan* p, bool* done, StreamJob* job = nullptr) {
         const int rc = upload_stream(job->sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
                                      p->colptr, p->cdata, b);
         if (rc != AZI_OK) return rc;
+        b.images = !p->m.two_d || stream_images(p->m.nnz(), b.nparts, p->dtype);
         p->stream = std::move(b);
     } catch (const std::bad_alloc&) {
         return fail(AZI_ENOMEM, "out of host memory building the stream encoding");
@@ -2102,7 +2120,7 @@ int azi_integrate1d(const azi_plan* p, const void* x, void* I, void* W, void* U,
         AZI_HIP(plan_launch_image(p, x, I, W, U, empty, s), "band forward kernels");
         return AZI_OK;
     }
-    if (p->layout == AZI_LAYOUT_PIXEL && p->stream.on) {
+    if (p->layout == AZI_LAYOUT_PIXEL && p->stream.on && p->stream.images) {
         AZI_HIP(plan_launch_image(p, x, I, W, U, empty, s), "map forward kernels");
         return AZI_OK;
     }
@@ -2158,7 +2176,7 @@ int azi_integrate1d_staged(const azi_plan* p, void* I, void* W, void* U, double 
                 "band forward kernels");
         return AZI_OK;
     }
-    if (p->layout == AZI_LAYOUT_PIXEL && p->stream.on) {
+    if (p->layout == AZI_LAYOUT_PIXEL && p->stream.on && p->stream.images) {
         AZI_HIP(plan_launch_image(p, p->xwork.p, I, W, U, empty, static_cast<hipStream_t>(stream)),
                 "map forward kernels");
         return AZI_OK;

@@ -79,7 +79,8 @@ def routes(over_fake_device):
     ((330, 330, 100, 36), "forward", "correct forward"),    # set up in a few us: no encoding
     ((999, 1000, 100, 12), "forward", "correct forward"),   # a row short of the line
     ((1000, 1000, 100, 12), "stream", "stream"),
+    ((1000, 1000, 320, 360), "forward", "stream"),          # 9 entries a partial sum
 ], ids=str)
-def test_maps_are_encoded_from_a_million_pixels(shape, image, raw, routes):
+def test_map_passes_by_size_and_entries_per_partial_sum(shape, image, raw, routes):
     r = subprocess.run([routes, *map(str, shape)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip() == f"image {image}, raw {raw}", r.stdout + r.stderr
