@@ -371,6 +371,26 @@ bool stream_tiling(const azi_tiling& t, int32_t layout, bool two_d) {
     return layout == AZI_LAYOUT_RUN && t.tile_nnz == 0 && t.band == 16 && t.grid == 0;
 }
 
+// Images of few rows: their tiles, 64 columns wide, hold a few rows' pixels
+// and leave most of a workgroup idle.  What counts is how many of them a launch
+// has: up to two rounds of the 2048 resident workgroups cost nothing, from
+// there on the run encoding is faster up to 8 rows.  us a frame, runs and
+// stream, float64 / float32:
+//   1 x 100000 (1563 tiles)  10.1 and 9.9   / 10.3 and 9.8
+//   2 x 200000 (3125)        11.1 and 12.4  / 10.8 and 12.2
+//   1 x 300000 (4688)        11.2 and 15.0  / 11.7 and 14.8
+//   4 x 500000 (7813)        18.0 and 20.1  / 14.0 and 18.9
+//   3 x 3000000 (46875)      38.3 and 88.8  / 32.2 and 81.2
+//   8 x 1250000 (19532)      41.2 and 46.7  / 32.8 and 40.6
+//   12 x 800000 (12500)      40.8 and 38.1  / 33.5 and 30.6
+// In a batch the tiles of all such images count, 16 tiles wide or wider: 64
+// of 1 x 16000 pixels 11.5 and 33.5 us, 300 of 4 x 1280 15.3 and 16.2; 6000
+// of 3 x 130, for which runs are cut per image, 52.8 and 32.6.
+constexpr int64_t kStreamFewRows = 12, kStreamFewRowsTiles = 4096;
+int64_t few_rows_tiles(int32_t h, int32_t w) {
+    return h < kStreamFewRows && w > 15 * 64 ? ((int64_t)w + 63) / 64 : 0;
+}
+
 azi::StreamLaunch stream_args(const StreamBufs& b, const void* img, int32_t img_dtype,
                               int64_t npix, void* I, void* W, void* U, double empty, int32_t dtype,
                               int32_t accum) {
@@ -759,7 +779,8 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
 // Whether a plan is to have the stream encoding, where that applies.
 bool plan_streams(const azi_plan* p) {
     return stream_tiling(p->tiling, p->layout, p->m.two_d) &&
-           (!p->m.two_d || p->m.npix >= kStreamMapPix);
+           (p->m.two_d ? p->m.npix >= kStreamMapPix
+                       : few_rows_tiles(p->geom.h, p->geom.w) <= kStreamFewRowsTiles);
 }
 
 // The stream encoding of a plan's matrix, built by a thread of its own from
@@ -2574,6 +2595,9 @@ namespace {
 int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& ms, bool* done) {
     *done = false;
     if (!stream_tiling(b->tiling, b->layout, false)) return AZI_OK;
+    int64_t few = 0;
+    for (const auto& s : b->hw) few += few_rows_tiles(s.first, s.second);
+    if (few > kStreamFewRowsTiles) return AZI_OK;
     azi::StreamMatrix sm;
     const int32_t px = stream_tile_px(b->npix);
     std::vector<int64_t> stream_off(b->n + 1, 0), chunk_off(b->n + 1, 0);

@@ -75,12 +75,47 @@ def routes(over_fake_device):
     return over_fake_device("routes_harness")
 
 
-@pytest.mark.parametrize("shape,image,raw", [
-    ((330, 330, 100, 36), "forward", "correct forward"),    # set up in a few us: no encoding
-    ((999, 1000, 100, 12), "forward", "correct forward"),   # a row short of the line
-    ((1000, 1000, 100, 12), "stream", "stream"),
-    ((1000, 1000, 320, 360), "forward", "stream"),          # 9 entries a partial sum
+def kernels(routes, h, w, npt, npt_azim=0, dtype=0, n=0):
+    r = subprocess.run([routes, *map(str, (h, w, npt, npt_azim, dtype, n))], capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout.strip()
+
+
+ROWS = "image forward, raw correct forward, backward backward"
+MAP = "image stream, raw stream, backward backward"
+
+
+@pytest.mark.parametrize("shape,passes", [
+    ((330, 330, 100, 36), ROWS),             # encoding it would take longer than building it
+    ((999, 1000, 100, 12), ROWS),            # a row short of the line
+    ((1000, 1000, 100, 12), MAP),
+    ((1000, 1000, 320, 360), "image forward, raw stream, backward backward"),
 ], ids=str)
-def test_map_passes_by_size_and_entries_per_partial_sum(shape, image, raw, routes):
-    r = subprocess.run([routes, *map(str, shape)], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0 and r.stdout.strip() == f"image {image}, raw {raw}", r.stdout + r.stderr
+def test_map_passes(shape, passes, routes):
+    assert kernels(routes, *shape) == passes
+
+
+STREAM = "image stream, raw stream, backward stream_adjoint"
+RUNS = "image band, raw band, backward backward"
+
+
+@pytest.mark.parametrize("shape,passes", [
+    ((1, 262144, 100), STREAM),              # 4096 tiles
+    ((1, 262145, 100), RUNS),                # one more
+    ((11, 262145, 100), RUNS),
+    ((12, 262145, 100), STREAM),             # tiles of 12 rows
+    ((300, 1, 40), STREAM),
+], ids=str)
+def test_passes_of_few_rows(shape, passes, routes):
+    assert kernels(routes, *shape) == passes
+
+
+@pytest.mark.parametrize("n,shape,passes", [
+    (64, (1, 4096, 60), "image stream, backward stream_adjoint"),  # 4096 tiles together
+    (65, (1, 4096, 60), "image band, backward backward"),
+    (1000, (3, 130, 20), "image stream, backward stream_adjoint"),  # not wide
+    (1000, (12, 1025, 20), "image stream, backward stream_adjoint"),
+], ids=str)
+def test_batch_passes_of_few_rows(n, shape, passes, routes):
+    assert kernels(routes, *shape, n=n) == passes
