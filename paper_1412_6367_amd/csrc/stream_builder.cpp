@@ -69,7 +69,9 @@ struct Builder {
 
     Builder(const HostMatrix& m, int32_t w, int64_t pix_off, int64_t bin_off)
         : m(m), w(w), pix_off(pix_off), bin_off(bin_off) {
-        lanes.assign((size_t)kStreamSlots + kStreamMaxCount, 0);
+        // as many as a window may have (at its largest 0.36 MB to clear, 13 us for
+        // every image of a batch)
+        lanes.assign((size_t)std::min(kStreamSlots, m.npt), 0);
         seen.assign(lanes.size() << 6, 0);
         if (m.two_d) widx.assign((size_t)m.npt_azim, -1);
     }
