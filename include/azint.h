@@ -406,10 +406,11 @@ int azi_plan_run_schedule(const azi_plan* plan, int32_t tile_nnz, int64_t* nruns
  * coefficients in the order they are read, every workgroup adding its tile's
  * products into bins kept in LDS.  The frame is read once, in order.  Plans
  * it does not serve keep the run encoding: under four pixels, more than 63
- * bins in one pixel, bins so fine that a tile would hold under 192 pixels on
- * average, more than 8 MiB of partial sums, over 4096 tiles of under 12 rows
- * (a batch: one instance of these, or its wide images of few rows together,
- * or positions past 2^31).  The per-run dark values of AZI_STAGE_FOLD are
+ * bins in one pixel, more than 4.8 (6 from 3e6 pixels) on average, bins so fine
+ * that a tile would hold under 192 pixels on average, more than 8 MiB of
+ * partial sums, over 4096 tiles of under 12 rows (a batch: one instance of
+ * these, or its average and its wide images of few rows together, or positions
+ * past 2^31).  The per-run dark values of AZI_STAGE_FOLD are
  * per-pixel ones there, in the same types.
  * Two-dimensional plans of 1e6 pixels or more in AZI_LAYOUT_PIXEL with their
  * default tiling are integrated from the stream encoding too (their tiles' bins

@@ -391,6 +391,24 @@ int64_t few_rows_tiles(int32_t h, int32_t w) {
     return h < kStreamFewRows && w > 15 * 64 ? ((int64_t)w + 63) / 64 : 0;
 }
 
+// Bins so fine that most pixels have more than the kernel keeps in registers:
+// the further ones are loaded one after the other.  A frame that comes from HBM
+// hides some of it.  us a frame, runs and stream, by entries per pixel:
+//                       float64                float32
+//   1000 x 1000  4.66  18.3 and 18.2          17.2 and 14.0
+//                5.58  20.1 and 22.4          18.7 and 17.5
+//                7.41  24.5 and 28.8          21.2 and 25.1
+//   1400 x 1400  4.66  29.2 and 26.4          22.5 and 19.2
+//                5.58  34.7 and 37.2          25.2 and 25.3
+//   2048 x 2048  5.58  66.4 and 54.5          39.9 and 35.4
+//                6.50  76.5 and 64.4          45.3 and 42.0
+//                7.41  88.6 and 93.4          49.9 and 61.0
+//   2500 x 2500  5.58  96.7 and 84.5          55.3 and 53.4
+//                6.50  103 and 103            58.5 and 79.6
+bool stream_fine(int64_t npix, int64_t nnz) {
+    return nnz * 10 > npix * (npix < 3000000 ? 48 : 60);
+}
+
 azi::StreamLaunch stream_args(const StreamBufs& b, const void* img, int32_t img_dtype,
                               int64_t npix, void* I, void* W, void* U, double empty, int32_t dtype,
                               int32_t accum) {
@@ -777,10 +795,11 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
 }
 
 // Whether a plan is to have the stream encoding, where that applies.
-bool plan_streams(const azi_plan* p) {
+bool plan_streams(const azi_plan* p, int64_t nnz) {
     return stream_tiling(p->tiling, p->layout, p->m.two_d) &&
            (p->m.two_d ? p->m.npix >= kStreamMapPix
-                       : few_rows_tiles(p->geom.h, p->geom.w) <= kStreamFewRowsTiles);
+                       : few_rows_tiles(p->geom.h, p->geom.w) <= kStreamFewRowsTiles &&
+                             !stream_fine(p->m.npix, nnz));
 }
 
 // The stream encoding of a plan's matrix, built by a thread of its own from
@@ -821,7 +840,7 @@ struct StreamJob {
 // encoding in use, this one or the layout's, goes once the new one is placed.
 int plan_upload_stream(azi_plan* p, bool* done, StreamJob* job = nullptr) {
     *done = false;
-    if (!plan_streams(p)) return AZI_OK;
+    if (!plan_streams(p, p->m.nnz())) return AZI_OK;
     try {
         StreamJob own;
         if (!job) job = &own;
@@ -1623,7 +1642,7 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     // maps: the positions come to the host first, and are encoded there while
     // the rest of the matrix is ordered and copied
     StreamJob job;
-    const bool streams = two_d && plan_streams(p);
+    const bool streams = two_d && plan_streams(p, nnz);
     if (streams) {
         int rc = download(m.colptr, p->colptr.p, npix + 1, s);
         if (rc == AZI_OK) rc = download(m.rowidx, p->rowidx.p, nnz, s);
@@ -1959,7 +1978,7 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
         const int64_t nnz_alloc = round_up(nnz, kPad) + kPad;
         const size_t es = elem_size(p->dtype);
         StreamJob job;  // beside the copies below
-        if (p->m.two_d && plan_streams(p)) job.start(p);
+        if (p->m.two_d && plan_streams(p, nnz)) job.start(p);
         try {
             std::vector<int32_t> idx((size_t)nnz_alloc, 0);
             const double* coef = p->m.data.data();
@@ -2597,7 +2616,7 @@ int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& 
     if (!stream_tiling(b->tiling, b->layout, false)) return AZI_OK;
     int64_t few = 0;
     for (const auto& s : b->hw) few += few_rows_tiles(s.first, s.second);
-    if (few > kStreamFewRowsTiles) return AZI_OK;
+    if (few > kStreamFewRowsTiles || stream_fine(b->npix, b->nnz)) return AZI_OK;
     azi::StreamMatrix sm;
     const int32_t px = stream_tile_px(b->npix);
     std::vector<int64_t> stream_off(b->n + 1, 0), chunk_off(b->n + 1, 0);

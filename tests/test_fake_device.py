@@ -106,8 +106,12 @@ RUNS = "image band, raw band, backward backward"
     ((11, 262145, 100), RUNS),
     ((12, 262145, 100), STREAM),             # tiles of 12 rows
     ((300, 1, 40), STREAM),
+    ((300, 300, 600), STREAM),               # 4.7 entries a pixel
+    ((300, 300, 640), RUNS),                 # 4.9
+    ((1740, 1740, 4350), STREAM),            # 5.6, three million pixels
+    ((1740, 1740, 4900), RUNS),              # 6.2
 ], ids=str)
-def test_passes_of_few_rows(shape, passes, routes):
+def test_passes_of_few_rows_and_of_fine_bins(shape, passes, routes):
     assert kernels(routes, *shape) == passes
 
 
@@ -116,6 +120,8 @@ def test_passes_of_few_rows(shape, passes, routes):
     (65, (1, 4096, 60), "image band, backward backward"),
     (1000, (3, 130, 20), "image stream, backward stream_adjoint"),  # not wide
     (1000, (12, 1025, 20), "image stream, backward stream_adjoint"),
+    (40, (60, 60, 120), "image stream, backward stream_adjoint"),
+    (40, (60, 60, 130), "image band, backward backward"),
 ], ids=str)
-def test_batch_passes_of_few_rows(n, shape, passes, routes):
+def test_batch_passes_of_few_rows_and_of_fine_bins(n, shape, passes, routes):
     assert kernels(routes, *shape, n=n) == passes

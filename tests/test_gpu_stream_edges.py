@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle
-from tests.helpers import azint, norm_err
+from tests.helpers import azint, norm_err, oracle_matrix
 from tests.test_gpu_2d import oracle2d
 from tests.test_gpu_forward import TOL32_F64, TOL64, check
 
@@ -48,6 +48,37 @@ def test_gradient_towards_raw_of_masked_pixels(dtype, dev):
     assert torch.equal(a[keep], b[keep])
     assert torch.equal(torch.signbit(a[keep]), torch.signbit(b[keep]))
     assert bool(torch.isnan(a).any())
+
+
+# Bins as fine as the encoding takes them: most pixels have more than the kernels
+# keep in registers
+@pytest.mark.parametrize("h,w,npt,dtype,accum", [
+    (141, 150, 290, torch.float64, "f64"), (141, 150, 290, torch.float32, "f64"),
+    (141, 150, 290, torch.float32, "kahan32"),
+    (1740, 1750, 4300, torch.float64, "f64"), (1740, 1750, 4300, torch.float32, "f64")], ids=str)
+def test_fine_bins(h, w, npt, dtype, accum, dev):
+    say("fine bins", h, w, npt, dtype, accum)
+    az = azint()
+    npd = np.float64 if dtype == torch.float64 else np.float32
+    m = oracle_matrix(h, w, h / 2, w / 2, npt)
+    kw = dict(dtype=dtype, accum=accum, device=dev)
+    plan, entries = az.Plan(h, w, npt, **kw), az.Plan(h, w, npt, layout="pixel", **kw)
+    gen = np.random.default_rng(h)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    x = gen.uniform(0, 1000, h * w).astype(npd)
+    tol = TOL64 if dtype == torch.float64 else TOL32_F64
+    out = plan.integrate(t(x))
+    check(out, m, x.astype(np.float64), tol, what="image")
+    raw, flat = gen.integers(60, 1 << 20, h * w).astype(np.int32), gen.uniform(0.9, 1.1, h * w)
+    flat, dark = flat.astype(npd), gen.integers(0, 60, h * w).astype(npd)
+    plan.set_corrections(dark=t(dark), flat=t(flat))
+    check(plan.integrate_raw(t(raw)), m,
+          oracle.correct(raw, dark.astype(np.float64), flat.astype(np.float64), None, None), tol,
+          what="raw")
+    g = [t(gen.standard_normal(npt).astype(npd)) for _ in range(2)]
+    a, b = plan.backward(out[2], *g), entries.backward(out[2], *g)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
 
 
 # Maps of a million pixels or more, which are encoded: h, w, center_y, center_x,
