@@ -414,8 +414,11 @@ int azi_plan_run_schedule(const azi_plan* plan, int32_t tile_nnz, int64_t* nruns
  * per-pixel ones there, in the same types.
  * Two-dimensional plans of 1e6 pixels or more in AZI_LAYOUT_PIXEL with their
  * default tiling are integrated from the stream encoding too (their tiles' bins
- * are radial bins of a few wedges), unless a partial sum would stand for under
- * four nonzeros; smaller ones would take longer to encode than to build.
+ * are radial bins of a few wedges); smaller ones would take longer to encode
+ * than to build.  Not where its partial sums and the further wedges of its
+ * pixels outweigh the entries (under 2.6 entries each; images that are
+ * corrected already: 7 in float64, 4.6 in float32), nor with more than four
+ * bins a pixel on average below 2e6 pixels.
  * Raw frames are then integrated in one pass: A_bp / norm, rounded once when
  * the corrections are set, times raw - dark (as many roundings as A_bp times
  * (raw - dark) / norm), and the work image is not written.  azi_plan_stage and

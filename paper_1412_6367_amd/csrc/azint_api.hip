@@ -322,7 +322,7 @@ struct StreamBufs {
     int32_t ntiles = 0, nblanks = 0, nchunks = 0, slots = 4, ents_most = 0;
     int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
     bool over = true, cached = false, on = false;
-    bool images = true;       // images too, not raw frames alone (maps: stream_images)
+    bool images = true;       // images too, not raw frames alone (maps: map_gains)
     void release() {
         built.release();
         work.release();
@@ -474,20 +474,27 @@ bool stream_cached(const azi::StreamMatrix& sm, int32_t dtype) {
     return bytes <= ((int64_t)(dtype == AZI_F64 ? 64 : 160) << 20);
 }
 
-// Whether images that are corrected already take a map's encoding too.  The row
-// kernel reads such an image as it is, and its time follows the entries; the
-// stream kernel's follows the partial sums as well, which many wedges over
-// few pixels multiply (a raw frame always gains: the row kernel takes a
-// correction pass before it).  us an image, rows and stream, by entries per
-// partial sum (n x n pixels, one plan):
-//   float64  9.4 (1000)  14.9 and 19.1     float32  9.4 (1000)  11.9 and 16.7
-//            13.6 (1800) 27.4 and 31.0              13.6 (1800) 22.2 and 24.0
-//            17.0 (2300) 35.8 and 40.5              15.4 (2048) 31.1 and 27.7
-//            19.0 (2600) 42.7 and 46.2              19.0 (2600) 40.1 and 34.9
-//            22.9 (1800) 37.3 and 33.9              30.4 (2600) 70.4 and 40.4
-//            30.4 (2600) 89.1 and 55.4              61 (1000)   13.7 and 12.2
-bool stream_images(int64_t nnz, int64_t nparts, int32_t dtype) {
-    return nnz >= (dtype == AZI_F64 ? 20 : 14) * nparts;
+// What a map's tiles cost beside its entries: the partial sums, and the
+// scattered items, each a pixel gathered by itself.  Many wedges over few pixels
+// multiply both, while the row kernel's time follows the entries.  Entries per
+// partial sum or item from which a frame gains by the encoding, for raw frames,
+// before which the row kernel takes a correction pass, and for images, which it
+// reads as they are.  us a frame, stream and rows (n x n pixels, one plan):
+//                   raw float64    raw float32    image float64  image float32
+//   2.06 (n 1000)   26.6 and 23.9  23.5 and 23.5  24.8 and 16.1  21.1 and 13.4
+//   2.50 (n 1400)   35.5 and 31.5  30.7 and 26.6  32.5 and 20.7  26.3 and 18.7
+//   2.62 (n 1000)   19.6 and 22.7  17.3 and 20.9  18.2 and 12.6  15.4 and 12.3
+//   2.96 (n 1000)   20.7 and 22.9  18.5 and 22.5  19.1 and 14.9  16.7 and 11.9
+//   4.29 (n 1800)   33.8 and 42.5  28.8 and 34.1  31.0 and 27.4  24.0 and 22.2
+//   4.86 (n 2048)   37.3 and 52.8  31.8 and 44.0  35.5 and 32.5  27.7 and 31.1
+//   6.02 (n 2600)   49.4 and 93.0  41.5 and 61.0  46.2 and 42.7  34.9 and 40.1
+//   7.20 (n 3162)   64.4 and 129   52.8 and 109   60.5 and 65.8  43.9 and 54.8
+//   9.97 (n 1800)   36.0 and 52.6  29.8 and 50.1  33.9 and 37.3  25.5 and 38.6
+// Bins of over four entries a pixel cost both kernels' smaller frames more
+// (4.31, n 1000: raw 35.5 and 30.5, 31.2 and 32.7; 4.26, n 2048: 62.0 and 114).
+bool map_fine(int64_t npix, int64_t nnz) { return nnz > 4 * npix && npix < 2000000; }
+bool map_gains(int64_t nnz, int64_t side, bool images, int32_t dtype) {
+    return nnz * 10 >= side * (!images ? 26 : dtype == AZI_F64 ? 70 : 46);
 }
 
 // Places a stream encoding on the device; its coefficients are gathered from
@@ -797,7 +804,7 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
 // Whether a plan is to have the stream encoding, where that applies.
 bool plan_streams(const azi_plan* p, int64_t nnz) {
     return stream_tiling(p->tiling, p->layout, p->m.two_d) &&
-           (p->m.two_d ? p->m.npix >= kStreamMapPix
+           (p->m.two_d ? p->m.npix >= kStreamMapPix && !map_fine(p->m.npix, nnz)
                        : few_rows_tiles(p->geom.h, p->geom.w) <= kStreamFewRowsTiles &&
                              !stream_fine(p->m.npix, nnz));
 }
@@ -847,13 +854,15 @@ int plan_upload_stream(azi_plan* p, bool* done, StreamJob* job = nullptr) {
         if (job->started) job->wait();
         else job->build(p);
         if (job->memory) throw std::bad_alloc();
-        if (!job->built || (!p->m.two_d && (size_t)job->sm.nparts * 8 > kScratchBytes))
+        const int64_t side = job->sm.nparts + (int64_t)job->sm.xsrc.size();
+        if (!job->built || (p->m.two_d ? !map_gains(p->m.nnz(), side, false, p->dtype)
+                                       : (size_t)job->sm.nparts * 8 > kScratchBytes))
             return AZI_OK;
         StreamBufs b;
         const int rc = upload_stream(job->sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
                                      p->colptr, p->cdata, b);
         if (rc != AZI_OK) return rc;
-        b.images = !p->m.two_d || stream_images(p->m.nnz(), b.nparts, p->dtype);
+        b.images = !p->m.two_d || map_gains(p->m.nnz(), side, true, p->dtype);
         p->stream = std::move(b);
     } catch (const std::bad_alloc&) {
         return fail(AZI_ENOMEM, "out of host memory building the stream encoding");

@@ -91,6 +91,9 @@ MAP = "image stream, raw stream, backward backward"
     ((999, 1000, 100, 12), ROWS),            # a row short of the line
     ((1000, 1000, 100, 12), MAP),
     ((1000, 1000, 320, 360), "image forward, raw stream, backward backward"),
+    ((1000, 1000, 300, 720), ROWS),          # 2.1 entries per partial sum or item
+    ((1000, 1000, 1750, 36), ROWS),          # 4.3 entries a pixel
+    ((1450, 1450, 2500, 36), MAP),           # 4.2, two million pixels
 ], ids=str)
 def test_map_passes(shape, passes, routes):
     assert kernels(routes, *shape) == passes
