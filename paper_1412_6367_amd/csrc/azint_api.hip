@@ -321,7 +321,7 @@ struct StreamBufs {
     void* coef = nullptr;     // storage type
     int32_t ntiles = 0, nblanks = 0, nchunks = 0, slots = 4, ents_most = 0;
     int64_t ncoef = 0, nparts = 0, ents_per_chunk = 0;
-    bool over = true, cached = false, on = false;
+    bool over = true, cached = false, adj_cached = false, on = false;
     bool images = true;       // images too, not raw frames alone (maps: map_gains)
     void release() {
         built.release();
@@ -468,10 +468,17 @@ azi::StreamCoefLaunch stream_coef_args(const StreamBufs& b, const DevBuf& colptr
 //            4500 (500 MB) 99.4 / 126 and 110 / 144
 // and with three plans in turn: float32 46 MB 18.3 and 16.7, 86 MB 29.9 and
 // 30.0; float64 82 MB 29.0 and 29.4, 246 MB 53.0 and 57.6.  Doubles gain less,
-// their loads being whole lines more often, and lose sooner.
-bool stream_cached(const azi::StreamMatrix& sm, int32_t dtype) {
+// their loads being whole lines more often, and lose sooner.  The adjoint, whose
+// other traffic is its gradient alone, gains more, as k_csc_bwd did: float64
+// of n x n pixels, streamed, cached and k_csc_bwd, one plan / three in turn:
+//   2048, 99 MB   28.5, 22.4, 25.7 / 28.5, 29.0, 33.5
+//   2500, 147 MB  44.1, 33.3, 34.7 / 44.6, 49.0, 47.6
+//   2800, 184 MB  50.1, 41.2, 51.7 / 50.3, 52.8, 57.5
+// A batch is one matrix, used again at every pass: 3000 float64 images of 40 x
+// 40 (111 MB) 60.4 and 43.7 forward (runs 49.5), 53.6 and 35.7 adjoint.
+bool stream_cached(const azi::StreamMatrix& sm, int32_t dtype, bool again) {
     const int64_t bytes = (int64_t)sm.words.size() * 2 + sm.ncoef * (int64_t)elem_size(dtype);
-    return bytes <= ((int64_t)(dtype == AZI_F64 ? 64 : 160) << 20);
+    return bytes <= ((int64_t)(dtype == AZI_F64 && !again ? 64 : 160) << 20);
 }
 
 // What a map's tiles cost beside its entries: the partial sums, and the
@@ -501,7 +508,7 @@ bool map_gains(int64_t nnz, int64_t side, bool images, int32_t dtype) {
 // the pixel-major entries there (colptr, cdata), and the U of its npt bins,
 // which no frame changes, is summed once from them (the kernels over the unit
 // image, the same order as W).
-int upload_stream(const azi::StreamMatrix& sm, bool two_d, int64_t npt, int32_t dtype,
+int upload_stream(const azi::StreamMatrix& sm, bool two_d, bool batch, int64_t npt, int32_t dtype,
                   int32_t accum, int device, const DevBuf& colptr, const DevBuf& cdata,
                   StreamBufs& b) {
     b.release();
@@ -559,7 +566,8 @@ int upload_stream(const azi::StreamMatrix& sm, bool two_d, int64_t npt, int32_t 
     b.slots = 2;
     while (b.slots < 4 && sm.over[b.slots] * 1024 > sm.over[0]) ++b.slots;
     b.over = sm.over[b.slots] > 0;
-    b.cached = stream_cached(sm, dtype);
+    b.cached = stream_cached(sm, dtype, batch);
+    b.adj_cached = stream_cached(sm, dtype, true);
     b.ncoef = sm.ncoef;
     b.nparts = sm.nparts;
     b.ents_most = 0;
@@ -590,7 +598,7 @@ azi::StreamAdjointLaunch stream_adjoint_args(const StreamBufs& b, const void* U,
     a.coef = b.coef;
     a.slots = b.slots;
     a.over = b.over;
-    a.cached = b.cached;
+    a.cached = b.adj_cached;
     a.U = U;
     a.gI = gI;
     a.gW = gW;
@@ -859,8 +867,8 @@ int plan_upload_stream(azi_plan* p, bool* done, StreamJob* job = nullptr) {
                                        : (size_t)job->sm.nparts * 8 > kScratchBytes))
             return AZI_OK;
         StreamBufs b;
-        const int rc = upload_stream(job->sm, p->m.two_d, p->m.npt, p->dtype, p->accum, p->device,
-                                     p->colptr, p->cdata, b);
+        const int rc = upload_stream(job->sm, p->m.two_d, false, p->m.npt, p->dtype, p->accum,
+                                     p->device, p->colptr, p->cdata, b);
         if (rc != AZI_OK) return rc;
         b.images = !p->m.two_d || map_gains(p->m.nnz(), side, true, p->dtype);
         p->stream = std::move(b);
@@ -2637,7 +2645,7 @@ int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& 
         chunk_off[k + 1] = (int64_t)sm.chunks.size();
     }
     StreamBufs sb;
-    const int rc = upload_stream(sm, false, b->npt, b->dtype, b->accum, b->device, b->colptr,
+    const int rc = upload_stream(sm, false, true, b->npt, b->dtype, b->accum, b->device, b->colptr,
                                  b->cdata, sb);
     if (rc != AZI_OK) return rc;
     b->stream = std::move(sb);

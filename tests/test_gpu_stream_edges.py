@@ -200,3 +200,43 @@ def test_encoded_map_keeps_special_values_in_their_bins(dev):
         W = W.cpu().numpy()
         assert np.all(~np.isfinite(W[hit]))
         assert np.array_equal(W[~hit], ref[~hit])
+
+
+@pytest.mark.parametrize("n", [2500, 2800])
+def test_adjoint_around_its_cache_rule(n, dev):
+    """float64 matrices of 147 and 184 MB, the adjoint's words and coefficients
+    through the caches and past them: the bits of the entries' adjoint."""
+    say("adjoint caches", n)
+    az = azint()
+    plan = az.Plan.on_device(n, n, n, device=dev)
+    gen = torch.Generator(device=dev).manual_seed(n)
+    x = torch.rand(n * n, generator=gen, device=dev, dtype=torch.float64)
+    g = torch.randn(n, generator=gen, device=dev, dtype=torch.float64)
+    U = plan.integrate(x)[2]
+    want = plan.backward(U, g, g)
+    plan.set_layout("run")
+    plan.set_tiling(tile_nnz=0, band=16, grid=0)
+    for _ in range(2):
+        got = plan.backward(U, g, g)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("k", [40, 70, 130])
+def test_batch_around_its_cache_rule(k, dev):
+    """float64 batches of 57, 99 and 184 MB: one launch, the loop and the
+    entries' adjoint agree bit for bit."""
+    say("batch caches", k)
+    az = azint()
+    one = az.Plan(250, 250, 250)
+    batch = az.Batch([one] * k, device=dev)
+    gen = torch.Generator(device=dev).manual_seed(k)
+    x = torch.rand(batch.npix, generator=gen, device=dev, dtype=torch.float64)
+    g = torch.randn(batch.npt, generator=gen, device=dev, dtype=torch.float64)
+    out, loop = batch.forward(x), batch.forward(x, loop=True)
+    gx = batch.backward(out[2], g, g)
+    torch.cuda.synchronize()
+    for a, b in zip(out, loop):
+        assert torch.equal(a, b)
+    batch.set_tiling(tile_nnz=1024)
+    assert torch.equal(batch.backward(out[2], g, g), gx)
