@@ -2634,12 +2634,16 @@ int batch_build_stream(azi_batch* b, const std::vector<const azi::HostMatrix*>& 
     int64_t few = 0;
     for (const auto& s : b->hw) few += few_rows_tiles(s.first, s.second);
     if (few > kStreamFewRowsTiles || stream_fine(b->npix, b->nnz)) return AZI_OK;
+    // one instance that is refused sends the batch back: what can be seen of that
+    // is looked at before any is encoded
+    for (int32_t k = 0; k < b->n; ++k)
+        if (b->two_d[k] || b->pix_off[k + 1] - b->pix_off[k] < 4) return AZI_OK;
     azi::StreamMatrix sm;
     const int32_t px = stream_tile_px(b->npix);
     std::vector<int64_t> stream_off(b->n + 1, 0), chunk_off(b->n + 1, 0);
     for (int32_t k = 0; k < b->n; ++k) {
-        if (b->two_d[k] || !azi::build_stream(*ms[k], b->hw[k].first, b->hw[k].second, px,
-                                              b->pix_off[k], b->bin_off[k], sm))
+        if (!azi::build_stream(*ms[k], b->hw[k].first, b->hw[k].second, px, b->pix_off[k],
+                               b->bin_off[k], sm))
             return AZI_OK;
         stream_off[k + 1] = (int64_t)sm.tiles.size();
         chunk_off[k + 1] = (int64_t)sm.chunks.size();

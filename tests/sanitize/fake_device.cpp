@@ -13,6 +13,7 @@ azi::StreamLaunch stream;
 azi::BandLaunch band;
 const void *dark = nullptr, *norm = nullptr;
 int64_t fail_in = -1, live = 0;
+int encoded = 0;
 static std::map<void*, size_t> sizes;
 bool held(const void* p) {
     auto i = sizes.upper_bound(const_cast<void*>(p));
@@ -26,7 +27,17 @@ static hipError_t note(const char* name) {
 }
 }  // namespace fake
 
+// azi::build_stream, linked with --wrap
 extern "C" {
+bool __real__ZN3azi12build_streamERKNS_10HostMatrixEiiillRNS_12StreamMatrixE(
+    const azi::HostMatrix&, int32_t, int32_t, int32_t, int64_t, int64_t, azi::StreamMatrix&);
+bool __wrap__ZN3azi12build_streamERKNS_10HostMatrixEiiillRNS_12StreamMatrixE(
+    const azi::HostMatrix& m, int32_t h, int32_t w, int32_t px, int64_t pix, int64_t bin,
+    azi::StreamMatrix& sm) {
+    ++fake::encoded;
+    return __real__ZN3azi12build_streamERKNS_10HostMatrixEiiillRNS_12StreamMatrixE(m, h, w, px, pix,
+                                                                                  bin, sm);
+}
 hipError_t hipMalloc(void** p, size_t n) {
     if (fake::fail_in >= 0 && fake::fail_in-- == 0) return hipErrorOutOfMemory;
     *p = std::calloc(1, n);

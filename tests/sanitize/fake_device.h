@@ -17,6 +17,7 @@ extern azi::StreamLaunch stream;        // arguments of the last launch_stream
 extern azi::BandLaunch band;            // arguments of the last launch_band
 extern const void *dark, *norm;         // arrays of the last launch_correct
 extern int64_t fail_in;                 // allocations until one fails (negative: none does)
+extern int encoded;                     // images given to build_stream
 extern int64_t live;                    // bytes allocated
 bool held(const void* p);               // p lies in an allocation
 inline bool called(const char* name) {

@@ -11,6 +11,7 @@ from tests.helpers import ROOT
 
 CSRC = os.path.join(ROOT, "paper_1412_6367_amd", "csrc")
 SANITIZE = os.path.join(ROOT, "tests", "sanitize")
+BUILD = "_ZN3azi12build_streamERKNS_10HostMatrixEiiillRNS_12StreamMatrixE"
 
 
 @pytest.fixture(scope="module")
@@ -36,7 +37,7 @@ def over_fake_device(tmp_path_factory):
 
     def link(harness):
         exe = str(tmp / harness)
-        r = subprocess.run(["g++", "-fsanitize=address", "-pthread", *objects,
+        r = subprocess.run(["g++", "-fsanitize=address", "-pthread", f"-Wl,--wrap={BUILD}", *objects,
                             compile_one(os.path.join(SANITIZE, harness + ".cpp")), "-o", exe],
                            capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
@@ -128,3 +129,14 @@ def test_passes_of_few_rows_and_of_fine_bins(shape, passes, routes):
 ], ids=str)
 def test_batch_passes_of_few_rows_and_of_fine_bins(n, shape, passes, routes):
     assert kernels(routes, *shape, n=n) == passes
+
+
+@pytest.mark.parametrize("last,said", [
+    ((20, 30, 0), "image stream, 50 encoded"),
+    ((1, 3, 0), "image band, 0 encoded"),
+    ((20, 30, 6), "image band, 0 encoded"),
+], ids=str)
+def test_a_refused_instance_is_seen_before_the_others_are_encoded(last, said, over_fake_device):
+    r = subprocess.run([over_fake_device("mixed_batch_harness"), "50", *map(str, last)],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip() == said, r.stdout + r.stderr
