@@ -443,7 +443,10 @@ int azi_plan_get_layout(const azi_plan* plan, int32_t* layout);
  * Errors: AZI_EDEVICE (no such device / HIP failure), AZI_ENOMEM. */
 int azi_plan_upload(azi_plan* plan, int32_t device);
 
-/* Device memory held by the plan, in bytes (0 before upload). */
+/* Device memory held by the plan, in bytes (0 before upload).  An encoded
+ * two-dimensional plan holds its CSR beside the encoding (a copy of the
+ * coefficients each), with a norm the folded coefficients as well, and in
+ * float32 the coefficients as doubles, from which they are folded. */
 int64_t azi_plan_device_bytes(const azi_plan* plan);
 
 /*

@@ -624,6 +624,7 @@ struct azi_plan {
         fbin_ptr, fparts, corr, cfirst, rgbase, fcoef, ufix, wdark;
     int32_t nstiles = 0, nbtiles = 0, npieces = 0, band_rows = 8, nftiles = 0;
     StreamBufs stream;    // run layout, library-sized tilings: replaces the run encoding
+    DevBuf exact;         // encoded float32 maps: the double coefficients, for every fold
     DevBuf slab, slab2;   // a device-built plan's arrays, until it is uploaded again
     bool folded = false;  // run layout, AZI_STAGE_FOLD(_SUM), corrections set
     int32_t max_count = INT32_MAX;  // largest number of band partials of a bin
@@ -1147,14 +1148,24 @@ int plan_fold_stream(azi_plan* p, hipStream_t s) {
     // roundings as A_bp times (raw - dark) / norm
     const bool divide = p->m.two_d;
     if (p->has_norm) {
-        DevBuf exact;  // float32 plans: the double coefficients
+        // float32 plans: the double coefficients, brought for the fold, kept by
+        // maps (whose corrections cost 0.2 ms before they were folded, and
+        // 5.6 with the copy of 3162 x 3162 pixels' in every call)
+        DevBuf own;
+        DevBuf& exact = p->m.two_d ? p->exact : own;
         AZI_HIP(p->fcoef.alloc((size_t)(b.ncoef + kPad) * elem_size(p->dtype), p->device),
                 "folded coefficients");
         azi::StreamCoefLaunch c =
             stream_coef_args(b, p->colptr, p->cdata.p, p->fcoef.p, p->dtype);
         if (p->dtype != AZI_F64) {
-            AZI_HIP(exact.upload(p->m.cdata.data(), p->m.cdata.size() * 8, p->device),
-                    "exact coefficients");
+            if (!exact.p) {
+                const hipError_t e =
+                    exact.upload(p->m.cdata.data(), p->m.cdata.size() * 8, p->device);
+                if (e != hipSuccess) {
+                    exact.release();
+                    return hip_fail(e, "exact coefficients");
+                }
+            }
             c.src = exact.p;
             c.src_f64 = true;
         }
@@ -1636,7 +1647,9 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     kept.add(p->vwork, (size_t)(m.npt + kAdjPad) * 8);
     AZI_HIP(kept.place(p->slab, device), "matrix");
     DevBuf temp2, cdata64, pix, work, skeys, perm, data64, keys;
-    if (!f64) work_parts.add(cdata64, n1 * 8);
+    const bool streams = two_d && plan_streams(p, nnz);
+    if (!f64 && streams) AZI_HIP(p->exact.alloc(n1 * 8, device), "exact coefficients");
+    else if (!f64) work_parts.add(cdata64, n1 * 8);
     if (!f64) work_parts.add(data64, n1 * 8);
     work_parts.add(pix, n1 * 4);
     work_parts.add(work, azi::sort_work_bytes(nnz));
@@ -1645,7 +1658,8 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     if (!two_d) work_parts.add(keys, n1 * 4);
     AZI_HIP(work_parts.place(temp2, device), "sort work");
     // float64 plans: the doubles are the storage copy
-    double* c64 = f64 ? p->cdata.as<double>() : cdata64.as<double>();
+    double* c64 = f64 ? p->cdata.as<double>()
+                      : (streams ? p->exact : cdata64).as<double>();
     AZI_HIP(azi::launch_fill(g, p->unit, p->split, lo.as<double>(), hi.as<double>(), m.pmin, delta,
                              npt, nazim, p->colptr.as<int32_t>(), p->rowidx.as<int32_t>(), c64,
                              pix.as<int32_t>(), s), "fill");
@@ -1659,7 +1673,6 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     // maps: the positions come to the host first, and are encoded there while
     // the rest of the matrix is ordered and copied
     StreamJob job;
-    const bool streams = two_d && plan_streams(p, nnz);
     if (streams) {
         int rc = download(m.colptr, p->colptr.p, npix + 1, s);
         if (rc == AZI_OK) rc = download(m.rowidx, p->rowidx.p, nnz, s);
@@ -1711,6 +1724,7 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
             bool streamed = false;
             const int rc = plan_upload_stream(p, &streamed, &job);
             if (rc != AZI_OK) return rc;
+            if (!streamed) p->exact.release();
         }
         return plan_device_schedules(p, nnz, !two_d);
     } catch (const std::bad_alloc&) {
@@ -1846,7 +1860,10 @@ int azi_plan_set_tiling(azi_plan* p, const azi_tiling* t) {
                 bool streamed = false;
                 const int rc = p->layout == AZI_LAYOUT_PIXEL ? plan_upload_stream(p, &streamed)
                                                              : AZI_OK;
-                if (rc == AZI_OK && !streamed) p->stream.release();
+                if (rc == AZI_OK && !streamed) {
+                    p->stream.release();
+                    p->exact.release();
+                }
                 return rc;
             });
             if (rce != AZI_OK) {  // the encoding in use stays, with its tiling
@@ -1990,6 +2007,7 @@ int azi_plan_upload(azi_plan* p, int32_t device) {
         if (b->view) b->release();
     p->slab.release();
     p->slab2.release();
+    p->exact.release();
     auto body = [&]() -> int {
         const int64_t nnz = p->m.nnz();
         const int64_t nnz_alloc = round_up(nnz, kPad) + kPad;
@@ -2083,7 +2101,7 @@ int32_t azi_plan_correction_bytes(const azi_plan* p) {
 int64_t azi_plan_device_bytes(const azi_plan* p) {
     if (!p) return 0;
     const DevBuf* bufs[] = {&p->ftiles, &p->fslots, &p->fbin_ptr, &p->fparts, &p->corr, &p->cfirst,
-                            &p->fcoef, &p->ufix, &p->wdark,
+                            &p->fcoef, &p->ufix, &p->wdark, &p->exact,
                             &p->rowptr, &p->indices, &p->data, &p->colptr, &p->rowidx,
                             &p->cdata, &p->tiles, &p->splits, &p->parts, &p->dark,
                             &p->norm, &p->xwork, &p->vwork, &p->order, &p->dark_r,

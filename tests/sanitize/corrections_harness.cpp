@@ -60,6 +60,12 @@ int main(int argc, char** argv) {
             wrong = true;
         }
     }
+    fake::uploaded = 0;
+    if (azi_plan_set_corrections(p, image, image, nullptr, nullptr, nullptr) != AZI_OK) return 2;
+    if (two_d && fake::uploaded > 0) {
+        std::printf("%lld bytes of the matrix copied again\n", (long long)fake::uploaded);
+        wrong = true;
+    }
     azi_plan_destroy(p);
     std::free(image);
     if (fake::live != 0) {

@@ -12,7 +12,7 @@ std::vector<std::string> calls;
 azi::StreamLaunch stream;
 azi::BandLaunch band;
 const void *dark = nullptr, *norm = nullptr;
-int64_t fail_in = -1, live = 0;
+int64_t fail_in = -1, live = 0, uploaded = 0;
 int encoded = 0;
 static std::map<void*, size_t> sizes;
 bool held(const void* p) {
@@ -51,7 +51,8 @@ hipError_t hipFree(void* p) {
     std::free(p);
     return hipSuccess;
 }
-hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) {
+    if (k == hipMemcpyHostToDevice) fake::uploaded += (int64_t)n;
     std::memcpy(d, s, n);
     return hipSuccess;
 }

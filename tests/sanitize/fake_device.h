@@ -18,6 +18,7 @@ extern azi::BandLaunch band;            // arguments of the last launch_band
 extern const void *dark, *norm;         // arrays of the last launch_correct
 extern int64_t fail_in;                 // allocations until one fails (negative: none does)
 extern int encoded;                     // images given to build_stream
+extern int64_t uploaded;                // bytes copied from the host
 extern int64_t live;                    // bytes allocated
 bool held(const void* p);               // p lies in an allocation
 inline bool called(const char* name) {

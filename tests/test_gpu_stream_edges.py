@@ -240,3 +240,27 @@ def test_batch_around_its_cache_rule(k, dev):
         assert torch.equal(a, b)
     batch.set_tiling(tile_nnz=1024)
     assert torch.equal(batch.backward(out[2], g, g), gx)
+
+
+def test_float32_map_folds_from_the_same_doubles(dev):
+    """Kept from the build on the device, or copied from the host matrix: the
+    same folded coefficients, through several changes of corrections."""
+    say("float32 fold")
+    g = MAPS[0]
+    plan = map_plan(g, torch.float32, "f64", dev, on_device=True)
+    gen = torch.Generator(device=dev).manual_seed(9)
+    n = g[0] * g[1]
+    raw = torch.randint(0, 1 << 20, (n,), generator=gen, device=dev, dtype=torch.int32)
+    flats = [0.9 + 0.2 * torch.rand(n, generator=gen, device=dev) for _ in range(2)]
+    kept = []
+    for flat in flats:
+        plan.set_corrections(flat=flat)
+        kept.append(plan.integrate_raw(raw))
+    plan.set_tiling(variant=0)  # out of the encoding, and back
+    plan.set_tiling(variant=1)
+    for flat, want in list(zip(flats, kept))[::-1]:
+        plan.set_corrections(flat=flat)
+        got = plan.integrate_raw(raw)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
