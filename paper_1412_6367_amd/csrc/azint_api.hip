@@ -81,10 +81,16 @@ struct DevBuf {
         bytes = 0;
         view = false;
     }
+    // A view that is large enough is used again: its memory is there until
+    // the whole allocation goes.
     hipError_t alloc(size_t n, int dev) {
+        if (n == 0) n = 256;
+        if (view && dev == device && n <= bytes) {
+            bytes = n;
+            return hipSuccess;
+        }
         release();
         device = dev;
-        if (n == 0) n = 256;
         hipError_t e = hipMalloc(&p, n);
         if (e != hipSuccess) {
             p = nullptr;
@@ -2109,8 +2115,9 @@ int64_t azi_plan_device_bytes(const azi_plan* p) {
                             &p->btiles, &p->brows, &p->blp, &p->bcoef, &p->bin_ptr,
                             &p->bparts, &p->npieces_buf, &p->npacked, &p->ncoef, &p->bin_slot,
                             &p->bin_count, &p->nparts_buf};
-    int64_t s = p->stream.bytes();
-    for (const DevBuf* b : bufs) s += (int64_t)b->bytes;
+    int64_t s = p->stream.bytes() + (int64_t)(p->slab.bytes + p->slab2.bytes);
+    for (const DevBuf* b : bufs)
+        if (!b->view) s += (int64_t)b->bytes;
     return s;
 }
 

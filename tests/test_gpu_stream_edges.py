@@ -264,3 +264,30 @@ def test_float32_map_folds_from_the_same_doubles(dev):
         torch.cuda.synchronize()
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+def test_retiling_a_device_built_plan_holds_what_it_reports(dev):
+    """A plan built on the device has its arrays cut from shared allocations: a
+    change of tiling puts the new band arrays in the old ones' place, and
+    device_bytes is what the plan takes from the device."""
+    say("retile device built")
+    az = azint()
+    n = 1500
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info(dev)[0]
+    plan = az.Plan.on_device(n, n, n, device=dev)
+    x = torch.rand(n * n, device=dev, dtype=torch.float64)
+    ref = plan.integrate(x)
+    torch.cuda.synchronize()
+    slack = 16 << 20
+    first = plan.device_bytes()
+    held = free - torch.cuda.mem_get_info(dev)[0]
+    for tile_nnz in (1024, 4096, 512, 8192, 0):
+        plan.set_tiling(tile_nnz=tile_nnz)
+        out = plan.integrate(x)
+        torch.cuda.synchronize()
+        assert abs(plan.device_bytes() - first) < slack, tile_nnz
+        assert free - torch.cuda.mem_get_info(dev)[0] < held + slack, tile_nnz
+        for a, b in zip(out, ref):
+            assert ((a - b).abs() <= 8 * n * 2.0 ** -53 * b.abs()).all()
+    assert first < held + slack
