@@ -88,6 +88,7 @@ MAPS = [
     (1001, 1003, 500.5, 501.5, 400, 360, "bbox"),    # the beam inside a pixel: it lies in all wedges
     (997, 1009, -20.0, 400.0, 80, 90, "bbox"),       # the beam off the detector
     (1024, 980, 500.0, 490.0, 50, 24, "full"),
+    (1451, 1453, 725.5, 726.5, 1740, 360, "bbox"),   # the beam's pixel: more runs than a window holds
 ]
 KINDS = [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "kahan32")]
 
@@ -291,3 +292,103 @@ def test_retiling_a_device_built_plan_holds_what_it_reports(dev):
         for a, b in zip(out, ref):
             assert ((a - b).abs() <= 8 * n * 2.0 ** -53 * b.abs()).all()
     assert first < held + slack
+
+
+@pytest.mark.parametrize("dtype,accum", KINDS, ids=["f64", "f32", "k32"])
+@pytest.mark.parametrize("npt", [1, 8, 16, 17])
+def test_many_tiles_in_few_bins(npt, dtype, accum, dev):
+    """A thousand tiles that all reach the one or two chunks of bins: the
+    reduction of the longest lists."""
+    say("few bins", npt, dtype, accum)
+    az = azint()
+    h, w = 1000, 1010
+    m = oracle_matrix(h, w, 480.3, 520.7, npt)
+    npd = np.float64 if dtype == torch.float64 else np.float32
+    plan = az.Plan(h, w, npt, center=(480.3, 520.7), dtype=dtype, accum=accum, device=dev)
+    gen = np.random.default_rng(npt)
+    x = gen.uniform(0, 1000, h * w).astype(npd)
+    tol = TOL64 if dtype == torch.float64 else TOL32_F64
+    check(plan.integrate(torch.from_numpy(x).to(dev)), m, x.astype(np.float64), tol, what="image")
+    raw = gen.integers(0, 1 << 20, h * w).astype(np.int32)
+    check(plan.integrate_raw(torch.from_numpy(raw).to(dev)), m, raw.astype(np.float64), tol,
+          what="raw")
+
+
+def _shifted(t, by):
+    """The same values at an address that is `by` elements past an aligned one."""
+    room = torch.zeros(t.numel() + by, dtype=t.dtype, device=t.device)
+    room[by:] = t
+    out = room[by:]
+    assert out.is_contiguous() and (out.data_ptr() - room.data_ptr()) == by * t.element_size()
+    return out
+
+
+@pytest.mark.parametrize("g", [(131, 143, 60.2, 70.9, 90, 0, "bbox"), MAPS[0]],
+                         ids=["profile", "map"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+def test_frames_aligned_to_one_element(g, dtype, dev):
+    """Frames, images and gradients that start one to three elements past an
+    aligned address give the bits of the aligned ones, to the last pixel."""
+    say("alignment", g, dtype)
+    az = azint()
+    n = g[0] * g[1]
+    kw = dict(center=g[2:4], dtype=dtype, device=dev)
+    plan = map_plan(g, dtype, "f64", dev) if g[5] else az.Plan(g[0], g[1], g[4], **kw)
+    gen = torch.Generator(device=dev).manual_seed(17)
+    counts = torch.randint(0, 30000, (n,), generator=gen, device=dev, dtype=torch.int32)
+    flat = 0.9 + 0.2 * torch.rand(n, generator=gen, device=dev, dtype=dtype)
+    plan.set_corrections(dark=(counts % 61).to(dtype), flat=flat)
+    kinds = [k for k in ("int16", "uint16", "int32", "uint32", "float32", "float64")
+             if hasattr(torch, k)]
+    for stage in ("fold_sum", "fold", "fuse") if not g[5] else (None,):
+        if stage:
+            plan.set_tiling(stage=stage)
+        for kind in kinds:
+            raw = counts.cpu().numpy().astype(kind)
+            raw = torch.from_numpy(raw).to(dev)
+            want = plan.integrate_raw(raw)
+            for by in (1, 2, 3):
+                got = plan.integrate_raw(_shifted(raw, by))
+                torch.cuda.synchronize()
+                for a, b in zip(got, want):
+                    assert torch.equal(a, b), (stage, kind, by)
+    x = counts.to(dtype)
+    want = plan.integrate(x)
+    grad = torch.randn(plan.npt, generator=gen, device=dev, dtype=dtype)
+    gx = plan.backward(want[2], grad)
+    for by in (1, 2, 3):
+        got = plan.integrate(_shifted(x, by))
+        into = _shifted(torch.zeros(n, dtype=dtype, device=dev), by)
+        plan.backward(want[2], _shifted(grad, by), out=into)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b), by
+        assert torch.equal(into, gx), by
+
+
+@pytest.mark.parametrize("dtype,accum", KINDS, ids=["f64", "f32", "k32"])
+@pytest.mark.parametrize("band", [16, 32])
+def test_balanced_runs_where_the_encoding_is_refused(band, dtype, accum, dev):
+    """Bins too fine for the stream encoding, in the library-sized tiling: four
+    or eight bands a workgroup over balanced runs, every stage and reduction."""
+    say("balanced runs", band, dtype, accum)
+    az = azint()
+    h, w, npt = 300, 310, 1100
+    m = oracle_matrix(h, w, 140.3, 160.7, npt)
+    assert m["indices"].size > 4.8 * h * w
+    npd = np.float64 if dtype == torch.float64 else np.float32
+    tol = TOL64 if dtype == torch.float64 else TOL32_F64
+    gen = np.random.default_rng(band)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    raw = gen.integers(60, 1 << 20, h * w).astype(np.int32)
+    dark, flat = gen.integers(0, 60, h * w).astype(npd), gen.uniform(0.9, 1.1, h * w).astype(npd)
+    plan = az.Plan(h, w, npt, center=(140.3, 160.7), dtype=dtype, accum=accum, device=dev,
+                   tile_nnz=0, band=band)
+    x = oracle.correct(raw, dark.astype(np.float64), flat.astype(np.float64), None, None)
+    for stage in ("fold_sum", "fold", "fuse"):
+        plan.set_tiling(stage=stage)
+        plan.set_corrections(dark=t(dark), flat=t(flat))
+        check(plan.integrate_raw(t(raw), empty=5.0), m, x, tol, empty=5.0, what=stage)
+    image = raw.astype(npd)
+    check(plan.integrate(t(image), empty=5.0), m, image.astype(np.float64), tol, empty=5.0,
+          what="image")
