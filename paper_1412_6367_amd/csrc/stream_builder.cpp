@@ -270,9 +270,9 @@ struct Builder {
             const Shape s = shapes[k];
             const int32_t ng = across(s) * down(s);
             if (ng > kStreamMaxBlocks) continue;
-            int32_t l = xk;
-            for (int32_t q = 0; q < 3; ++q)
-                l = block_copies(s, (int32_t)((int64_t)(ng - 1) * q / 2), l);
+            int32_t l = block_copies(s, 0, xk);
+            if (ng > 2) l = block_copies(s, (ng - 1) / 2, l);
+            if (ng > 1) l = block_copies(s, ng - 1, l);
             if ((int64_t)pitch << l > kStreamSlots) continue;
             const int64_t cost = (240 + 4 * (64 >> s.lgw)) * (int64_t)ng +
                                  16 * (((int64_t)pitch << l) / 64);
@@ -458,9 +458,9 @@ bool build_stream(const HostMatrix& m, int32_t h, int32_t w, int32_t tile_px, in
     const int32_t bands = (h + rows - 1) / rows;
     const int64_t per_band = (w + strip - 1) / strip;
     const int64_t units = bands * per_band;
-    const int32_t threads = (int32_t)std::max<int64_t>(
-        1, std::min({(int64_t)std::thread::hardware_concurrency(), (int64_t)kBuildThreads, units,
-                     m.npix / kThreadPix}));
+    int64_t want = std::min({(int64_t)kBuildThreads, units, m.npix / kThreadPix});
+    if (want > 1) want = std::min(want, (int64_t)std::thread::hardware_concurrency());
+    const int32_t threads = (int32_t)std::max<int64_t>(1, want);
     std::vector<Builder> part;
     part.reserve(threads);
     for (int32_t k = 0; k < threads; ++k) part.emplace_back(m, w, pix_off, bin_off);
