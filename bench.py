@@ -139,6 +139,25 @@ def bwd_bytes(nnz, npix, npt, es):
     return nnz * es + (npix + 1) * 4 + npix * 4 + npix * es + 2 * npt * es
 
 
+def image_bytes(streams, nnz, npix, npt, es):
+    """Bytes one integration of a corrected image is credited with: over the
+    stream encoding its coefficients, a 16-bit word and the image's value per
+    pixel, three outputs (a map's further wedges and partial sums are not
+    counted); else the CSR's."""
+    if streams:
+        return nnz * es + npix * (2 + es) + 3 * npt * es
+    return spmv_bytes(nnz, npix, npt, es)
+
+
+def adjoint_bytes(streams, nnz, npix, npt, es):
+    """Bytes one adjoint is credited with: over the stream encoding its
+    coefficients, a 16-bit word and the gradient per pixel, U and the upstream
+    gradient; else those of the pixel-major entries."""
+    if streams:
+        return nnz * es + npix * (2 + es) + 2 * npt * es
+    return bwd_bytes(nnz, npix, npt, es)
+
+
 def build_plans(insts, dtype, az, threads=16):
     def mk(inst):
         g = inst.geom
@@ -267,7 +286,7 @@ def pipeline_line(az, torch, np, synth, dev, dtype, steps, warmup, frames_n=4, a
     torch.cuda.synchronize()
     graph_ms = mean_event_ms(gev)
     del graphs
-    b = spmv_bytes(nnz, g.npix, inst.npt, es)
+    b = image_bytes(streamed(plan.layout(), plan.tiling()), nnz, g.npix, inst.npt, es)
     # raw + dark + norm read, corrected image written
     corr_b = g.npix * (4 + 3 * es)
     line = dict(npix=g.npix, npt=inst.npt, nnz=nnz, layout=plan.layout(), accum=accum,
@@ -391,7 +410,8 @@ def batch_line(az, torch, np, synth, dev, cfg, dtype, with_bwd, tune, reps=20):
                               graph_forward_frac=fb0 / (p_graph * 1e6) / HBM_PEAK_GBS)
             batch.set_tiling(**{k: tiling[k] for k in ("tile_nnz", "block", "variant", "grid",
                                                        "band", "stage")})
-    fb = spmv_bytes(batch.nnz, batch.npix, batch.npt, es)
+    streams = streamed("run", tiling)
+    fb = image_bytes(streams, batch.nnz, batch.npix, batch.npt, es)
     line = dict(instances=batch.n, npix=batch.npix, npt=batch.npt, nnz=batch.nnz,
                 tiling=tiling, forward_ms=fwd_ms, forward_gbs=fb / (fwd_ms * 1e6),
                 forward_frac=fb / (fwd_ms * 1e6) / HBM_PEAK_GBS,
@@ -400,7 +420,7 @@ def batch_line(az, torch, np, synth, dev, cfg, dtype, with_bwd, tune, reps=20):
     if with_bwd:
         _, _, _ = batch.forward(x, out=(I, W, U))
         bwd_ms = timed(lambda: batch.backward(U, gI, out=gx))
-        bb = bwd_bytes(batch.nnz, batch.npix, batch.npt, es)
+        bb = adjoint_bytes(streams, batch.nnz, batch.npix, batch.npt, es)
         line.update(backward_ms=bwd_ms, backward_gbs=bb / (bwd_ms * 1e6),
                     backward_frac=bb / (bwd_ms * 1e6) / HBM_PEAK_GBS,
                     graph_fwd_bwd_ms=graph_ms,
@@ -440,9 +460,10 @@ def adjoint_line(az, torch, np, synth, dev, reps=50):
     torch.cuda.synchronize()
     f, b = mean_event_ms(fw), mean_event_ms(bw)
     nnz = plan.nnz
+    streams = streamed(plan.layout(), plan.tiling())
     return dict(npix=g.npix, npt=inst.npt, nnz=nnz, forward_ms=f, backward_ms=b,
-                forward_gbs=spmv_bytes(nnz, g.npix, inst.npt, 8) / (f * 1e6),
-                backward_gbs=bwd_bytes(nnz, g.npix, inst.npt, 8) / (b * 1e6))
+                forward_gbs=image_bytes(streams, nnz, g.npix, inst.npt, 8) / (f * 1e6),
+                backward_gbs=adjoint_bytes(streams, nnz, g.npix, inst.npt, 8) / (b * 1e6))
 
 
 def _timed(torch, fn, reps=20):
@@ -548,7 +569,8 @@ def two_d_line(az, torch, np, synth, dev, nr=1000, na=360, reps=30):
     cold, _ = flushed_ms(torch, lambda: plan.integrate(x, out=outs), flush)
     del flush
     nnz = plan.nnz
-    by = spmv_bytes(nnz, g.npix, plan.npt, 8)
+    # encoded: a million pixels or more, seven entries per partial sum or further wedge
+    by = image_bytes(True, nnz, g.npix, plan.npt, 8)
     line = dict(npix=g.npix, npt_rad=nr, npt_azim=na, nnz=nnz, layout=plan.layout(),
                 build_s=build_s, device_build_s=device_build_s,
                 integrate_ms=warm, integrate_cold_ms=cold,

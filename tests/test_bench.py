@@ -81,3 +81,19 @@ def test_measured_traffic_follows_the_kernel_sources(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "kernel_source_hash", lambda: "1" * 64)
     assert bench.measured_traffic("c2_f64") is None
     assert bench.measured_traffic("no_such_workload") is None
+
+
+def test_byte_counts_of_the_stream_encoding():
+    """Images and gradients over the stream encoding are credited with what it
+    moves, fewer bytes than the CSR; other encodings with the CSR's."""
+    nnz, npix, npt = 28323554, 10001406, 3162
+    for es in (4, 8):
+        got = bench.image_bytes(True, nnz, npix, npt, es)
+        assert got == nnz * es + npix * (2 + es) + 3 * npt * es
+        assert got < bench.spmv_bytes(nnz, npix, npt, es)
+        assert bench.image_bytes(False, nnz, npix, npt, es) == bench.spmv_bytes(nnz, npix, npt, es)
+        got = bench.adjoint_bytes(True, nnz, npix, npt, es)
+        assert got == nnz * es + npix * (2 + es) + 2 * npt * es
+        assert got < bench.bwd_bytes(nnz, npix, npt, es)
+        assert bench.adjoint_bytes(False, nnz, npix, npt, es) == \
+            bench.bwd_bytes(nnz, npix, npt, es)
