@@ -339,10 +339,17 @@ struct StreamBufs {
 
 // Pixels per stream tile.  One round of the 2048 workgroups that 256 CUs keep
 // resident, but at least 1024 (four blocks of 256, one for each wavefront) and
-// at most 3072 (three for each): 512, 1024 and 2048 at 1043 x 981 float32
-// Kahan 15.1, 14.7 and 14.8 us a pass; 1536, 2560, 3072 and 4096 at 3162 x
-// 3163 float64 60.3, 54.8, 53.3 and 53.1 us, float32 in 1000 bins 31.9, 31.2,
-// 30.9 and 32.2 us.
+// at most 3072 (three for each).  Device time of a raw frame, both kernels, in
+// us (40 captured in a row), by pixels a tile:
+//                                    512   768   1024  2048  3072  4096
+//   100 x 100, 100 bins, float64     7.3   6.3   6.8   8.9   9.7   11.3
+//   512 x 512, 512, float32          8.0   8.0   8.7   8.2   10.9  11.2
+//   700 x 700, 700, float64          10.8  10.9  10.5  11.4  10.9  11.6
+//   1043 x 981, 1000, Kahan          13.8  10.7  10.5  10.5  11.7  11.7
+//   1500 x 1500, 1500, float32       16.6  14.9  14.6  13.3  14.1  14.1
+//   2048 x 2048, 2048, float64       29.8  29.1  26.9  25.2  25.0  25.9
+//   3162 x 3163, 1000, float32       39.0  30.6  26.6  27.5  27.9  28.0
+//   3162 x 3163, 3162, float64       74.4  64.1  59.0  54.4  53.1  53.2
 // Two-dimensional plans start from 4096 (64 rows of 64), halved where the
 // window asks for it.
 int32_t stream_tile_px(int64_t npix, bool two_d = false) {
