@@ -412,13 +412,12 @@ int azi_plan_run_schedule(const azi_plan* plan, int32_t tile_nnz, int64_t* nruns
  * these, or its average and its wide images of few rows together, or positions
  * past 2^31).  The per-run dark values of AZI_STAGE_FOLD are
  * per-pixel ones there, in the same types.
- * Two-dimensional plans of 1e6 pixels or more in AZI_LAYOUT_PIXEL with their
+ * Two-dimensional plans of 2e6 pixels or more in AZI_LAYOUT_PIXEL with their
  * default tiling are integrated from the stream encoding too (their tiles' bins
- * are radial bins of a few wedges); smaller ones would take longer to encode
- * than to build.  Not where its partial sums and the further wedges of its
- * pixels outweigh the entries (under 2.6 entries each; images that are
- * corrected already: 7 in float64, 4.6 in float32), nor with more than four
- * bins a pixel on average below 2e6 pixels.
+ * are radial bins of a few wedges), where their set-up hides the encoder (not
+ * with many wedges over few entries).  Not where the partial sums and the
+ * further wedges of its pixels outweigh the entries (under 2.6 entries each;
+ * images that are corrected already: 7 in float64, 4.6 in float32).
  * Raw frames are then integrated in one pass: A_bp / norm, rounded once when
  * the corrections are set, times raw - dark (as many roundings as A_bp times
  * (raw - dark) / norm), and the work image is not written.  azi_plan_stage and

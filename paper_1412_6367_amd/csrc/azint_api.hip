@@ -357,18 +357,27 @@ int32_t stream_tile_px(int64_t npix, bool two_d = false) {
     return (int32_t)std::max<int64_t>(1024, std::min<int64_t>(3072, npix / 2048));
 }
 
-// Pixels from which a two-dimensional plan is encoded.  The encoder runs on the
-// host, beside the copies of the matrix that the plan's set-up makes anyway;
-// from here on they hide it, below they are too short.  Set-up of a plan built
-// on the device, in us, without and with the encoding, 16 host threads:
-//                  36 wedges          360 wedges
-//   330 x 330      620 and 1880       1000 and 4200
-//   720 x 720      2100 and 5800      2800 and 9900
-//   1000 x 1000    4200 and 4000      13200 and 13400
-//   3162 x 3162    98000 and 99000    105000 and 107000
-// (14000 and 20500, 115000 and 160000 for the latter two with the encoder
-// after the copies.)
-constexpr int64_t kStreamMapPix = 1000000;
+// Whether a two-dimensional plan's set-up hides its encoder.  That runs on the
+// host, beside the copies of the matrix that the set-up makes anyway: these
+// take longer with the entries, the encoder with the wedges that a tile meets
+// (its halvings), and under two million pixels the host's memory is mostly warm
+// and the copies short.  Set-up of a plan built on the device, in ms, without
+// and with the encoding, 16 host threads, entries a pixel / wedges per side:
+//   1000 x 1000  1.21 / 0.04  3.0 and 4.0    2048 x 2048  1.20 / 0.02  33.5 and 33.6
+//                1.78 / 0.18  4.5 and 7.9                 1.33 / 0.18  36.3 and 37.6
+//                1.98 / 0.36  5.2 and 11.7                1.94 / 0.35  50.7 and 52.6
+//   1400 x 1400  1.20 / 0.03  6.3 and 6.5                 1.48 / 0.35  39.8 and 48.2
+//                1.40 / 0.26  18.5 and 21.1  3162 x 3162  1.12 / 0.11  72.5 and 75.2
+//                2.12 / 0.51  25.9 and 29.1               1.38 / 0.23  86.6 and 95.4
+// (the encoder after the copies: 160 instead of 107 for the 3162 x 3163 map of
+// 1000 x 360 bins, 105 without an encoding).  With the arrays of the copies
+// sized by threads too, 3162 x 3162: 67.5 ms, 85.5 for the last; 2048 x 2048 the
+// first three: 14.9, 34.0, 48.
+constexpr int64_t kStreamMapPix = 2000000;
+bool map_hidden(int64_t npix, int64_t nnz, int32_t azim) {
+    return npix >= kStreamMapPix &&
+           (double)nnz >= 0.8 * (double)npix + 2.6 * azim * std::sqrt((double)npix);
+}
 
 // The tilings that take the stream encoding where it applies: in the run
 // layout, one-dimensional plans, those sized by the library (tile_nnz 0, four
@@ -510,9 +519,6 @@ bool stream_cached(const azi::StreamMatrix& sm, int32_t dtype, bool again) {
 //   6.02 (n 2600)   49.4 and 93.0  41.5 and 61.0  46.2 and 42.7  34.9 and 40.1
 //   7.20 (n 3162)   64.4 and 129   52.8 and 109   60.5 and 65.8  43.9 and 54.8
 //   9.97 (n 1800)   36.0 and 52.6  29.8 and 50.1  33.9 and 37.3  25.5 and 38.6
-// Bins of over four entries a pixel cost both kernels' smaller frames more
-// (4.31, n 1000: raw 35.5 and 30.5, 31.2 and 32.7; 4.26, n 2048: 62.0 and 114).
-bool map_fine(int64_t npix, int64_t nnz) { return nnz > 4 * npix && npix < 2000000; }
 bool map_gains(int64_t nnz, int64_t side, bool images, int32_t dtype) {
     return nnz * 10 >= side * (!images ? 26 : dtype == AZI_F64 ? 70 : 46);
 }
@@ -826,10 +832,38 @@ int upload_bands(const azi::BandMatrix& bm, int32_t dtype, int device, DevBuf& p
 // Whether a plan is to have the stream encoding, where that applies.
 bool plan_streams(const azi_plan* p, int64_t nnz) {
     return stream_tiling(p->tiling, p->layout, p->m.two_d) &&
-           (p->m.two_d ? p->m.npix >= kStreamMapPix && !map_fine(p->m.npix, nnz)
+           (p->m.two_d ? map_hidden(p->m.npix, nnz, p->m.npt_azim)
                        : few_rows_tiles(p->geom.h, p->geom.w) <= kStreamFewRowsTiles &&
                              !stream_fine(p->m.npix, nnz));
 }
+
+// A host array of the matrix, sized (and its memory touched) by a thread of its
+// own: the copy into it then finds its pages.  Maps do so for the time that
+// placing the encoding takes after the copies, 2 to 5 ms at 1e7 pixels.
+struct SizeJob {
+    std::thread thread;
+    bool memory = false;
+    SizeJob() = default;
+    SizeJob(const SizeJob&) = delete;
+    SizeJob& operator=(const SizeJob&) = delete;
+    ~SizeJob() { wait(); }
+    template <class T>
+    void start(std::vector<T>& v, int64_t n) {
+        try {
+            thread = std::thread([this, &v, n] {
+                try {
+                    v.resize((size_t)n);
+                } catch (...) {
+                    memory = true;
+                }
+            });
+        } catch (...) {  // no thread to be had: sized where it is copied into
+        }
+    }
+    void wait() {
+        if (thread.joinable()) thread.join();
+    }
+};
 
 // The stream encoding of a plan's matrix, built by a thread of its own from
 // its pixel-major positions while the caller copies the rest of the matrix.
@@ -1685,8 +1719,12 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     }
     // maps: the positions come to the host first, and are encoded there while
     // the rest of the matrix is ordered and copied
+    SizeJob sizes[3];
     StreamJob job;
     if (streams) {
+        sizes[0].start(m.cdata, nnz);
+        sizes[1].start(m.indices, nnz);
+        sizes[2].start(m.data, nnz);
         int rc = download(m.colptr, p->colptr.p, npix + 1, s);
         if (rc == AZI_OK) rc = download(m.rowidx, p->rowidx.p, nnz, s);
         if (rc != AZI_OK) return rc;
@@ -1716,6 +1754,10 @@ int plan_build_device(azi_plan* p, int32_t npt, int32_t npt_azim, const double* 
     // host copy of the matrix, for export and for the host-side layouts
     int32_t scattered = 0;
     try {
+        for (SizeJob& z : sizes) {
+            z.wait();
+            if (z.memory) throw std::bad_alloc();
+        }
         int rc = streams ? AZI_OK : download(m.colptr, p->colptr.p, npix + 1, s);
         if (rc == AZI_OK && !streams) rc = download(m.rowidx, p->rowidx.p, nnz, s);
         if (rc == AZI_OK) rc = download(m.cdata, c64, nnz, s);

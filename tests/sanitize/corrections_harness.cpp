@@ -13,8 +13,8 @@ int main(int argc, char** argv) {
     const bool two_d = std::atoi(argv[1]) != 0;
     const int32_t dtype = std::atoi(argv[2]) ? AZI_F32 : AZI_F64;
     azi_geom g{};
-    g.h = two_d ? 1000 : 300;
-    g.w = two_d ? 1000 : 280;
+    g.h = two_d ? 1420 : 300;
+    g.w = two_d ? 1420 : 280;
     g.center_y_px = g.h * 0.45;
     g.center_x_px = g.w * 0.55;
     g.pixel_y_m = g.pixel_x_m = 1e-4;

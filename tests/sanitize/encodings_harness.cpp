@@ -66,8 +66,8 @@ int main(int argc, char** argv) {
     if (argc != 2) return 2;
     kind = std::atoi(argv[1]);
     azi_geom g{};
-    g.h = kind == 0 ? 1000 : 200;
-    g.w = kind == 0 ? 1000 : 180;
+    g.h = kind == 0 ? 1420 : 200;
+    g.w = kind == 0 ? 1420 : 180;
     g.center_y_px = g.h * 0.45;
     g.center_x_px = g.w * 0.55;
     g.pixel_y_m = g.pixel_x_m = 1e-4;
@@ -98,7 +98,7 @@ int main(int argc, char** argv) {
     int failed = 0;
     for (const bool leave : {true, false})
         for (const bool device : {true, false}) {
-            for (long k = 0;; k += device || kind != 0 ? 1 : 7) {
+            for (long k = 0;; k += device || kind != 0 ? 1 : 41) {
                 if (set(leave ? on : off) != AZI_OK) return 2;
                 if (device) fake::fail_in = k;
                 else new_in = k;
@@ -122,7 +122,7 @@ int main(int argc, char** argv) {
                 if (over) break;
             }
         }
-    for (long k = 0; kind == 0; k += 5) {  // an upload: the encoder beside the copies
+    for (long k = 0; kind == 0; k += 37) {  // an upload: the encoder beside the copies
         new_in = k;
         int rc = AZI_OK;
         try {

@@ -81,13 +81,12 @@ def test_fine_bins(h, w, npt, dtype, accum, dev):
     assert torch.equal(a, b)
 
 
-# Maps of a million pixels or more, which are encoded: h, w, center_y, center_x,
-# npt, npt_azim, split
+# Maps that are encoded: h, w, center_y, center_x, npt, npt_azim, split
 MAPS = [
-    (1000, 1000, 500.3, 480.2, 60, 36, "bbox"),
-    (1001, 1003, 500.5, 501.5, 400, 360, "bbox"),    # the beam inside a pixel: it lies in all wedges
-    (997, 1009, -20.0, 400.0, 80, 90, "bbox"),       # the beam off the detector
-    (1024, 980, 500.0, 490.0, 50, 24, "full"),
+    (1420, 1420, 700.3, 680.2, 60, 36, "bbox"),
+    (1451, 1453, 725.5, 726.5, 580, 360, "bbox"),    # the beam inside a pixel: it lies in all wedges
+    (1409, 1427, -20.0, 600.0, 110, 90, "bbox"),     # the beam off the detector
+    (1441, 1390, 700.0, 690.0, 70, 24, "full"),
     (1451, 1453, 725.5, 726.5, 1740, 360, "bbox"),   # the beam's pixel: more runs than a window holds
 ]
 KINDS = [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "kahan32")]
@@ -188,7 +187,7 @@ def test_encoded_map_keeps_special_values_in_their_bins(dev):
     n = g[0] * g[1]
     x = np.random.default_rng(3).uniform(1, 50, n)
     ref = plan.integrate(torch.from_numpy(x).to(dev))[1].cpu().numpy()
-    beam = 500 * g[1] + 480
+    beam = 700 * g[1] + 680
     many = beam + 5  # a few pixels from the beam: in several wedges
     bad = {7 * g[1] + 13: np.nan, 600 * g[1] + 41: np.inf, many: -np.inf, n - 1: np.nan}
     for p, v in bad.items():
